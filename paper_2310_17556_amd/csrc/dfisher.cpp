@@ -300,6 +300,20 @@ dfi::GramPlan make_gram_plan(const dfisher_ctx* ctx, const float* S, int64_t n, 
   return dfi::gram_plan(n, m, lds, prec, al);
 }
 
+// Scratch of the one-launch Cholesky for nbatch matrices: the packed factors and the ticket.
+size_t chol_scratch_bytes(int64_t n, int64_t nbatch) {
+  return (size_t)nbatch * dfi::chol_pack_bytes(n) + dfi::CHOL_TICKET_BYTES;
+}
+
+// nbatch matrices factored in one launch when pack (chol_scratch_bytes) is there, else in place in a
+// chain of launches.
+hipError_t factor_launch(double* A, int64_t n, int64_t nbatch, int64_t sA, int64_t* info, int32_t* flag, double* dkk,
+                         double* pack, hipStream_t st) {
+  if (!pack) return dfi::potrf_launch_batched(A, n, nbatch, sA, info, flag, dkk, st);
+  auto* ticket = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(pack) + (size_t)nbatch * dfi::chol_pack_bytes(n));
+  return dfi::chol_launch_batched(A, n, nbatch, sA, info, flag, pack, ticket, st);
+}
+
 // Everything one factorisation + solve needs, carved from the workspace.
 struct SolveBufs {
   double* W;       // n x n, unshifted W (lower triangle)
@@ -319,6 +333,7 @@ struct SolveBufs {
   double* t;       // S^T y (m, FP64)
   double* Dinv;    // inverses of L's 64 x 64 diagonal blocks
   double* dkk;     // Cholesky scratch: current diagonal block inverse
+  double* pack;    // Cholesky scratch: the packed factor, then its ticket (in the Gram partials, free by then)
   double* tw;      // triangular-solve work vector (n)
   uint8_t* q8;     // scaled-FP8 codes of S (n x ldq), when the Gram is MXFP8
   uint8_t* sc8;    // their E8M0 scales (n x ldq/32)
@@ -359,6 +374,10 @@ SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const
   s.t = need_t ? c.take<double>((size_t)m) : nullptr;
   s.Dinv = c.take<double>(dfi::trsv_dinv_bytes(n) / sizeof(double));
   s.dkk = c.take<double>(dfi::POTRF_DKK_BYTES / sizeof(double));
+  // (8 slices or more of partial tiles always hold the packed factor's half matrix)
+  s.pack = !need_L && !s.W ? nullptr
+           : gp && gp->part_bytes >= chol_scratch_bytes(n, 1)
+               ? reinterpret_cast<double*>(s.gpart) : c.take<double>(chol_scratch_bytes(n, 1) / sizeof(double));
   s.tw = c.take<double>((size_t)n);
   s.ldq = dfi::fp8_ldq(m);
   const bool fp8 = gp && gp->prec == DFISHER_GRAM_MXFP8;
@@ -381,7 +400,7 @@ SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const
 // `spec`, if given, is enqueued right after the first attempt's factorisation and before the wait
 // for its status (work that depends on L, started speculatively so that the host enqueues it while
 // the device is still busy); *spec_ok tells whether that work saw the final factor.
-dfisher_status factor_with_policy(dfisher_ctx* ctx, const double* W, double* L, double* dkk, int64_t n, int policy,
+dfisher_status factor_with_policy(dfisher_ctx* ctx, const double* W, double* L, double* dkk, double* pack, int64_t n, int policy,
                                   double unit, hipStream_t st, double* shift_out, int64_t* info_out,
                                   int32_t* attempts_out, const std::function<dfisher_status()>& spec = {},
                                   bool* spec_ok = nullptr) {
@@ -394,7 +413,7 @@ dfisher_status factor_with_policy(dfisher_ctx* ctx, const double* W, double* L, 
   if (policy != DFISHER_SHIFT_NONE) HIP_TRY(dfi::diag_max(W, n, ctx->d_scalar, st));
   for (;;) {
     HIP_TRY(dfi::shift_copy(W, L, n, scale, ctx->d_scalar, st));
-    HIP_TRY(dfi::potrf_launch(L, n, ctx->d_info, ctx->d_flag, dkk, st));
+    HIP_TRY(factor_launch(L, n, 1, n * n, ctx->d_info, ctx->d_flag, dkk, pack, st));
     if (attempts == 0 && spec) DF_TRY(spec());
     HIP_TRY(hipMemcpyAsync(ctx->h_status, ctx->d_info, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     if (policy != DFISHER_SHIFT_NONE)
@@ -402,6 +421,7 @@ dfisher_status factor_with_policy(dfisher_ctx* ctx, const double* W, double* L, 
     HIP_TRY(hipStreamSynchronize(st));
     ++attempts;
     info = ctx->h_status[0];
+    if (info < 0) return fail(DFISHER_E_DEVICE, "the Cholesky gave up waiting for one of its own tiles");
     if (info == 0 || policy == DFISHER_SHIFT_NONE || attempts >= MAX_SHIFT_ATTEMPTS) break;
     if (!std::isfinite(ctx->h_scalar[0])) break;  // NaN/Inf in W: shifting cannot help
     scale = (scale == 0.0) ? base_scale : 8.0 * scale;
@@ -899,6 +919,11 @@ struct UnevenLayout {
   int64_t ntot = 0, nmax = 0, mmax = 0;
   SolveBufs shared{};                      // scratch reused by every problem (largest sizes)
   double *W = nullptr, *Dinv = nullptr, *dkk = nullptr, *dmax = nullptr;
+  bool packed = true;                      // room for the factors' packed copies (the one-launch Cholesky)
+  std::vector<int64_t> poff;               // doubles
+  double* pack = nullptr;
+  uint32_t* ticket = nullptr;
+  int64_t ntask = 0;
   double *b = nullptr, *d = nullptr, *y = nullptr, *z = nullptr, *r = nullptr, *wk = nullptr;
   double *zc = nullptr, *p = nullptr, *nq = nullptr, *zero = nullptr, *rz = nullptr;   // refinement (PCG)
   double *bb = nullptr, *rr = nullptr, *prev = nullptr, *resid = nullptr;   // per table entry
@@ -943,6 +968,9 @@ void uneven_layout(const dfisher_ctx* ctx, char* base, int32_t np, const float* 
   U.voff.assign((size_t)np, 0);
   U.woff.assign((size_t)np, 0);
   U.doff.assign((size_t)np, 0);
+  U.poff.assign((size_t)np, 0);
+  U.ntask = 0;
+  int64_t ptot = 0;
   U.ntot = U.nmax = U.mmax = 0;
   int64_t wtot = 0, dtot = 0;
   size_t gpart = 0, rpart = 0, cpart = 0, q8 = 0, sc8 = 0, planes = 0;
@@ -957,6 +985,9 @@ void uneven_layout(const dfisher_ctx* ctx, char* base, int32_t np, const float* 
     U.ntot += n[p];
     wtot += n[p] * n[p];
     dtot += (int64_t)(dfi::trsv_dinv_bytes(n[p]) / sizeof(double));
+    U.poff[(size_t)p] = ptot;
+    ptot += (int64_t)(dfi::chol_pack_bytes(n[p]) / sizeof(double));
+    U.ntask += dfi::chol_task_count(n[p]);
     U.nmax = std::max(U.nmax, n[p]);
     U.mmax = std::max(U.mmax, m[p]);
     gpart = std::max(gpart, U.gp.back().part_bytes);
@@ -1026,6 +1057,9 @@ void uneven_layout(const dfisher_ctx* ctx, char* base, int32_t np, const float* 
   U.W = c.take<double>((size_t)wtot);
   U.Dinv = c.take<double>((size_t)dtot);
   U.dkk = c.take<double>((size_t)np * 64 * 64);
+  if (U.ntask > 0x7FFFFFFF) U.packed = false;
+  U.pack = U.packed ? c.take<double>((size_t)ptot) : nullptr;
+  U.ticket = U.packed ? c.take<uint32_t>(dfi::CHOL_TICKET_BYTES / sizeof(uint32_t)) : nullptr;
   U.dmax = c.take<double>((size_t)np);
   U.b = c.take<double>((size_t)U.ntot);
   U.d = c.take<double>((size_t)U.ntot);
@@ -1088,7 +1122,7 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
                               const int64_t* lds, const float* const* v, const double* lambda, void* const* x,
                               const dfisher_options& o, const UnevenLayout& U, const std::vector<int32_t>& order,
                               const std::vector<int>& sw, const std::vector<int64_t>& nactive,
-                              const dfi::FactorJob* fjobs, const dfi::TrsvJob* tj_fwd, const dfi::TrsvJob* tj_bwd,
+                              const dfi::FactorJob* fjobs, const dfi::FactorTask* ftasks, const dfi::TrsvJob* tj_fwd, const dfi::TrsvJob* tj_bwd,
                               const dfi::TrsvJob* tj_bwd_c, const int64_t* seg, const int* cap, double tol,
                               bool predict, const std::vector<int32_t>& jpos, const GroupedPasses& G,
                               hipStream_t st) {
@@ -1143,8 +1177,9 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
       HIP_TRY(dfi::shift_add_copy(Wp, Wp, n[p], scale, U.dmax + p, 0.0, st));
     }
   }
-  // all Cholesky factorisations in the same launches (in place), then the diagonal-block inverses
-  HIP_TRY(dfi::potrf_launch_grouped(fjobs, np, U.nmax, st));
+  // all Cholesky factorisations in the same launch, then the diagonal-block inverses
+  if (U.packed) HIP_TRY(dfi::chol_launch_grouped(fjobs, np, U.nmax, ftasks, U.ntask, U.ticket, st));
+  else HIP_TRY(dfi::potrf_launch_grouped(fjobs, np, U.nmax, st));
   HIP_TRY(dfi::trsv_diag_inv_grouped(tj_fwd, np, U.nmax, st));
   const size_t vb = (size_t)U.ntot * sizeof(double);
   // y = L^-T L^-1 b for every problem (wk is each solve's reduced right-hand side)
@@ -1297,7 +1332,11 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   const int need_t = (max_sw > 0 || o.final_resid) ? 1 : 0;
   const bool want_f8 = o.sweeps != 0 && !o.final_resid && (o.flags & DFISHER_EXACT_APPLY) == 0;
   uneven_layout(ctx, nullptr, np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
-  DF_TRY(ensure_ws(ctx, U.bytes));
+  if (ensure_ws(ctx, U.bytes) != DFISHER_OK) {   // no room for the packed copies: the factorisations run in place
+    U.packed = false;
+    uneven_layout(ctx, nullptr, np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
+    DF_TRY(ensure_ws(ctx, U.bytes));
+  }
   uneven_layout(ctx, static_cast<char*>(ctx->ws), np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
   // largest problems first (their Gram kernels fill the device; small ones follow)
   std::vector<int32_t> order((size_t)np);
@@ -1324,7 +1363,9 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
     const int32_t p = jord[(size_t)j];
     const size_t q = (size_t)p;
     double* Wp = U.W + U.woff[q];
-    fj[(size_t)j] = dfi::FactorJob{Wp, n[p], U.info + p, U.flag + p, U.dkk + (int64_t)p * 64 * 64};
+    double* pk = U.packed ? U.pack + U.poff[q] : nullptr;
+    fj[(size_t)j] = dfi::FactorJob{Wp, n[p], U.info + p, U.flag + p, U.dkk + (int64_t)p * 64 * 64, pk,
+                                   pk ? dfi::chol_ready_at(pk, n[p]) : nullptr};
     tf[(size_t)j] = dfi::TrsvJob{Wp, U.Dinv + U.doff[q], n[p], U.wk + U.voff[q], U.z + U.voff[q]};
     tb[(size_t)j] = dfi::TrsvJob{Wp, U.Dinv + U.doff[q], n[p], U.wk + U.voff[q], U.y + U.voff[q]};
     tr[(size_t)j] = dfi::TrsvJob{Wp, U.Dinv + U.doff[q], n[p], U.wk + U.voff[q], U.zc + U.voff[q]};
@@ -1332,6 +1373,19 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
     seg[(size_t)(2 * j + 1)] = n[p];
     capj[(size_t)j] = sw[q];
     jpos[q] = j;
+  }
+  // the Cholesky's tasks of all problems: the longest remaining chains of block columns first
+  std::vector<dfi::FactorTask> ft;
+  if (U.packed) {
+    ft.reserve((size_t)U.ntask);
+    for (int64_t left = (U.nmax + 63) / 64; left > 0; --left)   // block columns left, this one included
+      for (int32_t j = 0; j < np; ++j) {
+        const int32_t nb = (int32_t)((fj[(size_t)j].n + 63) / 64), c = nb - (int32_t)left;
+        if (c < 0) continue;
+        ft.push_back(dfi::FactorTask{j, c, 0, 0});
+        for (int32_t i = 1; c > 0 && c + i < nb; ++i) ft.push_back(dfi::FactorTask{j, c, i, 0});
+      }
+    if ((int64_t)ft.size() != U.ntask) return fail(DFISHER_E_DEVICE, "Cholesky task table of the wrong length");
   }
   // grouped whole-line passes, in table order: per class the residual jobs (cap > 0) and the
   // conjugate-gradient jobs (cap > 1), and the matching residual-reduction jobs
@@ -1419,7 +1473,8 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   const size_t rrbytes = align_up(rres.size() * sizeof(dfi::ReduceJob));
   const size_t rcbytes = align_up(rcg.size() * sizeof(dfi::ReduceJob));
   const size_t gjbytes = align_up(gjobs.size() * sizeof(dfi::GramJob));
-  gbytes += rrbytes + rcbytes + gjbytes;
+  const size_t ftbytes = align_up(ft.size() * sizeof(dfi::FactorTask));
+  gbytes += rrbytes + rcbytes + gjbytes + ftbytes;
   const size_t fbytes = align_up(fj.size() * sizeof(dfi::FactorJob));
   const size_t tbytes = align_up(tf.size() * sizeof(dfi::TrsvJob));
   const size_t sbytes = align_up(seg.size() * sizeof(int64_t));
@@ -1438,6 +1493,7 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   HIP_TRY(hipMemcpyAsync(d_tr, tr.data(), tr.size() * sizeof(dfi::TrsvJob), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(d_seg, seg.data(), seg.size() * sizeof(int64_t), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(d_cap, capj.data(), capj.size() * sizeof(int), hipMemcpyHostToDevice, st));
+  const dfi::FactorTask* d_ft = nullptr;
   {
     char* gp = tb0 + fbytes + 3 * tbytes + sbytes + cbytes;
     for (int c = 0; c < 3; ++c) {
@@ -1463,6 +1519,10 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
     if (!gjobs.empty())
       HIP_TRY(hipMemcpyAsync(dgj, gjobs.data(), gjobs.size() * sizeof(dfi::GramJob), hipMemcpyHostToDevice, st));
     G.gram = dgj;
+    auto* dft = reinterpret_cast<dfi::FactorTask*>(gp + rrbytes + rcbytes + gjbytes);
+    if (!ft.empty())
+      HIP_TRY(hipMemcpyAsync(dft, ft.data(), ft.size() * sizeof(dfi::FactorTask), hipMemcpyHostToDevice, st));
+    d_ft = dft;
   }
   HIP_TRY(hipStreamSynchronize(st));   // the host tables go out of scope; the graph reads the device copies
 
@@ -1508,7 +1568,7 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
         bool ok = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
         dfisher_status se = DFISHER_OK;
         if (ok)
-          se = uneven_enqueue(ctx, np, S, n, m, lds, v, lambda, x, o, U, order, sw, nactive, d_fj, d_tf, d_tb, d_tr,
+          se = uneven_enqueue(ctx, np, S, n, m, lds, v, lambda, x, o, U, order, sw, nactive, d_fj, d_ft, d_tf, d_tb, d_tr,
                               d_seg, d_cap, tol, autos, jpos, G, ctx->cap_stream);
         if (ok) ok = hipStreamEndCapture(ctx->cap_stream, &graph) == hipSuccess && graph != nullptr;
         if (ok && se == DFISHER_OK) {
@@ -1528,7 +1588,7 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
     }
   }
   if (!ran)
-    DF_TRY(uneven_enqueue(ctx, np, S, n, m, lds, v, lambda, x, o, U, order, sw, nactive, d_fj, d_tf, d_tb, d_tr, d_seg,
+    DF_TRY(uneven_enqueue(ctx, np, S, n, m, lds, v, lambda, x, o, U, order, sw, nactive, d_fj, d_ft, d_tf, d_tb, d_tr, d_seg,
                           d_cap, tol, autos, jpos, G, st));
   std::vector<int64_t> hinfo((size_t)np);
   std::vector<double> hmax((size_t)np, 0.0), hres((size_t)(2 * np), -1.0), hrho((size_t)np, -1.0);
@@ -1551,6 +1611,7 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
     const size_t j = (size_t)jpos[(size_t)p];
     inf.resid = tol > 0.0 && sw[(size_t)p] > 0 ? hrho[j] : -1.0;
     inf.potrf_info = hinfo[(size_t)p];
+    if (inf.potrf_info < 0) return fail(DFISHER_E_DEVICE, "the Cholesky gave up waiting for one of its own tiles");
     inf.attempts = 1;
     inf.sweeps_done = sw[(size_t)p] > 0 ? hdone[j] : 0;
     if (tol > 0.0 && sw[(size_t)p] > 0 && !hmet[j] && inf.potrf_info == 0) unmet = true;
@@ -1799,11 +1860,20 @@ dfisher_status dfisher_potrf(dfisher_ctx* ctx, double* W, int64_t n, int64_t* in
   *info = 0;
   DeviceGuard g(ctx->device);
   hipStream_t st = as_stream(stream);
-  DF_TRY(ensure_ws(ctx, dfi::POTRF_DKK_BYTES));
-  HIP_TRY(dfi::potrf_launch(W, n, ctx->d_info, ctx->d_flag, static_cast<double*>(ctx->ws), st));
+  const size_t dkk_bytes = align_up(dfi::POTRF_DKK_BYTES);
+  double* pack = nullptr;
+  if (ensure_ws(ctx, dkk_bytes + chol_scratch_bytes(n, 1)) == DFISHER_OK)
+    pack = reinterpret_cast<double*>(static_cast<char*>(ctx->ws) + dkk_bytes);
+  else   // no room for the packed copy: in place
+    DF_TRY(ensure_ws(ctx, dkk_bytes));
+  HIP_TRY(factor_launch(W, n, 1, n * n, ctx->d_info, ctx->d_flag, static_cast<double*>(ctx->ws), pack, st));
   HIP_TRY(hipMemcpyAsync(ctx->h_status, ctx->d_info, sizeof(int64_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   *info = ctx->h_status[0];
+  if (*info < 0) {
+    *info = 0;
+    return fail(DFISHER_E_DEVICE, "the Cholesky gave up waiting for one of its own tiles");
+  }
   if (*info != 0) return fail(DFISHER_E_NOT_SPD, "Cholesky failed at pivot %lld", (long long)*info);
   HIP_TRY(dfi::zero_upper(W, n, st));
   return DFISHER_OK;
@@ -1910,7 +1980,7 @@ dfisher_status dfisher_factor_create(dfisher_ctx* ctx, const float* S, int64_t n
   dfisher_info inf{};
   inf.resid = -1.0;
   inf.w_resid = -1.0;
-  dfisher_status s = factor_with_policy(ctx, B.W, f->L, B.dkk, n, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift, &inf.potrf_info,
+  dfisher_status s = factor_with_policy(ctx, B.W, f->L, B.dkk, B.pack, n, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift, &inf.potrf_info,
                                        &inf.attempts);
   if (o.sweeps == DFISHER_SWEEPS_AUTO) {   // resolved once, with the factored shift known
     const double wmax = (o.shift_policy != DFISHER_SHIFT_NONE) ? ctx->h_scalar[0] : 0.0;
@@ -2079,7 +2149,7 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
     return DFISHER_OK;
   };
   bool spec_ok = false;
-  DF_TRY(factor_with_policy(ctx, B.W, B.L, B.dkk, n, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift,
+  DF_TRY(factor_with_policy(ctx, B.W, B.L, B.dkk, B.pack, n, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift,
                             &inf.potrf_info, &inf.attempts, first_solve, &spec_ok));
   if (!spec_ok) DF_TRY(first_solve());
   // DFISHER_SWEEPS_AUTO: measured, predictive stop at tol (default 1e-7), at most MAX_SWEEPS
@@ -2157,7 +2227,7 @@ dfisher_status dfisher_solve_rowspace(dfisher_ctx* ctx, const float* S, int64_t 
     return DFISHER_OK;
   };
   bool spec_ok = false;
-  DF_TRY(factor_with_policy(ctx, B.W, B.L, B.dkk, n, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift,
+  DF_TRY(factor_with_policy(ctx, B.W, B.L, B.dkk, B.pack, n, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift,
                             &inf.potrf_info, &inf.attempts, first_solve, &spec_ok));
   if (!spec_ok) DF_TRY(first_solve());
   const bool autos = o.sweeps == DFISHER_SWEEPS_AUTO;
@@ -2317,7 +2387,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
   clk.mark(3);
   dfisher_info inf{};
   inf.resid = -1.0;
-  DF_TRY(factor_with_policy(ctx, B.W, B.L, B.dkk, N, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift,
+  DF_TRY(factor_with_policy(ctx, B.W, B.L, B.dkk, B.pack, N, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift,
                             &inf.potrf_info, &inf.attempts));
   clk.mark(4);
   HIP_TRY(dfi::trsv_diag_inv(B.L, N, B.Dinv, st));
@@ -2390,6 +2460,9 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   const bool final8 = o.gram_prec == DFISHER_GRAM_MXFP8 && o.sweeps != 0 && (o.flags & DFISHER_EXACT_APPLY) == 0;
   // workspace: the single-solve buffers (Gram stage, retry scratch), nlam factors, their block
   // inverses and statuses, and the multi-vector buffers
+  // (packed: the factors' packed copies too, in the Gram partials where they fit)
+  bool packed = true;
+  double* packs = nullptr;
   auto layout = [&](char* base, SolveBufs& B, double*& Lall, double*& Dall, double*& dkk, int64_t*& dinfo,
                     int32_t*& dflag, MultiBufs& mb) {
     B = carve(base, n, m, &gp, rp, cp, true, false);
@@ -2399,6 +2472,10 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
     Lall = c.take<double>((size_t)(nlam * n * n));
     Dall = c.take<double>((size_t)nlam * dinv_el);
     dkk = c.take<double>((size_t)nlam * 64 * 64);
+    packs = nullptr;
+    if (packed)
+      packs = gp.part_bytes >= chol_scratch_bytes(n, nlam)
+                  ? reinterpret_cast<double*>(B.gpart) : c.take<double>(chol_scratch_bytes(n, nlam) / sizeof(double));
     dinfo = c.take<int64_t>((size_t)nlam);
     dflag = c.take<int32_t>((size_t)nlam);
     mb = carve_multi(c, n, m, nrhs, nvec, rm, o.sweeps != 0, final8, is_centered(o), nlam);
@@ -2409,7 +2486,13 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   int64_t* dinfo;
   int32_t* dflag;
   MultiBufs mb;
-  const size_t need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
+  size_t need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
+  // without the memory (or, in a capture, the workspace of the call before it) for the packed copies the
+  // factorisations run in place
+  if (capturing ? need > ctx->ws_bytes : ensure_ws(ctx, need) != DFISHER_OK) {
+    packed = false;
+    need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
+  }
   if (capturing) {   // no allocation inside a capture; the graph will hold the workspace's addresses
     if (need > ctx->ws_bytes)
       return fail(DFISHER_E_UNSUPPORTED,
@@ -2433,7 +2516,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   if (scale0 != 0.0) HIP_TRY(dfi::diag_max(B.W, n, ctx->d_scalar, st));
   for (int32_t l = 0; l < nlam; ++l)
     HIP_TRY(dfi::shift_add_copy(B.W, Lall + (int64_t)l * n * n, n, scale0, ctx->d_scalar, lambdas[l], st));
-  HIP_TRY(dfi::potrf_launch_batched(Lall, n, nlam, n * n, dinfo, dflag, dkk, st));
+  HIP_TRY(factor_launch(Lall, n, nlam, n * n, dinfo, dflag, dkk, packs, st));
   if (async) {   // nothing read back: the sweep count is fixed a priori, the statuses go to infos on the device
     const int sweeps = o.sweeps == DFISHER_SWEEPS_AUTO ? auto_sweeps(o.gram_prec, n, m, scale0, is_centered(o))
                                                        : o.sweeps;
@@ -2457,13 +2540,14 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
     inf.w_resid = -1.0;
     inf.attempts = 1;
     inf.potrf_info = hinfo[(size_t)l];
+    if (inf.potrf_info < 0) return fail(DFISHER_E_DEVICE, "the Cholesky gave up waiting for one of its own tiles");
     inf.shift = scale0 * dmax;
     double tau_rel = scale0;
     if (inf.potrf_info != 0 && o.shift_policy != DFISHER_SHIFT_NONE) {
       // rare: refactor this lambda alone with escalating shifts (B.L holds G + lambda_l I)
       HIP_TRY(dfi::add_diag_copy(B.W, B.L, n, lambdas[l], st));
       int32_t att = 0;
-      const dfisher_status s = factor_with_policy(ctx, B.L, Lall + (int64_t)l * n * n, B.dkk, n, o.shift_policy, unit,
+      const dfisher_status s = factor_with_policy(ctx, B.L, Lall + (int64_t)l * n * n, B.dkk, B.pack, n, o.shift_policy, unit,
                                                   st, &inf.shift, &inf.potrf_info, &att);
       inf.attempts += att;
       if (s != DFISHER_OK && s != DFISHER_E_NOT_SPD) return s;

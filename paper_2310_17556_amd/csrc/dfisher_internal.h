@@ -231,8 +231,27 @@ struct FactorJob {
   int64_t* info;     // 0 or the 1-based index of the first bad pivot
   int32_t* flag;     // stop flag
   double* dkk;       // 64 x 64 scratch
+  double* pack;      // chol_pack_bytes(n) scratch (chol_launch_grouped)
+  uint32_t* ready;   // chol_ready_at(pack, n)
 };
 hipError_t potrf_launch_grouped(const FactorJob* jobs_dev, int64_t njobs, int64_t nmax, hipStream_t st);
+
+// The same factorisations in one launch (chol.hip): tasks per 64 x 64 tile ordered by flags in
+// device memory. Needs scratch for a packed copy of the factor: pack, nbatch matrices of
+// chol_pack_bytes(n) each, and ticket, 2 words. A status of -1 says that a wait inside the launch gave up.
+constexpr size_t CHOL_TICKET_BYTES = 256;
+size_t chol_pack_bytes(int64_t n);
+uint32_t* chol_ready_at(double* pack, int64_t n);
+hipError_t chol_launch_batched(double* A, int64_t n, int64_t nbatch, int64_t sA, int64_t* info_dev, int32_t* flag_dev,
+                               double* pack, uint32_t* ticket, hipStream_t st);
+// Grouped: tasks_dev lists every job's tasks (chol_task of s = 0 .. chol_task_count(n) - 1 of each job), any
+// interleaving that keeps each job's order.
+struct FactorTask {
+  int32_t job, c, i, pad;
+};
+int64_t chol_task_count(int64_t n);
+hipError_t chol_launch_grouped(const FactorJob* jobs_dev, int64_t njobs, int64_t nmax, const FactorTask* tasks_dev,
+                               int64_t ntasks, uint32_t* ticket, hipStream_t st);
 
 // ----------------------------------------------------------------------------- triangular solves
 // Inverses of the 64 x 64 diagonal blocks of L and their transposes (Dinv: trsv_dinv_bytes(n)),
