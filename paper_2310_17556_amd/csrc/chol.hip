@@ -345,15 +345,20 @@ __device__ __forceinline__ bool solve_strip(f64x4 (&T)[4], const double* tile, c
   return ok;
 }
 
-// The finished strip of an off-diagonal tile into the row-major factor.
+// The finished strip of an off-diagonal tile into the row-major factor, and mirrored above the diagonal
+// (the triangular solves read both).
 __device__ __forceinline__ void store_strip(const f64x4 (&T)[4], double* A, int64_t n, int I, int J, int w, int lane) {
   const int64_t row = (int64_t)I * NB + 16 * w + (lane & 15);
   if (row >= n) return;
   double* ar = A + row * n + (int64_t)J * NB + (lane >> 4);
+  double* at = A + ((int64_t)J * NB + (lane >> 4)) * n + row;
 #pragma unroll
   for (int p = 0; p < 4; ++p)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) ar[16 * p + 4 * q] = T[p][q];
+    for (int q = 0; q < 4; ++q) {
+      ar[16 * p + 4 * q] = T[p][q];
+      at[(int64_t)(16 * p + 4 * q) * n] = T[p][q];
+    }
 }
 
 struct CholLds {

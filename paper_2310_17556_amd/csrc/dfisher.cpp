@@ -105,8 +105,8 @@ struct dfisher_factor {
   int64_t n = 0, m = 0, lds = 0;
   double lambda = 0.0;
   dfisher_options opt{};
-  double* L = nullptr;     // owned: n x n
-  double* Dinv = nullptr;  // owned: inverses of the 64 x 64 diagonal blocks of L
+  double* L = nullptr;     // owned: n x n, L^T above the diagonal
+  double* Dinv = nullptr;  // owned: inverses of the 128 x 128 diagonal blocks of L
   double shift = 0.0;
 };
 
@@ -305,11 +305,14 @@ size_t chol_scratch_bytes(int64_t n, int64_t nbatch) {
   return (size_t)nbatch * dfi::chol_pack_bytes(n) + dfi::CHOL_TICKET_BYTES;
 }
 
-// nbatch matrices factored in one launch when pack (chol_scratch_bytes) is there, else in place in a
+// nbatch matrices factored (L below the diagonal, L^T above it), in one launch when pack (chol_scratch_bytes) is there, else in place in a
 // chain of launches.
 hipError_t factor_launch(double* A, int64_t n, int64_t nbatch, int64_t sA, int64_t* info, int32_t* flag, double* dkk,
                          double* pack, hipStream_t st) {
-  if (!pack) return dfi::potrf_launch_batched(A, n, nbatch, sA, info, flag, dkk, st);
+  if (!pack) {
+    const hipError_t e = dfi::potrf_launch_batched(A, n, nbatch, sA, info, flag, dkk, st);
+    return e != hipSuccess ? e : dfi::tri_mirror_batched(A, n, nbatch, sA, st);
+  }
   auto* ticket = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(pack) + (size_t)nbatch * dfi::chol_pack_bytes(n));
   return dfi::chol_launch_batched(A, n, nbatch, sA, info, flag, pack, ticket, st);
 }
@@ -331,10 +334,10 @@ struct SolveBufs {
   double* nq;      // -(W p)
   double* zero;    // n zeros (right-hand side of the W p pass)
   double* t;       // S^T y (m, FP64)
-  double* Dinv;    // inverses of L's 64 x 64 diagonal blocks
+  double* Dinv;    // inverses of L's 128 x 128 diagonal blocks
   double* dkk;     // Cholesky scratch: current diagonal block inverse
   double* pack;    // Cholesky scratch: the packed factor, then its ticket (in the Gram partials, free by then)
-  double* tw;      // triangular-solve work vector (n)
+  double* tw;      // the triangular solves' tickets
   uint8_t* q8;     // scaled-FP8 codes of S (n x ldq), when the Gram is MXFP8
   uint8_t* sc8;    // their E8M0 scales (n x ldq/32)
   int64_t ldq;
@@ -372,13 +375,13 @@ SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const
   s.nq = c.take<double>((size_t)n);
   s.zero = c.take<double>((size_t)n);
   s.t = need_t ? c.take<double>((size_t)m) : nullptr;
-  s.Dinv = c.take<double>(dfi::trsv_dinv_bytes(n) / sizeof(double));
+  s.Dinv = c.take<double>(dfi::tri_dinv_bytes(n) / sizeof(double));
   s.dkk = c.take<double>(dfi::POTRF_DKK_BYTES / sizeof(double));
   // (8 slices or more of partial tiles always hold the packed factor's half matrix)
   s.pack = !need_L && !s.W ? nullptr
            : gp && gp->part_bytes >= chol_scratch_bytes(n, 1)
                ? reinterpret_cast<double*>(s.gpart) : c.take<double>(chol_scratch_bytes(n, 1) / sizeof(double));
-  s.tw = c.take<double>((size_t)n);
+  s.tw = c.take<double>(1);
   s.ldq = dfi::fp8_ldq(m);
   const bool fp8 = gp && gp->prec == DFISHER_GRAM_MXFP8;
   s.q8 = fp8 ? c.take<uint8_t>((size_t)(n * s.ldq)) : nullptr;
@@ -394,6 +397,12 @@ SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const
   s.use8 = final8 ? c.take<int>(2) : nullptr;   // [1]: the centered projection was applied
   s.bytes = c.off;
   return s;
+}
+
+// y = L^-T L^-1 b (scratch B.z).
+hipError_t apply_factor(const double* L, const double* Dinv, int64_t n, const double* b, const SolveBufs& B, double* y,
+                        hipStream_t st) {
+  return dfi::tri_solve_batched(L, n * n, Dinv, n, 1, 1, b, B.z, y, reinterpret_cast<uint32_t*>(B.tw), st);
 }
 
 // Cholesky of W (+ tau I) into L following the shift policy. Synchronises once per attempt.
@@ -426,7 +435,6 @@ dfisher_status factor_with_policy(dfisher_ctx* ctx, const double* W, double* L, 
     if (!std::isfinite(ctx->h_scalar[0])) break;  // NaN/Inf in W: shifting cannot help
     scale = (scale == 0.0) ? base_scale : 8.0 * scale;
   }
-  HIP_TRY(dfi::zero_upper(L, n, st));
   if (spec_ok) *spec_ok = attempts == 1 && info == 0;
   *shift_out = (info == 0 && policy != DFISHER_SHIFT_NONE) ? scale * ctx->h_scalar[0] : 0.0;
   *info_out = info;
@@ -530,8 +538,7 @@ dfisher_status solve_y_op(int64_t n, const double* L, const double* Dinv, const 
                           double tol = 0.0, int* done = nullptr, double* resid = nullptr, bool initial = true,
                           double predict = 0.0, bool* met = nullptr, const Final8* f8 = nullptr) {
   if (initial) {   // (else the caller has formed y = L^-T L^-1 b already)
-    HIP_TRY(dfi::trsv_launch(L, Dinv, n, 0, B.b, B.z, B.tw, st));
-    HIP_TRY(dfi::trsv_launch(L, Dinv, n, 1, B.z, B.y, B.tw, st));
+    HIP_TRY(apply_factor(L, Dinv, n, B.b, B, B.y, st));
     if (clk) clk->mark(5);
   }
   const bool measure = ctx && tol > 0.0;
@@ -556,8 +563,7 @@ dfisher_status solve_y_op(int64_t n, const double* L, const double* Dinv, const 
         rho = bb > 0.0 ? std::sqrt(rrh / bb) : (rrh > 0.0 ? INFINITY : 0.0);
         if (resid) *resid = rho;
       }
-      HIP_TRY(dfi::trsv_launch(L, Dinv, n, 0, B.r, B.z, B.tw, st));
-      HIP_TRY(dfi::trsv_launch(L, Dinv, n, 1, B.z, B.zc, B.tw, st));
+      HIP_TRY(apply_factor(L, Dinv, n, B.r, B, B.zc, st));
       bool stop = s >= sweeps;
       if (measure) {
         const double expect =
@@ -620,11 +626,12 @@ dfisher_status final_residual(dfisher_ctx* ctx, const float* S, int64_t n, int64
 
 // Many right-hand sides against nfac factors in shared launches (multi-vector passes over S, batched
 // triangular solves). Vector j = f * nrhs + r pairs factor f (L + f n^2, its block inverses at
-// Dinv + f trsv_dinv_bytes(n) / 8, damping lams[f]) with v_r = V + r ldv; x_j goes to X + j ldx.
+// Dinv + f tri_dinv_bytes(n) / 8, damping lams[f]) with v_r = V + r ldv; x_j goes to X + j ldx.
 // Per vector: y = W_f^-1 S v_r, `sweeps` FP64 refinement sweeps against the exact operator, then
 // x = (v_r - S^T y) / lambda_f. Needs nfac * nrhs <= 65535.
 struct MultiBufs {
-  double *Bs, *Bexp, *Y, *R, *D, *W1, *T, *T1, *Yi, *part, *part1;   // T1, part1: a second group
+  uint32_t* ticket;
+  double *Bs, *Bexp, *Y, *R, *D, *T, *T1, *Yi, *part, *part1;   // T1, part1: a second group
   double *Zc, *P, *NQ, *zero, *rz;   // refinement: M^-1 R, directions, -(W P), n zeros, r.z per vector
   // the final step through the FP8 codes (apply8.hip), when planned: S^T y carried per vector (Tacc)
   // and S^T p of the last directions (Uacc), both in the passes' T layout; step lengths; the
@@ -653,7 +660,7 @@ MultiBufs carve_multi(Carver& c, int64_t n, int64_t m, int64_t nrhs, int64_t nve
   b.Y = c.take<double>((size_t)(nvec * n));
   b.R = c.take<double>((size_t)(nvec * n));
   b.D = c.take<double>((size_t)(nvec * n));
-  b.W1 = c.take<double>((size_t)(nvec * n));
+  b.ticket = c.take<uint32_t>(2);
   const bool two = nvec > dfi::MULTI_VECS;   // passes take two groups of vectors at a time
   b.T = need_t ? c.take<double>((size_t)(m * dfi::MULTI_VECS)) : nullptr;
   b.T1 = need_t && two ? c.take<double>((size_t)(m * dfi::MULTI_VECS)) : nullptr;
@@ -707,8 +714,7 @@ dfisher_status multi_solve(const float* S, int64_t n, int64_t m, int64_t lds, in
   for (int64_t f = 0; f < nfac; ++f)
     HIP_TRY(hipMemcpyAsync(b.Bexp + f * nrhs * n, b.Bs, (size_t)(nrhs * n) * sizeof(double), hipMemcpyDeviceToDevice, st));
   // Y = L^-T L^-1 B for every vector
-  HIP_TRY(dfi::trsv_launch_batched(L, sL, Dinv, n, nvec, nrhs, 0, b.Bexp, b.D, b.W1, st));
-  HIP_TRY(dfi::trsv_launch_batched(L, sL, Dinv, n, nvec, nrhs, 1, b.D, b.Y, b.W1, st));
+  HIP_TRY(dfi::tri_solve_batched(L, sL, Dinv, n, nvec, nrhs, b.Bexp, b.D, b.Y, b.ticket, st));
   // refinement: OUT_j = RHS_j - lambda_j U_j - S (S^T U_j), MV vectors per pair of passes (the
   // conjugate-gradient sweeps of solve_y, for every vector at once; RHS = B for the residual of Y,
   // RHS = 0 for -(W P))
@@ -755,8 +761,7 @@ dfisher_status multi_solve(const float* S, int64_t n, int64_t m, int64_t lds, in
     HIP_TRY(dfi::fill_zero(b.zero, n, st));
     DF_TRY(w_pass(b.Y, b.Bexp, false, b.R, f8 ? b.Tacc : nullptr));
     for (int s = 1;; ++s) {
-      HIP_TRY(dfi::trsv_launch_batched(L, sL, Dinv, n, nvec, nrhs, 0, b.R, b.D, b.W1, st));
-      HIP_TRY(dfi::trsv_launch_batched(L, sL, Dinv, n, nvec, nrhs, 1, b.D, b.Zc, b.W1, st));
+      HIP_TRY(dfi::tri_solve_batched(L, sL, Dinv, n, nvec, nrhs, b.R, b.D, b.Zc, b.ticket, st));
       if (s >= sweeps) {
         if (!f8) HIP_TRY(dfi::axpy_many(b.Y, b.Zc, nvec * n, st));   // else the final step takes Zc
         break;
@@ -924,7 +929,8 @@ struct UnevenLayout {
   double* pack = nullptr;
   uint32_t* ticket = nullptr;
   int64_t ntask = 0;
-  double *b = nullptr, *d = nullptr, *y = nullptr, *z = nullptr, *r = nullptr, *wk = nullptr;
+  double *b = nullptr, *d = nullptr, *y = nullptr, *z = nullptr, *r = nullptr;
+  uint32_t* tick = nullptr;                // the triangular solves' tickets
   double *zc = nullptr, *p = nullptr, *nq = nullptr, *zero = nullptr, *rz = nullptr;   // refinement (PCG)
   double *bb = nullptr, *rr = nullptr, *prev = nullptr, *resid = nullptr;   // per table entry
   int *stop = nullptr, *done = nullptr, *met = nullptr;
@@ -984,7 +990,7 @@ void uneven_layout(const dfisher_ctx* ctx, char* base, int32_t np, const float* 
     U.doff[(size_t)p] = dtot;
     U.ntot += n[p];
     wtot += n[p] * n[p];
-    dtot += (int64_t)(dfi::trsv_dinv_bytes(n[p]) / sizeof(double));
+    dtot += (int64_t)(dfi::tri_dinv_bytes(n[p]) / sizeof(double));
     U.poff[(size_t)p] = ptot;
     ptot += (int64_t)(dfi::chol_pack_bytes(n[p]) / sizeof(double));
     U.ntask += dfi::chol_task_count(n[p]);
@@ -1066,7 +1072,7 @@ void uneven_layout(const dfisher_ctx* ctx, char* base, int32_t np, const float* 
   U.y = c.take<double>((size_t)U.ntot);
   U.z = c.take<double>((size_t)U.ntot);
   U.r = c.take<double>((size_t)U.ntot);
-  U.wk = c.take<double>((size_t)U.ntot);
+  U.tick = c.take<uint32_t>(2);
   U.zc = c.take<double>((size_t)U.ntot);
   U.p = c.take<double>((size_t)U.ntot);
   U.nq = c.take<double>((size_t)U.ntot);
@@ -1122,8 +1128,8 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
                               const int64_t* lds, const float* const* v, const double* lambda, void* const* x,
                               const dfisher_options& o, const UnevenLayout& U, const std::vector<int32_t>& order,
                               const std::vector<int>& sw, const std::vector<int64_t>& nactive,
-                              const dfi::FactorJob* fjobs, const dfi::FactorTask* ftasks, const dfi::TrsvJob* tj_fwd, const dfi::TrsvJob* tj_bwd,
-                              const dfi::TrsvJob* tj_bwd_c, const int64_t* seg, const int* cap, double tol,
+                              const dfi::FactorJob* fjobs, const dfi::FactorTask* ftasks, const dfi::TriJob* tj_y, const dfi::TriJob* tj_c,
+                              const int64_t* seg, const int* cap, double tol,
                               bool predict, const std::vector<int32_t>& jpos, const GroupedPasses& G,
                               hipStream_t st) {
   (void)ctx;
@@ -1179,14 +1185,13 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
   }
   // all Cholesky factorisations in the same launch, then the diagonal-block inverses
   if (U.packed) HIP_TRY(dfi::chol_launch_grouped(fjobs, np, U.nmax, ftasks, U.ntask, U.ticket, st));
-  else HIP_TRY(dfi::potrf_launch_grouped(fjobs, np, U.nmax, st));
-  HIP_TRY(dfi::trsv_diag_inv_grouped(tj_fwd, np, U.nmax, st));
-  const size_t vb = (size_t)U.ntot * sizeof(double);
-  // y = L^-T L^-1 b for every problem (wk is each solve's reduced right-hand side)
-  HIP_TRY(hipMemcpyAsync(U.wk, U.b, vb, hipMemcpyDeviceToDevice, st));
-  HIP_TRY(dfi::trsv_launch_grouped(tj_fwd, np, U.nmax, 0, st));    // wk -> z
-  HIP_TRY(hipMemcpyAsync(U.wk, U.z, vb, hipMemcpyDeviceToDevice, st));
-  HIP_TRY(dfi::trsv_launch_grouped(tj_bwd, np, U.nmax, 1, st));    // wk -> y
+  else {
+    HIP_TRY(dfi::potrf_launch_grouped(fjobs, np, U.nmax, st));
+    HIP_TRY(dfi::tri_mirror_grouped(fjobs, np, U.nmax, st));
+  }
+  HIP_TRY(dfi::tri_inv_grouped(tj_y, np, U.nmax, st));
+  // y = L^-T L^-1 b for every problem
+  HIP_TRY(dfi::tri_solve_grouped(tj_y, np, U.nmax, U.tick, st));
   // out_p = rhs_p - lambda_p u_p - S_p (S_p^T u_p) (FP64 accumulation): the residual of y_p
   // (rhs = b, u = y) or -(W_p p_p) (rhs = 0, u = p)
   // (skip: the problem's stop flag; its fused pass then reads nothing. The column pass + row pass
@@ -1251,10 +1256,7 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
       const int64_t act = nactive[(size_t)(s - 1)];
       const int64_t cont = s < max_sw ? nactive[(size_t)s] : 0;
       // zc = L^-T L^-1 r for the problems that may run this sweep
-      HIP_TRY(hipMemcpyAsync(U.wk, U.r, vb, hipMemcpyDeviceToDevice, st));
-      HIP_TRY(dfi::trsv_launch_grouped(tj_fwd, act, U.nmax, 0, st));     // wk -> z
-      HIP_TRY(hipMemcpyAsync(U.wk, U.z, vb, hipMemcpyDeviceToDevice, st));
-      HIP_TRY(dfi::trsv_launch_grouped(tj_bwd_c, act, U.nmax, 1, st));   // wk -> zc
+      HIP_TRY(dfi::tri_solve_grouped(tj_c, act, U.nmax, U.tick, st));
       HIP_TRY(dfi::pcg_decide(seg, 0, 0, act, s, c, U.zc, U.y, st));      // stop: y += zc
       if (cont == 0) break;
       if (s == 1) HIP_TRY(dfi::pcg_init(seg, 0, 0, cont, U.r, U.zc, U.p, U.rz, st, U.stop));
@@ -1344,8 +1346,8 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
     return (double)n[a] * (double)n[a] * (double)m[a] > (double)n[b] * (double)n[b] * (double)m[b];
   });
-  // job tables: factor jobs, forward solves (wk -> z, the first entry set also drives diag_inv)
-  // and backward solves (wk -> y for the first solve, wk -> zc inside sweeps: two tables)
+  // job tables: factor jobs, triangular solves (b -> y for the first, which also drives tri_inv, and
+  // r -> zc inside sweeps)
   // table entry j holds problem jord[j]: decreasing sweep count, so that the problems still
   // refining in sweep s are a prefix of the tables (nactive[s] entries)
   std::vector<int32_t> jord((size_t)np);
@@ -1355,7 +1357,7 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   for (int s = 0; s < max_sw; ++s)
     for (int32_t p = 0; p < np; ++p) nactive[(size_t)s] += sw[(size_t)p] > s ? 1 : 0;
   std::vector<dfi::FactorJob> fj((size_t)np);
-  std::vector<dfi::TrsvJob> tf((size_t)np), tb((size_t)np), tr((size_t)np);
+  std::vector<dfi::TriJob> ty((size_t)np), tc((size_t)np);
   std::vector<int64_t> seg((size_t)(2 * np));   // refinement vectors in table order: (offset, length)
   std::vector<int> capj((size_t)np);               // sweep cap in table order
   std::vector<int32_t> jpos((size_t)np);           // table entry of each problem
@@ -1366,9 +1368,9 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
     double* pk = U.packed ? U.pack + U.poff[q] : nullptr;
     fj[(size_t)j] = dfi::FactorJob{Wp, n[p], U.info + p, U.flag + p, U.dkk + (int64_t)p * 64 * 64, pk,
                                    pk ? dfi::chol_ready_at(pk, n[p]) : nullptr};
-    tf[(size_t)j] = dfi::TrsvJob{Wp, U.Dinv + U.doff[q], n[p], U.wk + U.voff[q], U.z + U.voff[q]};
-    tb[(size_t)j] = dfi::TrsvJob{Wp, U.Dinv + U.doff[q], n[p], U.wk + U.voff[q], U.y + U.voff[q]};
-    tr[(size_t)j] = dfi::TrsvJob{Wp, U.Dinv + U.doff[q], n[p], U.wk + U.voff[q], U.zc + U.voff[q]};
+    double* Dp = U.Dinv + U.doff[q];
+    ty[(size_t)j] = dfi::TriJob{Wp, Dp, n[p], U.b + U.voff[q], U.z + U.voff[q], U.y + U.voff[q], nullptr};
+    tc[(size_t)j] = dfi::TriJob{Wp, Dp, n[p], U.r + U.voff[q], U.z + U.voff[q], U.zc + U.voff[q], U.stop + j};
     seg[(size_t)(2 * j)] = U.voff[q];
     seg[(size_t)(2 * j + 1)] = n[p];
     capj[(size_t)j] = sw[q];
@@ -1476,26 +1478,24 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   const size_t ftbytes = align_up(ft.size() * sizeof(dfi::FactorTask));
   gbytes += rrbytes + rcbytes + gjbytes + ftbytes;
   const size_t fbytes = align_up(fj.size() * sizeof(dfi::FactorJob));
-  const size_t tbytes = align_up(tf.size() * sizeof(dfi::TrsvJob));
+  const size_t tbytes = align_up(ty.size() * sizeof(dfi::TriJob));
   const size_t sbytes = align_up(seg.size() * sizeof(int64_t));
   const size_t cbytes = align_up(capj.size() * sizeof(int));
-  DF_TRY(ensure_tbuf(ctx, fbytes + 3 * tbytes + sbytes + cbytes + gbytes));
+  DF_TRY(ensure_tbuf(ctx, fbytes + 2 * tbytes + sbytes + cbytes + gbytes));
   char* tb0 = static_cast<char*>(ctx->tbuf);
   auto* d_fj = reinterpret_cast<dfi::FactorJob*>(tb0);
-  auto* d_tf = reinterpret_cast<dfi::TrsvJob*>(tb0 + fbytes);
-  auto* d_tb = reinterpret_cast<dfi::TrsvJob*>(tb0 + fbytes + tbytes);
-  auto* d_tr = reinterpret_cast<dfi::TrsvJob*>(tb0 + fbytes + 2 * tbytes);
-  auto* d_seg = reinterpret_cast<int64_t*>(tb0 + fbytes + 3 * tbytes);
-  auto* d_cap = reinterpret_cast<int*>(tb0 + fbytes + 3 * tbytes + sbytes);
+  auto* d_ty = reinterpret_cast<dfi::TriJob*>(tb0 + fbytes);
+  auto* d_tc = reinterpret_cast<dfi::TriJob*>(tb0 + fbytes + tbytes);
+  auto* d_seg = reinterpret_cast<int64_t*>(tb0 + fbytes + 2 * tbytes);
+  auto* d_cap = reinterpret_cast<int*>(tb0 + fbytes + 2 * tbytes + sbytes);
   HIP_TRY(hipMemcpyAsync(d_fj, fj.data(), fj.size() * sizeof(dfi::FactorJob), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(d_tf, tf.data(), tf.size() * sizeof(dfi::TrsvJob), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(d_tb, tb.data(), tb.size() * sizeof(dfi::TrsvJob), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(d_tr, tr.data(), tr.size() * sizeof(dfi::TrsvJob), hipMemcpyHostToDevice, st));
+  HIP_TRY(hipMemcpyAsync(d_ty, ty.data(), ty.size() * sizeof(dfi::TriJob), hipMemcpyHostToDevice, st));
+  HIP_TRY(hipMemcpyAsync(d_tc, tc.data(), tc.size() * sizeof(dfi::TriJob), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(d_seg, seg.data(), seg.size() * sizeof(int64_t), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(d_cap, capj.data(), capj.size() * sizeof(int), hipMemcpyHostToDevice, st));
   const dfi::FactorTask* d_ft = nullptr;
   {
-    char* gp = tb0 + fbytes + 3 * tbytes + sbytes + cbytes;
+    char* gp = tb0 + fbytes + 2 * tbytes + sbytes + cbytes;
     for (int c = 0; c < 3; ++c) {
       auto* dres = reinterpret_cast<dfi::LineJob*>(gp);
       auto* dcg = reinterpret_cast<dfi::LineJob*>(gp + lbytes[c]);
@@ -1568,8 +1568,7 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
         bool ok = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
         dfisher_status se = DFISHER_OK;
         if (ok)
-          se = uneven_enqueue(ctx, np, S, n, m, lds, v, lambda, x, o, U, order, sw, nactive, d_fj, d_ft, d_tf, d_tb, d_tr,
-                              d_seg, d_cap, tol, autos, jpos, G, ctx->cap_stream);
+          se = uneven_enqueue(ctx, np, S, n, m, lds, v, lambda, x, o, U, order, sw, nactive, d_fj, d_ft, d_ty, d_tc, d_seg, d_cap, tol, autos, jpos, G, ctx->cap_stream);
         if (ok) ok = hipStreamEndCapture(ctx->cap_stream, &graph) == hipSuccess && graph != nullptr;
         if (ok && se == DFISHER_OK) {
           hipGraphExec_t ex = nullptr;
@@ -1588,7 +1587,7 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
     }
   }
   if (!ran)
-    DF_TRY(uneven_enqueue(ctx, np, S, n, m, lds, v, lambda, x, o, U, order, sw, nactive, d_fj, d_ft, d_tf, d_tb, d_tr, d_seg,
+    DF_TRY(uneven_enqueue(ctx, np, S, n, m, lds, v, lambda, x, o, U, order, sw, nactive, d_fj, d_ft, d_ty, d_tc, d_seg,
                           d_cap, tol, autos, jpos, G, st));
   std::vector<int64_t> hinfo((size_t)np);
   std::vector<double> hmax((size_t)np, 0.0), hres((size_t)(2 * np), -1.0), hrho((size_t)np, -1.0);
@@ -1961,7 +1960,7 @@ dfisher_status dfisher_factor_create(dfisher_ctx* ctx, const float* S, int64_t n
   f->lambda = lambda;
   f->opt = o;
   if (hipMalloc(&f->L, (size_t)(n * n) * sizeof(double)) != hipSuccess ||
-      hipMalloc(&f->Dinv, dfi::trsv_dinv_bytes(n)) != hipSuccess) {
+      hipMalloc(&f->Dinv, dfi::tri_dinv_bytes(n)) != hipSuccess) {
     (void)hipGetLastError();
     if (f->L) (void)hipFree(f->L);
     delete f;
@@ -1990,7 +1989,7 @@ dfisher_status dfisher_factor_create(dfisher_ctx* ctx, const float* S, int64_t n
   inf.sweeps_done = f->opt.sweeps;
   if (info) *info = inf;
   if (s != DFISHER_OK) return cleanup(s);
-  if (dfi::trsv_diag_inv(f->L, n, f->Dinv, st) != hipSuccess)
+  if (dfi::tri_inv_batched(f->L, n * n, n, 1, f->Dinv, st) != hipSuccess)
     return cleanup(fail(DFISHER_E_DEVICE, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())));
   f->shift = inf.shift;
   *out = f;
@@ -2060,7 +2059,7 @@ dfisher_status dfisher_factor_solve_noalloc(const dfisher_factor* f, const float
     B.p = c.take<double>((size_t)n);
     B.nq = c.take<double>((size_t)n);
     B.zero = c.take<double>((size_t)n);
-    B.tw = c.take<double>((size_t)n);
+    B.tw = c.take<double>(1);
     return c.off;
   };
   SolveBufs B;
@@ -2093,6 +2092,7 @@ dfisher_status dfisher_factor_copy_L(const dfisher_factor* f, double* L, void* s
   DeviceGuard g(f->ctx->device);
   HIP_TRY(hipMemcpyAsync(L, f->L, (size_t)(f->n * f->n) * sizeof(double), hipMemcpyDeviceToDevice,
                          as_stream(stream)));
+  HIP_TRY(dfi::zero_upper(L, f->n, as_stream(stream)));   // the factor holds L^T there
   return DFISHER_OK;
 }
 
@@ -2142,9 +2142,8 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
   // the host waits for its status, and repeated only if that attempt was not the final one.
   auto first_solve = [&]() -> dfisher_status {
     clk.mark(4);
-    HIP_TRY(dfi::trsv_diag_inv(B.L, n, B.Dinv, st));
-    HIP_TRY(dfi::trsv_launch(B.L, B.Dinv, n, 0, B.b, B.z, B.tw, st));
-    HIP_TRY(dfi::trsv_launch(B.L, B.Dinv, n, 1, B.z, B.y, B.tw, st));
+    HIP_TRY(dfi::tri_inv_batched(B.L, n * n, n, 1, B.Dinv, st));
+    HIP_TRY(apply_factor(B.L, B.Dinv, n, B.b, B, B.y, st));
     clk.mark(5);
     return DFISHER_OK;
   };
@@ -2220,9 +2219,8 @@ dfisher_status dfisher_solve_rowspace(dfisher_ctx* ctx, const float* S, int64_t 
   inf.resid = -1.0;
   auto first_solve = [&]() -> dfisher_status {
     clk.mark(4);
-    HIP_TRY(dfi::trsv_diag_inv(B.L, n, B.Dinv, st));
-    HIP_TRY(dfi::trsv_launch(B.L, B.Dinv, n, 0, B.b, B.z, B.tw, st));
-    HIP_TRY(dfi::trsv_launch(B.L, B.Dinv, n, 1, B.z, B.y, B.tw, st));
+    HIP_TRY(dfi::tri_inv_batched(B.L, n * n, n, 1, B.Dinv, st));
+    HIP_TRY(apply_factor(B.L, B.Dinv, n, B.b, B, B.y, st));
     clk.mark(5);
     return DFISHER_OK;
   };
@@ -2390,7 +2388,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
   DF_TRY(factor_with_policy(ctx, B.W, B.L, B.dkk, B.pack, N, o.shift_policy, gram_unit(o.gram_prec, m), st, &inf.shift,
                             &inf.potrf_info, &inf.attempts));
   clk.mark(4);
-  HIP_TRY(dfi::trsv_diag_inv(B.L, N, B.Dinv, st));
+  HIP_TRY(dfi::tri_inv_batched(B.L, N * N, N, 1, B.Dinv, st));
   const bool autos = o.sweeps == DFISHER_SWEEPS_AUTO;
   const int sweeps = autos ? MAX_SWEEPS : o.sweeps;
   const double tol = autos && !(o.tol > 0.0) ? AUTO_TOL : o.tol;
@@ -2455,7 +2453,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   const dfi::RowMultiPlan rm = dfi::rowmulti_plan(n, m, lds);
   const int64_t nvec = (int64_t)nlam * nrhs;
-  const size_t dinv_el = dfi::trsv_dinv_bytes(n) / sizeof(double);
+  const size_t dinv_el = dfi::tri_dinv_bytes(n) / sizeof(double);
   // the final step through the codes of the Gram (apply8.hip) for every (lambda, rhs) pair
   const bool final8 = o.gram_prec == DFISHER_GRAM_MXFP8 && o.sweeps != 0 && (o.flags & DFISHER_EXACT_APPLY) == 0;
   // workspace: the single-solve buffers (Gram stage, retry scratch), nlam factors, their block
@@ -2520,7 +2518,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   if (async) {   // nothing read back: the sweep count is fixed a priori, the statuses go to infos on the device
     const int sweeps = o.sweeps == DFISHER_SWEEPS_AUTO ? auto_sweeps(o.gram_prec, n, m, scale0, is_centered(o))
                                                        : o.sweeps;
-    HIP_TRY(dfi::trsv_diag_inv_batched(Lall, n * n, n, nlam, Dall, st));
+    HIP_TRY(dfi::tri_inv_batched(Lall, n * n, n, nlam, Dall, st));
     DF_TRY(multi_solve(S, n, m, lds, nlam, Lall, Dall, lambdas, V, nrhs, ldv, X, ldx, o.x_fp64, sweeps, rm, mb, st,
                            final8 ? &mf8 : nullptr));
     if (infos) HIP_TRY(write_batch_infos(infos, nlam, dinfo, scale0, ctx->d_scalar, sweeps, st));
@@ -2562,7 +2560,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
     linf[(size_t)l].sweeps_done = sweeps;
     if (infos) infos[l] = linf[(size_t)l];
   }
-  HIP_TRY(dfi::trsv_diag_inv_batched(Lall, n * n, n, nlam, Dall, st));
+  HIP_TRY(dfi::tri_inv_batched(Lall, n * n, n, nlam, Dall, st));
   DF_TRY(multi_solve(S, n, m, lds, nlam, Lall, Dall, lambdas, V, nrhs, ldv, X, ldx, o.x_fp64, sweeps, rm, mb, st,
                            final8 ? &mf8 : nullptr));
   if (worst != DFISHER_OK) return fail(worst, "at least one lambda failed to factor (its x is not meaningful)");

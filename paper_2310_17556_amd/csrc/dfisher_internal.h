@@ -237,7 +237,7 @@ struct FactorJob {
 hipError_t potrf_launch_grouped(const FactorJob* jobs_dev, int64_t njobs, int64_t nmax, hipStream_t st);
 
 // The same factorisations in one launch (chol.hip): tasks per 64 x 64 tile ordered by flags in
-// device memory. Needs scratch for a packed copy of the factor: pack, nbatch matrices of
+// device memory. Also writes L^T above the diagonal blocks (see tri_solve). Needs scratch for a packed copy of the factor: pack, nbatch matrices of
 // chol_pack_bytes(n) each, and ticket, 2 words. A status of -1 says that a wait inside the launch gave up.
 constexpr size_t CHOL_TICKET_BYTES = 256;
 size_t chol_pack_bytes(int64_t n);
@@ -254,31 +254,37 @@ hipError_t chol_launch_grouped(const FactorJob* jobs_dev, int64_t njobs, int64_t
                                int64_t ntasks, uint32_t* ticket, hipStream_t st);
 
 // ----------------------------------------------------------------------------- triangular solves
-// Inverses of the 64 x 64 diagonal blocks of L and their transposes (Dinv: trsv_dinv_bytes(n)),
-// computed once per factor.
+// For a caller's L (dfisher_trsv): inverses of its 64 x 64 diagonal blocks and their transposes (Dinv:
+// trsv_dinv_bytes(n)).
 size_t trsv_dinv_bytes(int64_t n);
 hipError_t trsv_diag_inv(const double* L, int64_t n, double* Dinv, hipStream_t st);
 // y = L^-1 b (trans 0) or L^-T b (trans 1); work: n doubles, not aliasing b or y; b may alias y.
 hipError_t trsv_launch(const double* L, const double* Dinv, int64_t n, int trans, const double* b, double* y,
                        double* work, hipStream_t st);
-// Batched: nfac factors at L + f sL with their block inverses at Dinv + f trsv_dinv_bytes(n) / 8.
-hipError_t trsv_diag_inv_batched(const double* L, int64_t sL, int64_t n, int64_t nfac, double* Dinv, hipStream_t st);
-// nvec right-hand sides (vector j at b + j n, result at y + j n, work nvec x n) solved in the same
-// launches; vector j uses factor j / nper. nvec <= 65535.
-hipError_t trsv_launch_batched(const double* L, int64_t sL, const double* Dinv, int64_t n, int64_t nvec, int64_t nper,
-                               int trans, const double* b, double* y, double* work, hipStream_t st);
+// The same for the library's own factors, which are kept mirrored (L below the diagonal, L^T above it;
+// tri.hip). tri_inv: Dinv (tri_dinv_bytes(n) per factor), the 128 x 128 diagonal blocks' inverses and their
+// transposes, once per factor. tri_solve: y = L^-T L^-1 b for nvec vectors (vector j at j n, factor j / nper at
+// L + (j / nper) sL); z: nvec n doubles of scratch, ticket: 2 words of scratch; b must not alias z or y.
+size_t tri_dinv_bytes(int64_t n);
+hipError_t tri_inv_batched(const double* L, int64_t sL, int64_t n, int64_t nfac, double* Dinv, hipStream_t st);
+hipError_t tri_solve_batched(const double* L, int64_t sL, const double* Dinv, int64_t n, int64_t nvec, int64_t nper,
+                             const double* b, double* z, double* y, uint32_t* ticket, hipStream_t st);
 // Systems of different sizes in the same launches (device job table, njobs <= 65535; nmax = the
-// largest n). diag_inv: Dinv of each L. Solve: r holds the right-hand side on entry and is reduced
-// in place (it is the work vector); the solution goes to out (not aliasing r).
-struct TrsvJob {
+// largest n); a job whose skip (device int, may be null) is set is left alone.
+struct TriJob {
   const double* L;
   double* Dinv;
   int64_t n;
-  double* r;
-  double* out;
+  const double* b;
+  double* z;
+  double* y;
+  const int* skip;
 };
-hipError_t trsv_diag_inv_grouped(const TrsvJob* jobs_dev, int64_t njobs, int64_t nmax, hipStream_t st);
-hipError_t trsv_launch_grouped(const TrsvJob* jobs_dev, int64_t njobs, int64_t nmax, int trans, hipStream_t st);
+hipError_t tri_inv_grouped(const TriJob* jobs_dev, int64_t njobs, int64_t nmax, hipStream_t st);
+hipError_t tri_solve_grouped(const TriJob* jobs_dev, int64_t njobs, int64_t nmax, uint32_t* ticket, hipStream_t st);
+// The upper triangle of factors made in place (potrf_launch_*) := the transposed lower one.
+hipError_t tri_mirror_batched(double* A, int64_t n, int64_t nbatch, int64_t sA, hipStream_t st);
+hipError_t tri_mirror_grouped(const FactorJob* jobs_dev, int64_t njobs, int64_t nmax, hipStream_t st);
 
 // ----------------------------------------------------------------------------- refinement (PCG)
 // n-vector steps of conjugate gradients on W y = b preconditioned by the Gram's factor (pcg.hip).

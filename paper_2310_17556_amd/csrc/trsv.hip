@@ -1,5 +1,5 @@
-// Triangular solves with the Cholesky factor L (row-major n x n FP64, lower): the L^-1 and L^-T
-// applications of the right-to-left evaluation of S^T L^-T L^-1 S v (Section 2, after Algorithm 1).
+// Triangular solves with a Cholesky factor L (row-major n x n FP64, lower), dfisher_trsv: the L^-1 and
+// L^-T applications of the right-to-left evaluation of S^T L^-T L^-1 S v (Section 2, after Algorithm 1).
 //
 // Blocked by 64-row blocks, in two parts:
 //   * diag_inv: the inverse of every 64 x 64 diagonal block D_k = L_kk^-1 (one workgroup per
@@ -16,9 +16,8 @@
 //     launch; a launch costs a few microseconds however little it does, and the solve is a chain
 //     of them, so halving their number halves most of its time.
 // Every launch reads only the panel it needs; the whole solve reads the lower triangle once.
-// Batched form: grid dimension y indexes right-hand sides (vector j at offset j n); vector j uses
-// factor j / nper (L + (j / nper) sL, Dinv + (j / nper) sD), so several right-hand sides of one
-// factor and several factors share every launch.
+// This form takes a caller's L, of which only the lower triangle may be read; the library's own factors
+// are solved by tri.hip, which needs them mirrored.
 #include "dfisher_internal.h"
 
 #include <algorithm>
@@ -32,19 +31,8 @@ constexpr int LDP = NB + 1;
 // D_k = inverse of the lower-triangular 64 x 64 block L_kk (identity-padded past n).
 // One 64-lane workgroup per block; lane c computes column c: x_c = e_c, x_i = -(sum_{c<=l<i} L_il x_l)/L_ii.
 __global__ void __launch_bounds__(64)
-diag_inv_kernel(const double* __restrict__ L, int64_t n, double* __restrict__ Dinv, int64_t sL, int64_t sD,
-                const TrsvJob* __restrict__ jobs) {
+diag_inv_kernel(const double* __restrict__ L, int64_t n, double* __restrict__ Dinv) {
   __shared__ double Lk[NB * LDP];
-  if (jobs) {
-    const TrsvJob& j = jobs[blockIdx.y];
-    L = j.L;
-    Dinv = j.Dinv;
-    n = j.n;
-    if ((int64_t)blockIdx.x * NB >= n) return;
-  } else {
-    L += (int64_t)blockIdx.y * sL;
-    Dinv += (int64_t)blockIdx.y * sD;
-  }
   const int64_t k = blockIdx.x;
   const int64_t r0 = k * NB;
   const int c = threadIdx.x;
@@ -83,31 +71,15 @@ diag_inv_kernel(const double* __restrict__ L, int64_t n, double* __restrict__ Di
 // n); z: output. Grid: 1 + number of row blocks below b (at least 1). 256 threads.
 __global__ void __launch_bounds__(256)
 fwd_step2_kernel(const double* __restrict__ L, int64_t n, const double* __restrict__ Dinv, int64_t s,
-                 double* __restrict__ r, double* __restrict__ z, int64_t sL, int64_t sD, int64_t nper,
-                 const TrsvJob* __restrict__ jobs) {
+                 double* __restrict__ r, double* __restrict__ z) {
   __shared__ double za[NB], zb[NB], rbv[NB];
   __shared__ double part[4][NB];
   __shared__ double lpa[NB * LDP];   // this workgroup's piece of panel a: lpa[i * LDP + c] = L[J NB + i][a NB + c]
   __shared__ double lpb[NB * LDP];   // the same rows of panel b
   double* const lab = lpa;           // L_ba, read before the panel pieces are stored
-  if (jobs) {
-    const TrsvJob& j = jobs[blockIdx.y];
-    L = j.L;
-    Dinv = j.Dinv;
-    n = j.n;
-    r = j.r;
-    z = j.out;
-  } else {
-    const int64_t j = blockIdx.y, f = j / nper;
-    L += f * sL;
-    Dinv += f * sD;
-    r += j * n;
-    z += j * n;
-  }
   const int64_t nblk = (n + NB - 1) / NB;
   const int64_t a = 2 * s, b = a + 1;
   const bool hasb = b < nblk;
-  // grouped launches size the grid for the largest system
   if (a >= nblk || (int64_t)blockIdx.x >= (hasb ? nblk - b : 1)) return;
   const int tid = threadIdx.x;
   const int64_t ra = a * NB, rb = b * NB;
@@ -221,24 +193,9 @@ fwd_step2_kernel(const double* __restrict__ L, int64_t n, const double* __restri
 // (at least 1). 256 threads.
 __global__ void __launch_bounds__(256)
 bwd_step2_kernel(const double* __restrict__ L, int64_t n, const double* __restrict__ Dinv, int64_t t,
-                 double* __restrict__ r, double* __restrict__ y, int64_t sL, int64_t sD, int64_t nper,
-                 const TrsvJob* __restrict__ jobs) {
+                 double* __restrict__ r, double* __restrict__ y) {
   __shared__ double yh[NB], yl[NB], rl[NB];
   __shared__ double part[4][NB];
-  if (jobs) {
-    const TrsvJob& j = jobs[blockIdx.y];
-    L = j.L;
-    Dinv = j.Dinv;
-    n = j.n;
-    r = j.r;
-    y = j.out;
-  } else {
-    const int64_t j = blockIdx.y, f = j / nper;
-    L += f * sL;
-    Dinv += f * sD;
-    r += j * n;
-    y += j * n;
-  }
   const int64_t nblk = (n + NB - 1) / NB;
   const int64_t h = nblk - 1 - 2 * t;
   const int64_t l = h - 1;
@@ -340,62 +297,9 @@ static int64_t bwd2_grid(int64_t nblk, int64_t t) { return 1 + std::max<int64_t>
 // the diagonal-block inverses, then their transposes
 size_t trsv_dinv_bytes(int64_t n) { return 2 * (size_t)((n + NB - 1) / NB) * NB * NB * sizeof(double); }
 
-hipError_t trsv_diag_inv_batched(const double* L, int64_t sL, int64_t n, int64_t nfac, double* Dinv, hipStream_t st) {
-  if (nfac < 1 || nfac > 65535) return hipErrorInvalidValue;
-  const int64_t nblk = (n + NB - 1) / NB;
-  hipLaunchKernelGGL(diag_inv_kernel, dim3((unsigned)nblk, (unsigned)nfac), dim3(64), 0, st, L, n, Dinv, sL,
-                     (int64_t)(trsv_dinv_bytes(n) / sizeof(double)), (const TrsvJob*)nullptr);
-  return hipGetLastError();
-}
-
 hipError_t trsv_diag_inv(const double* L, int64_t n, double* Dinv, hipStream_t st) {
-  return trsv_diag_inv_batched(L, n * n, n, 1, Dinv, st);
-}
-
-hipError_t trsv_launch_batched(const double* L, int64_t sL, const double* Dinv, int64_t n, int64_t nvec, int64_t nper,
-                               int trans, const double* b, double* y, double* work, hipStream_t st) {
-  if (nvec < 1 || nvec > 65535 || nper < 1) return hipErrorInvalidValue;
   const int64_t nblk = (n + NB - 1) / NB;
-  const int64_t sD = (int64_t)(trsv_dinv_bytes(n) / sizeof(double));
-  const unsigned nv = (unsigned)nvec;
-  const int64_t tot = n * nvec;
-  hipLaunchKernelGGL(copy_vec_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, b, work, tot);
-  if (trans == 0) {
-    for (int64_t s = 0; 2 * s < nblk; ++s)
-      hipLaunchKernelGGL(fwd_step2_kernel, dim3((unsigned)fwd2_grid(nblk, s), nv), dim3(256), 0, st, L, n, Dinv, s, work,
-                         y, sL, sD, nper, (const TrsvJob*)nullptr);
-  } else {
-    for (int64_t t = 0; 2 * t < nblk; ++t)
-      hipLaunchKernelGGL(bwd_step2_kernel, dim3((unsigned)bwd2_grid(nblk, t), nv), dim3(256), 0, st, L, n, Dinv, t, work,
-                         y, sL, sD, nper, (const TrsvJob*)nullptr);
-  }
-  return hipGetLastError();
-}
-
-hipError_t trsv_diag_inv_grouped(const TrsvJob* jobs_dev, int64_t njobs, int64_t nmax, hipStream_t st) {
-  if (njobs < 1 || njobs > 65535) return hipErrorInvalidValue;
-  const int64_t nblk = (nmax + NB - 1) / NB;
-  hipLaunchKernelGGL(diag_inv_kernel, dim3((unsigned)nblk, (unsigned)njobs), dim3(64), 0, st, (const double*)nullptr,
-                     (int64_t)0, (double*)nullptr, (int64_t)0, (int64_t)0, jobs_dev);
-  return hipGetLastError();
-}
-
-hipError_t trsv_launch_grouped(const TrsvJob* jobs_dev, int64_t njobs, int64_t nmax, int trans, hipStream_t st) {
-  if (njobs < 1 || njobs > 65535) return hipErrorInvalidValue;
-  const int64_t nblk = (nmax + NB - 1) / NB;
-  const unsigned nj = (unsigned)njobs;
-  // every system starts its backward sweep at its own last block, so the largest sets the grids
-  if (trans == 0) {
-    for (int64_t s = 0; 2 * s < nblk; ++s)
-      hipLaunchKernelGGL(fwd_step2_kernel, dim3((unsigned)fwd2_grid(nblk, s), nj), dim3(256), 0, st,
-                         (const double*)nullptr, (int64_t)0, (const double*)nullptr, s, (double*)nullptr,
-                         (double*)nullptr, (int64_t)0, (int64_t)0, (int64_t)1, jobs_dev);
-  } else {
-    for (int64_t t = 0; 2 * t < nblk; ++t)
-      hipLaunchKernelGGL(bwd_step2_kernel, dim3((unsigned)bwd2_grid(nblk, t), nj), dim3(256), 0, st,
-                         (const double*)nullptr, (int64_t)0, (const double*)nullptr, t, (double*)nullptr,
-                         (double*)nullptr, (int64_t)0, (int64_t)0, (int64_t)1, jobs_dev);
-  }
+  hipLaunchKernelGGL(diag_inv_kernel, dim3((unsigned)nblk), dim3(64), 0, st, L, n, Dinv);
   return hipGetLastError();
 }
 
@@ -403,7 +307,16 @@ hipError_t trsv_launch_grouped(const TrsvJob* jobs_dev, int64_t njobs, int64_t n
 // b may alias y; work must not alias either.
 hipError_t trsv_launch(const double* L, const double* Dinv, int64_t n, int trans, const double* b, double* y,
                        double* work, hipStream_t st) {
-  return trsv_launch_batched(L, n * n, Dinv, n, 1, 1, trans, b, y, work, st);
+  const int64_t nblk = (n + NB - 1) / NB;
+  hipLaunchKernelGGL(copy_vec_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, b, work, n);
+  if (trans == 0) {
+    for (int64_t s = 0; 2 * s < nblk; ++s)
+      hipLaunchKernelGGL(fwd_step2_kernel, dim3((unsigned)fwd2_grid(nblk, s)), dim3(256), 0, st, L, n, Dinv, s, work, y);
+  } else {
+    for (int64_t t = 0; 2 * t < nblk; ++t)
+      hipLaunchKernelGGL(bwd_step2_kernel, dim3((unsigned)bwd2_grid(nblk, t)), dim3(256), 0, st, L, n, Dinv, t, work, y);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace dfi
