@@ -8,9 +8,9 @@
 //     and stores the FP32 partial tile. gram_reduce then adds the slices in FP64 in a fixed
 //     order (deterministic, and the FP32 error stays that of one slice).
 //   * XCD-aware mapping: workgroups are dealt round-robin to the 8 XCDs, so workgroup w runs on
-//     XCD w % 8. Each XCD gets its own group of slices, and consecutive workgroups on an XCD
-//     take different tiles of the same slice: tiles that run together read the same columns
-//     of S, which then come from that XCD's L2 instead of HBM.
+//     XCD w % 8. Each XCD gets its own run of work items in slice order, and consecutive workgroups
+//     on an XCD take different tiles of the same slice: tiles that run together read the same
+//     columns of S, which then come from that XCD's L2 instead of HBM.
 //   * Each workgroup has 8 waves in a 2 x 4 layout; a wave owns a 128 x 64 sub-tile as
 //     4 x 2 blocks of 32 x 32 MFMA accumulators (128 FP32 accumulators per lane).
 //   * Per k-step, 32 columns of the row panels S_I and S_J are loaded from global memory into
@@ -63,6 +63,24 @@ __device__ __forceinline__ int64_t uni64(int64_t x) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32));
   return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// The (slice, tile) work item of workgroup w: items in slice order, an eighth of them per XCD. False for
+// the few workgroups past the last item (the count need not be a multiple of 8).
+__host__ __device__ __forceinline__ int64_t items_per_xcd(int64_t ntri, int64_t nslice) { return (ntri * nslice + 7) >> 3; }
+__device__ __forceinline__ bool work_item(int64_t w, int64_t ntri, int64_t nslice, int64_t& slice, int64_t& tile) {
+  const int64_t per = items_per_xcd(ntri, nslice), local = w >> 3;
+  const int64_t item = (w & 7) * per + local;
+  if (local >= per || item >= ntri * nslice) return false;
+  slice = uni64(item / ntri);
+  tile = item - slice * ntri;
+  return true;
+}
+
+// Whether the reduction reads anything of the 32 x 32 block at (row, col) of a tile (rows and columns of
+// W below n, lower triangle): the others are not stored.
+__device__ __forceinline__ bool block_used(bool diag, int64_t rowA, int64_t rowB, int row, int col, int64_t n) {
+  return rowA + row < n && rowB + col < n && !(diag && col > row);
 }
 
 // Global -> register staging for one 256-row panel and one k-step.
@@ -152,13 +170,8 @@ gram_kernel(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int6
             int64_t nslice, int64_t kslice, float* __restrict__ part) {
   __shared__ Lds<PREC> sm;
 
-  // XCD-aware (slice, tile) assignment; nslice is a multiple of 8.
-  const int64_t w = blockIdx.x;
-  const int64_t xcd = w & 7;
-  const int64_t local = w >> 3;
-  const int64_t q = local / ntri;
-  const int64_t tile = local - q * ntri;
-  const int64_t slice = xcd * (nslice >> 3) + q;
+  int64_t slice, tile;
+  if (!work_item(blockIdx.x, ntri, nslice, slice, tile)) return;
   // odd slices negate A (see the alternating slice sign note of gram_kernel_v2)
   const float sgn = (slice & 1) ? -1.f : 1.f;
   const uint32_t bflip = (slice & 1) ? 0x80008000u : 0u;
@@ -276,11 +289,12 @@ gram_kernel(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int6
   for (int i = 0; i < IM; ++i)
 #pragma unroll
     for (int j = 0; j < IN; ++j)
+      if (block_used(diag, rowA, rowB, wr * BMW + i * 32, wc * BNW + j * 32, n))
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = wr * BMW + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
         const int col = wc * BNW + j * 32 + l32;
-        out[row * T + col] = active ? sgn * acc[i][j][r] : 0.f;
+        out[row * T + col] = sgn * acc[i][j][r];
       }
 }
 
@@ -432,12 +446,8 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
   __shared__ Stage st0;
   __shared__ Stage st1;
 
-  const int64_t w = blockIdx.x;
-  const int64_t xcd = w & 7;
-  const int64_t local = w >> 3;
-  const int64_t q = local / ntri;
-  const int64_t tile = local - q * ntri;
-  const int64_t slice = xcd * (nslice >> 3) + q;
+  int64_t slice, tile;
+  if (!work_item(blockIdx.x, ntri, nslice, slice, tile)) return;
   const float sgn = (slice & 1) ? -1.f : 1.f;
 
   int64_t ti, tj;
@@ -453,7 +463,6 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
   const int wr = wave >> 1, wc = wave & 1;
   const int half = lane >> 5;
   const int l32 = lane & 31;
-  const bool active = !(diag && wr == 0 && wc == 1);
 
   f32x16 acc[NB][NB];
 #pragma unroll
@@ -489,11 +498,12 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
+      if (block_used(diag, rowA, rowB, wr * WT + i * 32, wc * WT + j * 32, n))
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = wr * WT + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
         const int col = wc * WT + j * 32 + l32;
-        out[row * T + col] = active ? sgn * acc[i][j][r] : 0.f;
+        out[row * T + col] = sgn * acc[i][j][r];
       }
 }
 
@@ -615,11 +625,8 @@ __device__ __forceinline__ void gram_fp8_body(const uint8_t* __restrict__ q, con
                                               float* __restrict__ part, int64_t w) {
   __shared__ Stage stg0, stg1, stg2, stg3;
 
-  const int64_t xcd = w & 7;
-  const int64_t local = w >> 3;
-  const int64_t qq = uni64(local / ntri);
-  const int64_t tile = local - qq * ntri;
-  const int64_t slice = xcd * (nslice >> 3) + qq;
+  int64_t slice, tile;
+  if (!work_item(w, ntri, nslice, slice, tile)) return;
 
   int64_t ti, tj;
   tri_index(tile, ti, tj);
@@ -636,7 +643,6 @@ __device__ __forceinline__ void gram_fp8_body(const uint8_t* __restrict__ q, con
   const int wr = wave >> 1, wc = wave & 1;
   const int half = lane >> 5;
   const int l32 = lane & 31;
-  const bool active = !(diag && wr == 0 && wc == 1);
 
   f32x16 acc[NB][NB];
 #pragma unroll
@@ -809,11 +815,12 @@ __device__ __forceinline__ void gram_fp8_body(const uint8_t* __restrict__ q, con
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
+      if (block_used(diag, rowA, rowB, wr * WT + i * 32, wc * WT + j * 32, n))
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = wr * WT + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
         const int col = wc * WT + j * 32 + l32;
-        out[row * T + col] = active ? acc[i][j][r] : 0.f;
+        out[row * T + col] = acc[i][j][r];
       }
 }
 
@@ -931,12 +938,8 @@ gram_kernel_split(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ 
                   int64_t kcap, int64_t ntri, int64_t nslice, int64_t kslice, float* __restrict__ part) {
   __shared__ Stage stg0, stg1, stg2, stg3;
 
-  const int64_t w = blockIdx.x;
-  const int64_t xcd = w & 7;
-  const int64_t local = w >> 3;
-  const int64_t qq = uni64(local / ntri);
-  const int64_t tile = local - qq * ntri;
-  const int64_t slice = xcd * (nslice >> 3) + qq;
+  int64_t slice, tile;
+  if (!work_item(blockIdx.x, ntri, nslice, slice, tile)) return;
   const uint32_t bflip = (slice & 1) ? 0x80008000u : 0u;
 
   int64_t ti, tj;
@@ -954,7 +957,6 @@ gram_kernel_split(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ 
   const int wr = wave >> 1, wc = wave & 1;
   const int half = lane >> 5;
   const int l32 = lane & 31;
-  const bool active = !(diag && wr == 0 && wc == 1);
 
   f32x16 acc[NB][NB];
 #pragma unroll
@@ -1086,11 +1088,12 @@ gram_kernel_split(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ 
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
+      if (block_used(diag, rowA, rowB, wr * WT + i * 32, wc * WT + j * 32, n))
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = wr * WT + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
         const int col = wc * WT + j * 32 + l32;
-        out[row * T + col] = active ? sgn * acc[i][j][r] : 0.f;
+        out[row * T + col] = sgn * acc[i][j][r];
       }
 }
 
@@ -1098,38 +1101,75 @@ gram_kernel_split(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ 
 
 // W_ij = sum over slices of the partial tiles (FP64, slice order) for i > j, plus the products of
 // columns [ktail, m) that the tile kernel left out (FP64); W_ii = d_i + lambda.
-// mirror != 0 also writes W_ji. One workgroup covers 256 consecutive columns j of one row i.
-__global__ void gram_reduce_kernel(const float* __restrict__ part, int64_t n, int64_t ntri, int64_t nslice,
-                                   const double* __restrict__ d, double lambda, double* __restrict__ W,
-                                   int mirror, const float* __restrict__ S, int64_t lds, int64_t ktail, int64_t m) {
-  const int64_t nb = (n + 255) / 256;
-  const int64_t i = (int64_t)blockIdx.x / nb;
-  const int64_t j = ((int64_t)blockIdx.x - i * nb) * 256 + threadIdx.x;
-  if (j > i || i >= n) return;
-  double s;
-  if (i == j) {
-    s = d[i] + lambda;
-  } else {
-    const int64_t ti = i / T, tj = j / T;
-    const int64_t tile = ti * (ti + 1) / 2 + tj;
-    const int64_t off = (i - ti * T) * T + (j - tj * T);
-    s = 0.0;
-    // slices added in order; unrolled so that several slices' loads are in flight at once
-    const float* pp = part + tile * (int64_t)(T * T) + off;
-    const int64_t sstride = ntri * (int64_t)(T * T);
-    int64_t sl = 0;
-    for (; sl + 8 <= nslice; sl += 8) {
-      float v[8];
+// mirror != 0 also writes W_ji. A wave takes one row of a lower-triangle tile, a lane four consecutive
+// columns of it (16-byte loads), eight slices in flight. Bound by the partial tiles' HBM reads. SPLIT
+// (few tiles: the rows alone leave the chip idle): one row per workgroup, wave w a quarter of the slices,
+// the four sums added in LDS in wave order; else 16 rows per workgroup, so that it reads 16 KB of every
+// slice's tile in one piece. n = 4096, 32 slices (1.07 GB): 353 us with 4-byte loads a row per workgroup,
+// 266 now (4.0 TB/s); n = 256, 241 slices: 29 against 10. The line between the forms: at n = 1024 (10
+// tiles) both take 20 us, at n = 2048 (36) split takes 47, unsplit 34.
+constexpr int RED_ROWS = 16;
+template <bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 256 : 64 * RED_ROWS)
+gram_reduce_kernel(const float* __restrict__ part, int64_t n, int64_t ntri, int64_t nslice,
+                   const double* __restrict__ d, double lambda, double* __restrict__ W, int mirror,
+                   const float* __restrict__ S, int64_t lds, int64_t ktail, int64_t m) {
+  constexpr int ROWS = SPLIT ? 1 : RED_ROWS;
+  __shared__ double sums[SPLIT ? 4 : ROWS][T];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t tile = blockIdx.x / (T / ROWS);
+  const int r = (int)(blockIdx.x - tile * (T / ROWS)) * ROWS + (SPLIT ? 0 : wave);
+  int64_t ti, tj;
+  tri_index(tile, ti, tj);
+  ti = uni64(ti);
+  tj = uni64(tj);
+  const int64_t i = ti * T + r;
+  const int64_t sstride = ntri * (int64_t)(T * T / 4);
+  const int64_t j0 = tj * T + 4 * lane;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  if (i < n && j0 <= i && j0 < n) {   // (blocks above the diagonal or past n are not stored)
+    const f32x4* pp = reinterpret_cast<const f32x4*>(part + tile * (int64_t)(T * T) + r * T) + lane;
+    const int64_t s1 = SPLIT ? (wave + 1) * nslice / 4 : nslice;
+    int64_t sl = SPLIT ? wave * nslice / 4 : 0;
+    for (; sl + 8 <= s1; sl += 8) {
+      f32x4 v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) v[u] = pp[(sl + u) * sstride];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) s += (double)v[u];
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += (double)v[u][e];
     }
-    for (; sl < nslice; ++sl) s += (double)pp[sl * sstride];
-    for (int64_t k = ktail; k < m; ++k) s += (double)S[i * lds + k] * (double)S[j * lds + k];
+    if (sl < s1) {
+      // the last few: loaded together too, in place of the missing ones the last slice again, not added
+      f32x4 v[7];
+#pragma unroll
+      for (int u = 0; u < 7; ++u) v[u] = pp[min<int64_t>(sl + u, s1 - 1) * sstride];
+#pragma unroll
+      for (int u = 0; u < 7; ++u)
+        if (sl + u < s1)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[e] += (double)v[u][e];
+    }
   }
-  W[i * n + j] = s;
-  if (mirror && i != j) W[j * n + i] = s;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) sums[wave][4 * lane + e] = s[e];
+  __syncthreads();
+  if (i >= n) return;
+  // columns c, c + 64, ... of the row (split: one column per thread)
+#pragma unroll
+  for (int e = 0; e < (SPLIT ? 1 : 4); ++e) {
+    const int c = SPLIT ? (int)threadIdx.x : lane + 64 * e;
+    const int64_t j = tj * T + c;
+    if (j > i || j >= n) return;
+    double v = SPLIT ? sums[0][c] + sums[1][c] + sums[2][c] + sums[3][c] : sums[wave][c];
+    if (i == j) v = d[i] + lambda;
+    else
+      for (int64_t k = ktail; k < m; ++k) v += (double)S[i * lds + k] * (double)S[j * lds + k];
+    W[i * n + j] = v;
+    if (mirror && i != j) W[j * n + i] = v;
+  }
 }
 
 }  // namespace
@@ -1142,7 +1182,7 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
   p.prec = prec;
   p.ntile = (n + T - 1) / T;
   p.ntri = p.ntile * (p.ntile + 1) / 2;
-  // Slices per XCD (q): enough workgroups to fill 256 CUs several times with little tail,
+  // The base plan: slices per XCD (q), enough workgroups to fill 256 CUs several times with little tail,
   // while keeping at least ~2048 columns per slice.
   const int64_t maxq_cols = std::max<int64_t>(1, m / (8 * 2048));
   int64_t best_q = 1;
@@ -1159,14 +1199,47 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
       best_q = q;
     }
   }
-  if (q_override > 0) best_q = q_override;
-  p.nslice = 8 * best_q;
-  const int64_t kstep = (prec == 2) ? 64 : KS;
-  int64_t ks = (m + p.nslice - 1) / p.nslice;
-  ks = (ks + kstep - 1) / kstep * kstep;
-  if (ks < kstep) ks = kstep;
-  p.kslice = ks;
   p.ldh = (prec == 1 && aligned16 && split_mode != 0) ? split_ldh(m) : 0;
+  const int64_t cap = prec == 2 ? fp8_ldq(m) : (p.ldh > 0 ? p.ldh : m);   // columns the slices cover
+  const int64_t kstep = (prec == 2) ? 64 : KS;
+  auto columns = [&](int64_t ns) { return std::max<int64_t>(1, ((cap + ns - 1) / ns + kstep - 1) / kstep) * kstep; };
+  p.nslice = 8 * (q_override > 0 ? (int64_t)q_override : best_q);
+  if (q_override <= 0) {
+    // Then the cheapest of the base plan and the slice counts that just fill 1, 2, ... rounds of 256
+    // workgroups. A round takes the columns of a slice at the tile kernel's rate on a full chip, every
+    // work item writes and the reduction reads 256 KB of partials. (The base plan leaves most of the chip
+    // idle for small n, and a round nearly empty where ntri is a little over a multiple of 32: at
+    // n = 256, m = 1e5 FP32 48 workgroups took 550 us with the reduction, 241 take 140; at n = 2048, m = 1e4
+    // split-BF16 288 took 220, 504 take 167; at n = 4096, m = 1e5 FP8 32 slices took 1200, 9 take 905.) Measured rates, us a column and tile: FP32 0.27
+    // (0.34 unaligned), split-BF16 from planes 0.075, inside the kernel 0.16, FP8 0.0141.
+    // FP32 and split-BF16 never get fewer slices than the base plan: a slice is summed in FP32, and longer
+    // ones would round more. (The FP8 codes' own rounding is 1e4 times that of their sums.) Split-BF16
+    // keeps an even count: odd slices are negated against the accumulation's bias.
+    const double rate = prec == 2 ? 0.0141 : prec == 0 ? (aligned16 ? 0.27 : 0.34) : (p.ldh > 0 ? 0.075 : 0.16);
+    auto cost = [&](int64_t ns) {
+      const int64_t ks = columns(ns), items = p.ntri * ((cap + ks - 1) / ks);
+      return (double)((items + 255) / 256) * ((double)ks * rate + 3.0) + 0.145 * (double)items;
+    };
+    const int64_t lo = prec == 2 ? 8 : p.nslice;
+    double best = cost(p.nslice);
+    auto consider = [&](int64_t ns) {
+      if (prec == 1) ns &= ~(int64_t)1;
+      if (ns < lo || (ns > lo && columns(ns) < 256) || p.ntri * ns > 4352) return;
+      const double c = cost(ns);
+      if (c < best - 1e-9) {
+        best = c;
+        p.nslice = ns;
+      }
+    };
+    consider(lo);
+    for (int64_t r = 1; r < 8; ++r) consider(32 * r / p.ntri);   // (an eighth of the chip, ...)
+    for (int64_t r = 1; r <= 17; ++r) consider(256 * r / p.ntri);
+  }
+  p.kslice = columns(p.nslice);
+  if (q_override <= 0) {   // no slice past the last column
+    const int64_t used = (cap + p.kslice - 1) / p.kslice;
+    p.nslice = prec == 1 ? (used + 1) & ~(int64_t)1 : used;
+  }
   p.part_bytes = (size_t)p.nslice * (size_t)p.ntri * (size_t)(T * T) * sizeof(float);
   return p;
 }
@@ -1187,7 +1260,7 @@ void gram_q_candidates(int64_t n, int64_t m, size_t max_part_bytes, int* out, in
 
 hipError_t gram_launch_fp8(const GramPlan& p, const uint8_t* q, const uint8_t* sc, int64_t ldq, float* part,
                            hipStream_t st) {
-  const dim3 grid((unsigned)(p.nslice * p.ntri));
+  const dim3 grid((unsigned)(8 * items_per_xcd(p.ntri, p.nslice)));
   if ((ldq & 127) != 0 || ldq < p.m || p.nslice * p.kslice < ldq || (p.kslice & 63) != 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(v3::gram_kernel_fp8, grid, dim3(v3::NT), 0, st, q, sc, p.n, ldq, p.ntri, p.nslice, p.kslice,
                      part);
@@ -1202,7 +1275,7 @@ hipError_t gram_launch_fp8_grouped(const GramJob* jobs_dev, int njobs, int64_t n
 
 hipError_t gram_launch_split(const GramPlan& p, const uint16_t* hi, const uint16_t* lo, float* part, hipStream_t st) {
   if (p.prec != 1 || p.ldh <= 0 || (p.ldh & 63) != 0) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(p.nslice * p.ntri));
+  const dim3 grid((unsigned)(8 * items_per_xcd(p.ntri, p.nslice)));
   if (p.nslice * p.kslice < p.ldh || (p.kslice & 15) != 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(v4::gram_kernel_split, grid, dim3(v4::NT), 0, st, hi, lo, p.n, p.ldh, p.ntri, p.nslice,
                      p.kslice, part);
@@ -1229,7 +1302,7 @@ int64_t gram_tail_start(const GramPlan& p, const float* S) { return tail_start(p
 
 hipError_t gram_launch(const GramPlan& p, const float* S, float* part, hipStream_t st) {
   const bool vec = ((p.lds & 3) == 0) && ((reinterpret_cast<uintptr_t>(S) & 15) == 0);
-  const dim3 grid((unsigned)(p.nslice * p.ntri));
+  const dim3 grid((unsigned)(8 * items_per_xcd(p.ntri, p.nslice)));
   if (use_v2(p, S)) {
     hipLaunchKernelGGL((v2::gram_kernel_v2<0>), grid, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
   } else if (p.prec == 0) {
@@ -1245,10 +1318,12 @@ hipError_t gram_launch(const GramPlan& p, const float* S, float* part, hipStream
 hipError_t gram_reduce(const GramPlan& p, const float* S, const float* part, const double* d, double lambda,
                        double* W, int mirror, hipStream_t st) {
   const int64_t ktail = tail_start(p, S);   // first column the tile kernel left out
-  const int64_t nb = (p.n + 255) / 256;
-  const dim3 grid((unsigned)(nb * p.n));
-  hipLaunchKernelGGL(gram_reduce_kernel, grid, dim3(256), 0, st, part, p.n, p.ntri, p.nslice, d, lambda, W, mirror,
-                     S, p.lds, ktail, p.m);
+  if (p.ntri <= 16)   // n <= 1280
+    hipLaunchKernelGGL(gram_reduce_kernel<true>, dim3((unsigned)(p.ntri * T)), dim3(256), 0, st, part, p.n, p.ntri,
+                       p.nslice, d, lambda, W, mirror, S, p.lds, ktail, p.m);
+  else
+    hipLaunchKernelGGL(gram_reduce_kernel<false>, dim3((unsigned)(p.ntri * (T / RED_ROWS))), dim3(64 * RED_ROWS), 0, st,
+                       part, p.n, p.ntri, p.nslice, d, lambda, W, mirror, S, p.lds, ktail, p.m);
   return hipGetLastError();
 }
 
