@@ -160,7 +160,7 @@ def cpu_baseline(S, v, lam, m_sample):
 
 
 SHIFT = {"on_failure": "DFISHER_SHIFT_ON_FAILURE", "always": "DFISHER_SHIFT_ALWAYS", "none": "DFISHER_SHIFT_NONE"}
-GRAM_KERNEL = {"fp32": "gram_kernel_v2<0>", "bf16x3": "gram_kernel_split", "mxfp8": "gram_kernel_fp8"}
+GRAM_KERNEL = {"fp32": "gram_kernel_v2", "bf16x3": "gram_kernel_split", "mxfp8": "gram_kernel_fp8"}
 
 
 # HBM bytes per launch of the Gram tile kernel at the full workload, from rocprofv3 FETCH_SIZE /

@@ -30,6 +30,7 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -172,7 +173,11 @@ gram_kernel(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int6
 
   int64_t slice, tile;
   if (!work_item(blockIdx.x, ntri, nslice, slice, tile)) return;
-  // odd slices negate A (see the alternating slice sign note of gram_kernel_v2)
+  // Alternating slice sign: on odd k-slices the A operand is negated and the stored partial tile negated back. The bf16
+  // matrix-core accumulation shows a small sign-independent bias (low-order bits of the aligned addends are dropped toward
+  // minus infinity); it is the same for +A and -A, so it cancels between even and odd slices instead of adding up
+  // coherently over all entries (which would shift W along directions where many entries add, such as the all-ones
+  // direction of a column-centered S).
   const float sgn = (slice & 1) ? -1.f : 1.f;
   const uint32_t bflip = (slice & 1) ? 0x80008000u : 0u;
 
@@ -301,25 +306,28 @@ gram_kernel(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int6
 // ---------------------------------------------------------------------------------------------
 // Gram kernel v2 (16-byte aligned rows): asynchronous direct-to-LDS loads into a two-stage ring.
 //
-//   * Each k-step stages the FP32 columns [k, k+32) of the two 256-row panels with
-//     global_load_lds_dwordx4: every wave instruction moves 8 rows x 128 B straight from global
+//   * Each k-step stages the FP32 columns [k, k+32) of the two 256-row panels (of a diagonal tile's one panel: 64 columns)
+//     with buffer loads to LDS: every wave instruction moves 8 rows x 128 B straight from global
 //     memory to LDS (no register staging). Row r's eight 16-byte chunks are stored XOR-swizzled
 //     (LDS chunk p holds column chunk p ^ (r & 7)) so that fragment reads of 8 consecutive rows
 //     hit distinct banks.
 //   * Two LDS stages: the loads for step s+1 are in flight while step s is multiplied; one
 //     barrier per step.
 //   * 4 waves in a 2 x 2 layout, each owning a 128 x 128 sub-tile (4 x 4 blocks of 32 x 32
-//     accumulators). Split-BF16 fragments are formed when a wave reads its FP32 fragment from
-//     LDS: hi = bf16_rne(a), lo = bf16_rne(a - hi).
-//   * Rows beyond n load a valid row (their products only reach discarded outputs). The kernel
-//     covers columns [0, m4) with m4 = m rounded down to a multiple of 4; chunks past a slice end
-//     load zeros, and the FP64 reduction adds the products of the last m - m4 (< 4) columns.
-//   * Alternating slice sign: on odd k-slices the A operand is negated and the stored partial
-//     tile negated back. The bf16 matrix-core accumulation shows a small sign-independent bias
-//     (low-order bits of the aligned addends are dropped toward minus infinity); it is the same
-//     for +A and -A, so it cancels between even and odd slices instead of adding up coherently
-//     over all entries (which would shift W along directions where many entries add, such as
-//     the all-ones direction of a column-centered S).
+//     accumulators), or the 36 blocks of a diagonal tile's lower triangle, 9 per wave.
+//   * Rows beyond n and column chunks past a slice end lie outside the loads' buffers. The kernel
+//     covers columns [0, m4) with m4 = m rounded down to a multiple of 4; the FP64 reduction adds
+//     the products of the last m - m4 (< 4) columns.
+//   * Bound by the FP32 matrix rate, 64 cycles a product and SIMD. A 32-column step of 256 products takes 6.96 us where
+//     they alone need 6.83, a diagonal one of 64 columns and 288 products 7.89 (7.68). With 16 products' worth of idle
+//     diagonal blocks, sign multiplications of A between the products (they change nothing: these sums round
+//     symmetrically) and the loads' addresses in vector registers these took 7.97 and 15.9. Gram of 1024 x 10^6: 8.45 ms
+//     (10.44 before), 256 x 10^5: 87 us (129), 2048 x 2 10^5: 6.1 ms (7.4), of that 0.4 ms the uneven end of the launch.
+// vmcnt(N) with the other counters left alone (gfx9 encoding: vmcnt bits [3:0] and [15:14]).
+#define DFI_WAIT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
+// lgkmcnt(0) with the other counters left alone (lgkmcnt bits [11:8]).
+#define DFI_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4))
+
 namespace v2 {
 
 constexpr int NW = 4;
@@ -330,116 +338,29 @@ constexpr int PANEL = T * KS;           // floats per panel per stage (32 KB)
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-// Source of the zero chunks loaded past the end of a k-slice.
-__device__ __align__(16) float g_zero_chunk[4] = {0.f, 0.f, 0.f, 0.f};
-
-struct Stage {
+struct alignas(16) Stage {
   float a[PANEL];
   float b[PANEL];
 };
 
-// Issue the direct-to-LDS loads of one panel for one k-step. Wave w moves row groups
-// g = w, w + 4, ..., each of 8 rows.
-__device__ __forceinline__ void issue_panel(const float* __restrict__ S, int64_t lds, int64_t n, int64_t row0,
-                                            int64_t kcol, int64_t kend, float* panel) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int rsub = lane >> 3;        // row inside the 8-row group
-  const int p = lane & 7;            // LDS chunk position
-#pragma unroll
-  for (int i = 0; i < T / 8 / NW; ++i) {
-    const int g = wave + NW * i;
-    const int r = 8 * g + rsub;
-    const int c = p ^ (r & 7);       // column chunk this lane fetches
-    int64_t R = row0 + r;
-    if (R >= n) R = n - 1;
-    const int64_t col = kcol + 4 * c;
-    // kend is a multiple of 4 here: a chunk is either wholly inside the slice or wholly past it
-    const float* src = (col < kend) ? S + R * lds + col : g_zero_chunk;
-    __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(panel + 8 * g * KS), 16, 0, 0);
+// f(0) .. f(N - 1), the index a compile-time constant from the start: with a loop, unrolled only after the compiler has taken
+// the register arrays apart, LDS reads are split into words and lose their width and the name of their stage.
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
   }
 }
 
-// Read the 8 FP32 values of row r, step columns [c0, c0 + 8) (c0 a multiple of 8) from a
-// swizzled panel.
-__device__ __forceinline__ void read8(const float* panel, int r, int c0, float (&v)[8]) {
-  const int q0 = (c0 >> 2) ^ (r & 7);
-  const int q1 = ((c0 >> 2) + 1) ^ (r & 7);
-  const f32x4 x0 = *reinterpret_cast<const f32x4*>(panel + r * KS + 4 * q0);
-  const f32x4 x1 = *reinterpret_cast<const f32x4*>(panel + r * KS + 4 * q1);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    v[e] = x0[e];
-    v[4 + e] = x1[e];
-  }
-}
+// A diagonal tile's lower triangle has 36 of the 64 blocks of 32 x 32, as 36 unordered pairs of its 8 block rows. Wave w
+// takes 9 pairs that need each block row once: with F[t] the operand of block row (w + t) & 7, the pairs F[0] x F[0, 7, 6, 5],
+// F[4] x F[4, 3, 2, 1] and F[4] x F[0] (differences 0 .. 3 from rows w and w + 4, and the one pair of w at difference 4).
+// F[0]'s products that wrap around lie above the diagonal and are stored transposed.
+constexpr int NDIAG = 9;
+constexpr int DIAG_A[NDIAG] = {0, 0, 0, 0, 4, 4, 4, 4, 4};
+constexpr int DIAG_B[NDIAG] = {0, 7, 6, 5, 4, 3, 2, 1, 0};
 
-__device__ __forceinline__ void split8(const float (&v)[8], float sgn, bf16x8& hi, bf16x8& lo) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float a = v[e] * sgn;
-    const __bf16 h = (__bf16)a;
-    hi[e] = h;
-    lo[e] = (__bf16)(a - (float)h);
-  }
-}
-
-// One k-step of the wave's 128 x 128 sub-tile from the current LDS stage.
-template <int PREC>
-__device__ __forceinline__ void step_compute(const float* pa, const float* pb, int ra0, int rb0, int half, float sgn,
-                                             f32x16 (&acc)[NB][NB]) {
-  if constexpr (PREC == 1) {
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 8) {
-      // B fragments stay in registers for the substep; A fragments stream through, the next one
-      // read while the current one's products issue.
-      bf16x8 bh[NB], bl[NB];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        float v[8];
-        read8(pb, rb0 + j * 32, half * 16 + kk, v);
-        split8(v, 1.f, bh[j], bl[j]);
-      }
-      float va[8];
-      read8(pa, ra0, half * 16 + kk, va);
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        bf16x8 ah, al;
-        split8(va, sgn, ah, al);
-        if (i + 1 < NB) read8(pa, ra0 + (i + 1) * 32, half * 16 + kk, va);
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
-        }
-      }
-    }
-  } else {
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 8) {
-      float fb[NB][8];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) read8(pb, rb0 + j * 32, half * 16 + kk, fb[j]);
-      float fa[8];
-      read8(pa, ra0, half * 16 + kk, fa);
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        float a[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a[e] = fa[e] * sgn;
-        if (i + 1 < NB) read8(pa, ra0 + (i + 1) * 32, half * 16 + kk, fa);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], fb[j][e], acc[i][j], 0, 0, 0);
-      }
-    }
-  }
-}
-
-template <int PREC>
 __global__ void __launch_bounds__(NT, 1)
 gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntri, int64_t nslice,
                int64_t kslice, float* __restrict__ part) {
@@ -448,22 +369,178 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
 
   int64_t slice, tile;
   if (!work_item(blockIdx.x, ntri, nslice, slice, tile)) return;
-  const float sgn = (slice & 1) ? -1.f : 1.f;
 
   int64_t ti, tj;
   tri_index(tile, ti, tj);
+  ti = uni64(ti);
+  tj = uni64(tj);
   const bool diag = (ti == tj);
   const int64_t rowA = ti * T, rowB = tj * T;
-  const int64_t k0 = slice * kslice;
+  const int64_t k0 = uni64(slice * kslice);
   const int64_t kend = min(m & ~(int64_t)3, k0 + kslice);   // columns [m4, m) go to the reduction
-  const int64_t nsteps = (kend > k0) ? (kend - k0 + KS - 1) / KS : 0;
+  // a step is KS columns of both panels, or 2 KS columns of a diagonal tile's one panel: the same 16 loads a wave
+  const int64_t span = diag ? 2 * KS : KS;
+  const int64_t nsteps = (kend > k0) ? (kend - k0 + span - 1) / span : 0;
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = lane >> 5;
   const int l32 = lane & 31;
+  float* out = part + (slice * ntri + tile) * (int64_t)(T * T);
 
+  // Loads: instruction i of a panel carries rows 8 (wave + 4 i) .. + 7 of 32 columns, lane l row l / 8 and the column chunk
+  // (l % 8) ^ (row & 7). Its buffer begins at the first of these rows (64-bit scalar arithmetic) and ends behind the last
+  // row of S, and a lane whose chunk lies past the slice's end (a multiple of 4: a chunk is wholly inside or wholly past
+  // it) gets an offset outside every buffer: out of range reads nothing and gives zeros. Needs 8 lds * 4 < 2^32.
+  const int chunk = (lane & 7) ^ (lane >> 3);
+  const uint32_t rowbytes = (uint32_t)lds * 4;
+  const uint32_t voff = (uint32_t)(lane >> 3) * rowbytes + 16 * chunk;
+  const int64_t limA = kend - k0 - 4 * chunk, limB = diag ? limA - KS : limA;
+  const float* const baseA = S + (rowA + 8 * wave) * lds + k0;
+  const float* const baseB = S + (rowB + 8 * wave) * lds + (diag ? k0 + KS : k0);
+  const int leftA = (int)min(n - rowA, (int64_t)T) - 8 * wave, leftB = (int)min(n - rowB, (int64_t)T) - 8 * wave;
+  // Stage k, a compile-time constant: every LDS access then names its stage object, and the compiler's tracking of the
+  // direct-to-LDS loads can tell the stages apart.
+  auto stage = [&](auto k) __attribute__((always_inline)) -> Stage& {
+    if constexpr (decltype(k)::value == 0) return st0;
+    else return st1;
+  };
+  constexpr uint32_t OUT = 0xfffffff0u;
+  // Where the next load of a panel begins: first row and the rows left of S from there (<= 0 behind its end), and the lanes'
+  // offsets. The fences keep the scalar arithmetic of one load next to it, instead of 16 addresses in registers.
+  struct Cursor {
+    const float* p;
+    int left;
+    uint32_t v;
+  };
+  auto cursor = [&](int64_t off, bool second) __attribute__((always_inline)) {
+    Cursor c{(second ? baseB : baseA) + off, second ? leftB : leftA, off < (second ? limB : limA) ? voff : OUT};
+    asm volatile("" : "+s"(c.p), "+s"(c.left));
+    return c;
+  };
+  // load i of a panel at its cursor, which moves on
+  auto issue = [&](float* panel, int i, Cursor& c) __attribute__((always_inline)) {
+    int rows = max(c.left, 0);
+    asm volatile("" : "+s"(rows));
+    rows = min(rows, 8);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(c.p), 0, (int)((uint32_t)rows * rowbytes), 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(panel + 8 * (wave + NW * i) * KS), 16, c.v, 0, 0, 0);
+    c.p += 8 * NW * lds;
+    c.left -= 8 * NW;
+    asm volatile("" : "+s"(c.p), "+s"(c.left));
+  };
+  static_assert(T / 8 / NW == 8, "16 loads of both panels: four in each of four groups");
+  using K0 = std::integral_constant<int, 0>;
+  using K1 = std::integral_constant<int, 1>;
+  // LDS word of row l32, chunk u (0 .. 3) of this lane's half of the 32 columns
+  int lo[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) lo[u] = l32 * KS + 4 * ((half * 4 + u) ^ (l32 & 7));
+
+  if (nsteps > 0) {
+    Cursor ca = cursor(0, false), cb = cursor(0, true);
+#pragma unroll
+    for (int i = 0; i < T / 8 / NW; ++i) {
+      issue(st0.a, i, ca);
+      issue(st0.b, i, cb);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("s_barrier" ::: "memory");
+  }
+
+  // Both loops: a step in groups of products whose operands were read one group ahead; the last group reads the next
+  // step's first operands, after the wait for that step's loads (issued a step ago) and the barrier that also frees this
+  // step's stage, which the next step refills. The FP32 matrix instruction occupies the vector unit: a vector instruction
+  // between two products that depends on nothing in flight still costs tens of cycles, so the loops hold none but the
+  // addresses of the loads' lanes, once a step: LDS addresses are kept in registers for both stages, the loads' bases and
+  // bounds are scalar, and the LDS reads take the rest as immediate offsets.
+  if (diag) {
+    f32x16 acc[NDIAG];
+#pragma unroll
+    for (int j = 0; j < NDIAG; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+    // byte offsets of this lane's chunk u of block rows w + t: t = 0 .. 4 from ad[.][0], t = 5 .. 7 (may wrap) of their own
+    int ad[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      ad[u][0] = 4 * (lo[u] + wave * 32 * KS);
+#pragma unroll
+      for (int t = 5; t < 8; ++t) ad[u][t - 4] = 4 * (lo[u] + ((wave + t) & 7) * 32 * KS);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) asm volatile("" : "+v"(ad[u][t]));
+    }
+    constexpr int NG = 8;   // groups: chunk g & 3 of panel g >> 2
+    f32x4 f[2][8];
+    auto read_f = [&](const Stage& st, auto gc) __attribute__((always_inline)) {
+      constexpr int g = decltype(gc)::value;
+      const char* p = reinterpret_cast<const char*>(g < 4 ? st.a : st.b);
+      static_for<8>([&](auto tc) __attribute__((always_inline)) {
+        constexpr int t = decltype(tc)::value;
+        constexpr int r = t < 5 ? 0 : t - 4, o = t < 5 ? t * 32 * KS * 4 : 0;
+        f[g & 1][t] = *reinterpret_cast<const f32x4*>(p + ad[g & 3][r] + o);
+      });
+    };
+    auto body = [&](auto k, int64_t s) __attribute__((always_inline)) {
+      constexpr int K = decltype(k)::value;
+      const int64_t off = (s + 1) * span;
+      Cursor ca = cursor(off, false), cb = cursor(off, true);
+      static_for<NG>([&](auto gc) __attribute__((always_inline)) {
+        constexpr int g = decltype(gc)::value;
+        DFI_WAIT_LGKM0();
+        if constexpr (g + 1 < NG) {
+          read_f(stage(k), std::integral_constant<int, g + 1>{});
+        } else {
+          __builtin_amdgcn_s_waitcnt(0);
+          asm volatile("s_barrier" ::: "memory");
+          read_f(stage(std::integral_constant<int, 1 - K>{}), K0{});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<4>([&](auto ec) __attribute__((always_inline)) {
+          constexpr int e = decltype(ec)::value;
+          static_for<NDIAG>([&](auto jc) __attribute__((always_inline)) {
+            constexpr int j = decltype(jc)::value;
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f[g & 1][DIAG_A[j]][e], f[g & 1][DIAG_B[j]][e], acc[j], 0, 0, 0);
+          });
+          if constexpr (g < 4) {
+            __builtin_amdgcn_sched_barrier(0);
+            Stage& nx = stage(std::integral_constant<int, 1 - K>{});
+            if constexpr (e & 1) issue(nx.b, 2 * g + e / 2, cb);
+            else issue(nx.a, 2 * g + e / 2, ca);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    if (nsteps > 0) {
+      read_f(st0, K0{});
+      for (int64_t s = 0; s < nsteps; s += 2) {   // an odd count ends with a step of zeros
+        body(K0{}, s);
+        body(K1{}, s + 1);
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0);   // no load into LDS outlives the workgroup
+#pragma unroll
+    for (int j = 0; j < NDIAG; ++j) {
+      const int rb = (wave + DIAG_A[j]) & 7, cb = (wave + DIAG_B[j]) & 7;
+      if (!block_used(true, rowA, rowB, max(rb, cb) * 32, min(rb, cb) * 32, n)) continue;
+      if (cb <= rb) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          out[(rb * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * T + cb * 32 + l32] = acc[j][r];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; r += 4)
+          *reinterpret_cast<f32x4*>(&out[(cb * 32 + l32) * T + rb * 32 + 2 * r + 4 * half]) =
+              f32x4{acc[j][r], acc[j][r + 1], acc[j][r + 2], acc[j][r + 3]};
+      }
+    }
+    return;
+  }
+
+  const int wr = wave >> 1, wc = wave & 1;
   f32x16 acc[NB][NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i)
@@ -472,39 +549,84 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
+  // Groups of 8 columns of each half and one A block row (32 products); the four B blocks of the second 8 columns are read
+  // during the first four groups.
+  constexpr int NG = 2 * NB;
+  int aa[4], ab[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    aa[u] = 4 * (lo[u] + wr * WT * KS);
+    ab[u] = 4 * (lo[u] + wc * WT * KS);
+    asm volatile("" : "+v"(aa[u]), "+v"(ab[u]));
+  }
+  f32x8 fa[2], fb[2][NB];
+  auto read8 = [&](const float* p, int o0, int o1) __attribute__((always_inline)) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(p) + o0);
+    const f32x4 y = *reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(p) + o1);
+    return f32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+  };
+  auto read_a = [&](const Stage& st, int g, int d) __attribute__((always_inline)) {
+    const int o = 32 * (g % NB) * KS * 4;
+    fa[d] = read8(st.a, aa[2 * (g / NB)] + o, aa[2 * (g / NB) + 1] + o);
+  };
+  auto read_b = [&](const Stage& st, int h, int j) __attribute__((always_inline)) {
+    fb[h][j] = read8(st.b, ab[2 * h] + 32 * j * KS * 4, ab[2 * h + 1] + 32 * j * KS * 4);
+  };
+  auto head = [&](const Stage& st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) read_b(st, 0, j);
+    read_a(st, 0, 0);
+  };
+  auto body = [&](auto k, int64_t s) __attribute__((always_inline)) {
+    constexpr int K = decltype(k)::value;
+    const int64_t off = (s + 1) * span;
+    Cursor ca = cursor(off, false), cb = cursor(off, true);
+    static_for<NG>([&](auto gc) __attribute__((always_inline)) {
+      constexpr int g = decltype(gc)::value;
+      DFI_WAIT_LGKM0();
+      if constexpr (g + 1 < NG) {
+        read_a(stage(k), g + 1, (g + 1) & 1);
+        if constexpr (g < NB) read_b(stage(k), 1, g);
+      } else {
+        __builtin_amdgcn_s_waitcnt(0);
+        asm volatile("s_barrier" ::: "memory");
+        head(stage(std::integral_constant<int, 1 - K>{}));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<8>([&](auto ec) __attribute__((always_inline)) {
+        constexpr int e = decltype(ec)::value;
+        static_for<NB>([&](auto jc) __attribute__((always_inline)) {
+          constexpr int j = decltype(jc)::value;
+          acc[g % NB][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[g & 1][e], fb[g / NB][j][e], acc[g % NB][j], 0, 0, 0);
+        });
+        if constexpr (g < 4 && (e & 1)) {
+          __builtin_amdgcn_sched_barrier(0);
+          Stage& nx = stage(std::integral_constant<int, 1 - K>{});
+          if constexpr (e & 2) issue(nx.b, 2 * g + e / 4, cb);
+          else issue(nx.a, 2 * g + e / 4, ca);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
   if (nsteps > 0) {
-    issue_panel(S, lds, n, rowA, k0, kend, st0.a);
-    if (!diag) issue_panel(S, lds, n, rowB, k0, kend, st0.b);
-  }
-  for (int64_t s = 0; s < nsteps; ++s) {
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's loads for step s have landed
-    __syncthreads();                // ... and every wave's; stage (s+1)&1 is free again
-    const int64_t kc = k0 + s * KS;
-    if (s + 1 < nsteps) {
-      Stage& nx = ((s + 1) & 1) ? st1 : st0;
-      issue_panel(S, lds, n, rowA, kc + KS, kend, nx.a);
-      if (!diag) issue_panel(S, lds, n, rowB, kc + KS, kend, nx.b);
+    head(st0);
+    for (int64_t s = 0; s < nsteps; s += 2) {
+      body(K0{}, s);
+      body(K1{}, s + 1);
     }
-    // (in diagonal tiles the wave above the diagonal computes too; its result is not stored:
-    // a divergent skip here makes the compiler shuffle every accumulator each step)
-    const Stage& cu = (s & 1) ? st1 : st0;
-    const float* pa = cu.a;
-    const float* pb = diag ? cu.a : cu.b;
-    step_compute<PREC>(pa, pb, wr * WT + l32, wc * WT + l32, half, sgn, acc);
   }
+  __builtin_amdgcn_s_waitcnt(0);
 
-  float* out = part + (slice * ntri + tile) * (int64_t)(T * T);
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
-      if (block_used(diag, rowA, rowB, wr * WT + i * 32, wc * WT + j * 32, n))
+      if (block_used(false, rowA, rowB, wr * WT + i * 32, wc * WT + j * 32, n))
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = wr * WT + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        const int col = wc * WT + j * 32 + l32;
-        out[row * T + col] = sgn * acc[i][j][r];
-      }
+        for (int r = 0; r < 16; ++r)
+          out[(wr * WT + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * T + wc * WT + j * 32 + l32] = acc[i][j][r];
 }
 
 }  // namespace v2
@@ -612,11 +734,6 @@ __device__ __forceinline__ i32x8 read_frag(const uint8_t* panel, int r, int h) {
   }
   return v;
 }
-
-// vmcnt(N) with the other counters left alone (gfx9 encoding: vmcnt bits [3:0] and [15:14]).
-#define DFI_WAIT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
-// lgkmcnt(0) with the other counters left alone (lgkmcnt bits [11:8]).
-#define DFI_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4))
 
 // The work item of workgroup w (the kernel body; the grouped form below runs it for one problem's
 // share of a launch over many problems).
@@ -1215,7 +1332,9 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
     // FP32 and split-BF16 never get fewer slices than the base plan: a slice is summed in FP32, and longer
     // ones would round more. (The FP8 codes' own rounding is 1e4 times that of their sums.) Split-BF16
     // keeps an even count: odd slices are negated against the accumulation's bias.
-    const double rate = prec == 2 ? 0.0141 : prec == 0 ? (aligned16 ? 0.27 : 0.34) : (p.ldh > 0 ? 0.075 : 0.16);
+    // An aligned FP32 diagonal tile costs 9 / 16 of another.
+    const double mix = (double)(p.ntri - p.ntile) / (double)p.ntri + 0.5625 * (double)p.ntile / (double)p.ntri;
+    const double rate = prec == 2 ? 0.0141 : prec == 0 ? (aligned16 ? 0.227 * mix : 0.34) : (p.ldh > 0 ? 0.075 : 0.16);
     auto cost = [&](int64_t ns) {
       const int64_t ks = columns(ns), items = p.ntri * ((cap + ks - 1) / ks);
       return (double)((items + 255) / 256) * ((double)ks * rate + 3.0) + 0.145 * (double)items;
@@ -1289,7 +1408,7 @@ hipError_t gram_launch_split(const GramPlan& p, const uint16_t* hi, const uint16
 // convert it once per reading wave, which measured slower.)
 static bool use_v2(const GramPlan& p, const float* S) {
   const bool vec = ((p.lds & 3) == 0) && ((reinterpret_cast<uintptr_t>(S) & 15) == 0);
-  return vec && p.prec == 0;
+  return vec && p.prec == 0 && p.lds < ((int64_t)1 << 27);   // eight rows lie within one buffer of 2^32 bytes
 }
 
 static int64_t tail_start(const GramPlan& p, const float* S) {
@@ -1304,7 +1423,7 @@ hipError_t gram_launch(const GramPlan& p, const float* S, float* part, hipStream
   const bool vec = ((p.lds & 3) == 0) && ((reinterpret_cast<uintptr_t>(S) & 15) == 0);
   const dim3 grid((unsigned)(8 * items_per_xcd(p.ntri, p.nslice)));
   if (use_v2(p, S)) {
-    hipLaunchKernelGGL((v2::gram_kernel_v2<0>), grid, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
+    hipLaunchKernelGGL(v2::gram_kernel_v2, grid, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
   } else if (p.prec == 0) {
     hipLaunchKernelGGL((gram_kernel<0, false>), grid, dim3(NTHR), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
   } else if (vec) {
