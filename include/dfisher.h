@@ -386,7 +386,7 @@ DFISHER_API dfisher_status dfisher_ctx_enable_graphs(dfisher_ctx* ctx, int32_t e
 
 /* Gram autotuning. The split-K factor of the Gram kernels (how many k-slices the m columns are
  * cut into, which sets the number of workgroups and the partial-tile traffic) and, for
- * split-BF16 on 16-byte aligned rows, whether the row pass pre-splits S into bf16 planes, are
+ * split-BF16, whether the row pass pre-splits S into bf16 planes, are
  * chosen per size class (precision, ceil(n / 256), floor(log2 m), row alignment).
  * dfisher_autotune_gram times every candidate on the given S (Gram stage only: row pass, tile
  * kernel, reduction; one untimed and two timed runs each, HIP events on the stream, synchronous)

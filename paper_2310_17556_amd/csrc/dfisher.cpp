@@ -292,12 +292,26 @@ std::tuple<int, int64_t, int, int> tune_key(int prec, int64_t n, int64_t m, bool
 }
 
 // The Gram plan for a shape: the tuned split-K factor / split mode of its size class if the
-// context has one, else the built-in choice.
-dfi::GramPlan make_gram_plan(const dfisher_ctx* ctx, const float* S, int64_t n, int64_t m, int64_t lds, int prec) {
+// context has one, else the built-in choice. planes = false: rows that are not 16-byte aligned are split
+// inside the tile kernel (see ensure_gram_ws).
+dfi::GramPlan make_gram_plan(const dfisher_ctx* ctx, const float* S, int64_t n, int64_t m, int64_t lds, int prec,
+                             bool planes = true) {
   const bool al = rows_aligned16(S, lds);
+  const bool in_kernel = !al && !planes;
   auto it = ctx->tune.find(tune_key(prec, n, m, al));
-  if (it != ctx->tune.end()) return dfi::gram_plan(n, m, lds, prec, al, it->second.first, it->second.second);
-  return dfi::gram_plan(n, m, lds, prec, al);
+  if (it != ctx->tune.end())
+    return dfi::gram_plan(n, m, lds, prec, al, it->second.first, in_kernel ? 0 : it->second.second);
+  return dfi::gram_plan(n, m, lds, prec, al, 0, in_kernel ? 0 : -1);
+}
+
+// The workspace of a call, need() bytes under its Gram plan gp. Rows that are not 16-byte aligned do not depend on
+// the memory for their split-BF16 planes (as much as S takes): without it the tile kernel splits them itself.
+template <class F>
+dfisher_status ensure_gram_ws(dfisher_ctx* ctx, const float* S, dfi::GramPlan& gp, F need) {
+  const dfisher_status s = ensure_ws(ctx, need());
+  if (s == DFISHER_OK || gp.ldh == 0 || rows_aligned16(S, gp.lds)) return s;
+  gp = make_gram_plan(ctx, S, gp.n, gp.m, gp.lds, gp.prec, false);
+  return ensure_ws(ctx, need());
 }
 
 // Scratch of the one-launch Cholesky for nbatch matrices: the packed factors and the ticket.
@@ -814,7 +828,7 @@ dfisher_status multi_solve(const float* S, int64_t n, int64_t m, int64_t lds, in
 
 // ----------------------------------------------------------------------------- autotuning
 // For one size class, times the Gram stage (row pass + tile kernel + reduction) on the caller's
-// S for every split-K factor q from dfi::gram_q_candidates (and, for split-BF16 on aligned rows,
+// S for every split-K factor q from dfi::gram_q_candidates (and, for split-BF16,
 // with and without the pre-split planes), keeps the fastest in ctx->tune. Each candidate runs once
 // untimed and twice timed (HIP events on the stream; the minimum counts).
 constexpr size_t TUNE_MAX_PART_BYTES = (size_t)4 << 30;
@@ -826,16 +840,20 @@ dfisher_status tune_gram(dfisher_ctx* ctx, const float* S, int64_t n, int64_t m,
   int nq = 0;
   dfi::gram_q_candidates(n, m, TUNE_MAX_PART_BYTES, qs, &nq, 16);
   std::vector<int> modes = {-1};
-  if (prec == DFISHER_GRAM_BF16X3 && al) modes = {1, 0};
+  if (prec == DFISHER_GRAM_BF16X3) modes = {1, 0};
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
-  size_t need = 0;
-  for (int mode : modes)
-    for (int i = 0; i < nq; ++i) {
-      const dfi::GramPlan gp = dfi::gram_plan(n, m, lds, prec, al, qs[i], mode);
-      need = std::max(need, carve(nullptr, n, m, &gp, rp, cp, false, false).bytes);
-    }
-  DF_TRY(ensure_ws(ctx, need));
+  auto most = [&]() {
+    size_t need = 0;
+    for (int mode : modes)
+      for (int i = 0; i < nq; ++i) {
+        const dfi::GramPlan gp = dfi::gram_plan(n, m, lds, prec, al, qs[i], mode);
+        need = std::max(need, carve(nullptr, n, m, &gp, rp, cp, false, false).bytes);
+      }
+    return need;
+  };
+  if (!al && modes.size() > 1 && ensure_ws(ctx, most()) != DFISHER_OK) modes = {0};   // see ensure_gram_ws
+  DF_TRY(ensure_ws(ctx, most()));
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     (void)hipGetLastError();
@@ -925,6 +943,7 @@ struct UnevenLayout {
   SolveBufs shared{};                      // scratch reused by every problem (largest sizes)
   double *W = nullptr, *Dinv = nullptr, *dkk = nullptr, *dmax = nullptr;
   bool packed = true;                      // room for the factors' packed copies (the one-launch Cholesky)
+  bool planes = true;                      // room for the split-BF16 planes of rows that are not 16-byte aligned
   std::vector<int64_t> poff;               // doubles
   double* pack = nullptr;
   uint32_t* ticket = nullptr;
@@ -981,7 +1000,7 @@ void uneven_layout(const dfisher_ctx* ctx, char* base, int32_t np, const float* 
   int64_t wtot = 0, dtot = 0;
   size_t gpart = 0, rpart = 0, cpart = 0, q8 = 0, sc8 = 0, planes = 0;
   for (int32_t p = 0; p < np; ++p) {
-    U.gp.push_back(make_gram_plan(ctx, S[p], n[p], m[p], lds[p], prec));
+    U.gp.push_back(make_gram_plan(ctx, S[p], n[p], m[p], lds[p], prec, U.planes));
     U.rp.push_back(dfi::rowpass_plan(n[p], m[p], lds[p]));
     U.cp.push_back(dfi::colpass_plan(n[p], m[p]));
     U.fp.push_back(dfi::refine_pass_plan(n[p], m[p], lds[p], S[p]));
@@ -1337,7 +1356,11 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   if (ensure_ws(ctx, U.bytes) != DFISHER_OK) {   // no room for the packed copies: the factorisations run in place
     U.packed = false;
     uneven_layout(ctx, nullptr, np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
-    DF_TRY(ensure_ws(ctx, U.bytes));
+    if (ensure_ws(ctx, U.bytes) != DFISHER_OK) {   // nor for planes of rows that are not 16-byte aligned
+      U.planes = false;
+      uneven_layout(ctx, nullptr, np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
+      DF_TRY(ensure_ws(ctx, U.bytes));
+    }
   }
   uneven_layout(ctx, static_cast<char*>(ctx->ws), np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
   // largest problems first (their Gram kernels fill the device; small ones follow)
@@ -1823,12 +1846,11 @@ dfisher_status dfisher_gram(dfisher_ctx* ctx, const float* S, int64_t n, int64_t
   DeviceGuard g(ctx->device);
   hipStream_t st = as_stream(stream);
   if (ctx->autotune) DF_TRY(tune_if_new(ctx, S, n, m, lds, prec, st));
-  const dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, prec);
+  dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
-  SolveBufs B = carve(nullptr, n, m, &gp, rp, cp, false, false);
-  DF_TRY(ensure_ws(ctx, B.bytes));
-  B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, false, false);
+  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return carve(nullptr, n, m, &gp, rp, cp, false, false).bytes; }));
+  SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, false, false);
   StageClock clk(ctx, st);
   DF_TRY(gram_stage(S, nullptr, gp, rp, B, lambda, W, 1, st, &clk));
   clk.mark(3);
@@ -1945,12 +1967,11 @@ dfisher_status dfisher_factor_create(dfisher_ctx* ctx, const float* S, int64_t n
   DeviceGuard g(ctx->device);
   hipStream_t st = as_stream(stream);
   if (ctx->autotune) DF_TRY(tune_if_new(ctx, S, n, m, lds, o.gram_prec, st));
-  const dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
+  dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
-  SolveBufs B = carve(nullptr, n, m, &gp, rp, cp, false, false);
-  DF_TRY(ensure_ws(ctx, B.bytes));
-  B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, false, false);
+  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return carve(nullptr, n, m, &gp, rp, cp, false, false).bytes; }));
+  SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, false, false);
   dfisher_factor* f = new dfisher_factor();
   f->ctx = ctx;
   f->S = S;
@@ -2040,7 +2061,8 @@ dfisher_status dfisher_factor_solve_noalloc(const dfisher_factor* f, const float
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   const dfi::RefinePassPlan fp = dfi::refine_pass_plan(n, m, lds, f->S, false);   // small workspace
-  if (sweeps > 0 && !fp.usable)
+  const bool fused = fp.usable && rows_aligned16(f->S, lds);
+  if (sweeps > 0 && !fused)
     return fail(DFISHER_E_UNSUPPORTED, "the no-alloc solve refines with the one-read product only: it needs "
                 "n <= 4096, m >= 16 and 16-byte aligned rows of S (n = %lld, lds = %lld)", (long long)n,
                 (long long)lds);
@@ -2049,7 +2071,7 @@ dfisher_status dfisher_factor_solve_noalloc(const dfisher_factor* f, const float
     Carver c;
     c.base = base;
     B = SolveBufs{};
-    B.rpart = c.take<double>(std::max(rp.part_bytes, fp.part_bytes) / sizeof(double) + 1);
+    B.rpart = c.take<double>(std::max(rp.part_bytes, fused ? fp.part_bytes : 0) / sizeof(double) + 1);
     B.cpart = c.take<double>(cp.part_bytes / sizeof(double) + 1);
     B.b = c.take<double>((size_t)n);
     B.z = c.take<double>((size_t)n);
@@ -2118,7 +2140,7 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
   DeviceGuard g(ctx->device);
   hipStream_t st = as_stream(stream);
   if (ctx->autotune) DF_TRY(tune_if_new(ctx, S, n, m, lds, o.gram_prec, st));
-  const dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
+  dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   const dfi::RefinePassPlan fp = dfi::refine_pass_plan(n, m, lds, S);
@@ -2127,9 +2149,11 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
   // codes exist, the passes can carry S^T y, there is a correction, and the caller allows it
   const bool final8 = o.gram_prec == DFISHER_GRAM_MXFP8 && fp.usable && fp.line && o.sweeps != 0 &&
                       !o.final_resid && (o.flags & DFISHER_EXACT_APPLY) == 0;
-  SolveBufs B = carve(nullptr, n, m, &gp, rp, cp, true, need_t, &fp, final8, is_centered(o));
-  DF_TRY(ensure_ws(ctx, B.bytes));
-  B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, true, need_t, &fp, final8, is_centered(o));
+  auto lay = [&](char* base) {
+    return carve(base, n, m, &gp, rp, cp, true, need_t, &fp, final8, is_centered(o));
+  };
+  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
+  SolveBufs B = lay(static_cast<char*>(ctx->ws));
   StageClock clk(ctx, st);
   // one pass over S (b = S v, the exact diagonal |s_i|^2, the FP8 codes if used), then step 1
   DF_TRY(gram_stage(S, v, gp, rp, B, lambda, B.W, 0, st, &clk, is_centered(o), B.cs8 ? B.use8 + 1 : nullptr));
@@ -2202,14 +2226,13 @@ dfisher_status dfisher_solve_rowspace(dfisher_ctx* ctx, const float* S, int64_t 
   DeviceGuard g(ctx->device);
   hipStream_t st = as_stream(stream);
   if (ctx->autotune) DF_TRY(tune_if_new(ctx, S, n, m, lds, o.gram_prec, st));
-  const dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
+  dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   const dfi::RefinePassPlan fp = dfi::refine_pass_plan(n, m, lds, S);
   const bool need_t = (o.sweeps != 0 || o.final_resid) && !fp.usable;
-  SolveBufs B = carve(nullptr, n, m, &gp, rp, cp, true, need_t, &fp);
-  DF_TRY(ensure_ws(ctx, B.bytes));
-  B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, true, need_t, &fp);
+  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return carve(nullptr, n, m, &gp, rp, cp, true, need_t, &fp).bytes; }));
+  SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, true, need_t, &fp);
   StageClock clk(ctx, st);
   // one pass over S for the exact diagonal (and the FP8 codes), then step 1; b = f
   DF_TRY(gram_stage(S, nullptr, gp, rp, B, lambda, B.W, 0, st, &clk, is_centered(o)));
@@ -2310,7 +2333,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
   hipStream_t st = as_stream(stream);
   const int64_t N = 2 * n;
   if (ctx->autotune) DF_TRY(tune_if_new(ctx, Z, N, m, lds, o.gram_prec, st));
-  const dfi::GramPlan gp = make_gram_plan(ctx, Z, N, m, lds, o.gram_prec);
+  dfi::GramPlan gp = make_gram_plan(ctx, Z, N, m, lds, o.gram_prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(N, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(N, m);
   const dfi::RowMultiPlan rm = dfi::rowmulti_plan(N, m, lds);
@@ -2337,7 +2360,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
   };
   SolveBufs B;
   Extra X;
-  DF_TRY(ensure_ws(ctx, lay(nullptr, B, X)));
+  DF_TRY(ensure_gram_ws(ctx, Z, gp, [&] { return lay(nullptr, B, X); }));
   lay(static_cast<char*>(ctx->ws), B, X);
   StageClock clk(ctx, st);
   // Z Z^T (both triangles, exact FP64 diagonal) and the embedded W
@@ -2448,7 +2471,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
     capturing = cs == hipStreamCaptureStatusActive;
   }
   if (ctx->autotune && !async) DF_TRY(tune_if_new(ctx, S, n, m, lds, o.gram_prec, st));
-  const dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
+  dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   const dfi::RowMultiPlan rm = dfi::rowmulti_plan(n, m, lds);
@@ -2487,8 +2510,13 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   size_t need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
   // without the memory (or, in a capture, the workspace of the call before it) for the packed copies the
   // factorisations run in place
-  if (capturing ? need > ctx->ws_bytes : ensure_ws(ctx, need) != DFISHER_OK) {
+  auto no_room = [&]() { return capturing ? need > ctx->ws_bytes : ensure_ws(ctx, need) != DFISHER_OK; };
+  if (no_room()) {
     packed = false;
+    need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
+  }
+  if (!packed && gp.ldh > 0 && !rows_aligned16(S, lds) && no_room()) {   // and the planes (see ensure_gram_ws)
+    gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec, false);
     need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
   }
   if (capturing) {   // no allocation inside a capture; the graph will hold the workspace's addresses

@@ -24,9 +24,9 @@ struct GramPlan {
 };
 
 // aligned16: rows of S start on 16-byte boundaries (lds % 4 == 0 and S 16-byte aligned). For
-// split-BF16 on aligned rows the plan uses planes hi/lo written by the row pass (ldh > 0).
+// split-BF16 the plan uses planes hi/lo written by the row pass (ldh > 0).
 // q_override > 0 fixes the split-K factor (nslice = 8 q); split_mode 0 keeps split-BF16 inside the
-// tile kernel even on aligned rows (-1: planes whenever possible).
+// tile kernel (-1: planes).
 GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, int q_override = 0,
                    int split_mode = -1);
 // The split-K factors q (nslice = 8 q) worth trying for a shape: every q from 1 up to the largest
@@ -81,8 +81,8 @@ hipError_t rowpass_launch(const RowPassPlan& p, const float* S, const float* v, 
                           uint8_t* sc = nullptr, int64_t ldq = 0, bool blocked = false);
 // Row pass that also writes the split-BF16 planes of S: hi = bf16_rne(S), lo = bf16_rne(S - hi),
 // column-blocked in 16-column blocks of all n rows: element (i, k) at [((k / 16) n + i) 16 + k % 16]
-// (ldh = m rounded up to 64; entries k >= m are zero). Needs 16-byte aligned rows; always
-// computes d, and b when v != nullptr.
+// (ldh = m rounded up to 64; entries k >= m are zero). Always computes d, and b when
+// v != nullptr.
 hipError_t rowpass_launch_split(const RowPassPlan& p, const float* S, const float* v, double* part, uint16_t* hi,
                                 uint16_t* lo, int64_t ldh, hipStream_t st);
 // Reduce: b_i = sum_c part_b[c][i]; when r0 != nullptr: b_i = r0_i - lam * y_i - sum_c part_b[c][i]
@@ -106,7 +106,7 @@ hipError_t colpass_launch(const ColPassPlan& p, const float* S, int64_t n, int64
                           const int* skip = nullptr);
 
 // Fused refinement pass: part[g][i] = per-workgroup partials of (S S^T y)_i with one read of S
-// (n <= 4096, m >= 16, 16-byte aligned rows; `usable` is false otherwise and
+// (n <= 4096, m >= 16; `usable` is false otherwise and
 // the caller takes the column pass + row pass). The last m % 16 columns add one more group.
 // refine_pass_reduce: r_i = b_i - lam y_i - sum_g part[g][i] in fixed order.
 struct RefinePassPlan {

@@ -1316,7 +1316,9 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
       best_q = q;
     }
   }
-  p.ldh = (prec == 1 && aligned16 && split_mode != 0) ? split_ldh(m) : 0;
+  // (planes also for rows that are not 16-byte aligned: 1000 x 99999 row pass 154 + Gram 336 us, against 122 + 673 with the
+  // split in the tile kernel)
+  p.ldh = (prec == 1 && split_mode != 0) ? split_ldh(m) : 0;
   const int64_t cap = prec == 2 ? fp8_ldq(m) : (p.ldh > 0 ? p.ldh : m);   // columns the slices cover
   const int64_t kstep = (prec == 2) ? 64 : KS;
   auto columns = [&](int64_t ns) { return std::max<int64_t>(1, ((cap + ns - 1) / ns + kstep - 1) / kstep) * kstep; };
