@@ -304,7 +304,7 @@ gram_kernel(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int6
 }
 
 // ---------------------------------------------------------------------------------------------
-// Gram kernel v2 (16-byte aligned rows): asynchronous direct-to-LDS loads into a two-stage ring.
+// Gram kernel v2 (FP32): asynchronous direct-to-LDS loads into a two-stage ring.
 //
 //   * Each k-step stages the FP32 columns [k, k+32) of the two 256-row panels (of a diagonal tile's one panel: 64 columns)
 //     with buffer loads to LDS: every wave instruction moves 8 rows x 128 B straight from global
@@ -361,9 +361,10 @@ constexpr int NDIAG = 9;
 constexpr int DIAG_A[NDIAG] = {0, 0, 0, 0, 4, 4, 4, 4, 4};
 constexpr int DIAG_B[NDIAG] = {0, 7, 6, 5, 4, 3, 2, 1, 0};
 
-__global__ void __launch_bounds__(NT, 1)
-gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntri, int64_t nslice,
-               int64_t kslice, float* __restrict__ part) {
+// W: bytes a lane loads, 16 (16-byte aligned rows) or 4 (any rows).
+template <int W>
+__device__ __forceinline__ void gram_v2_body(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntri,
+                                             int64_t nslice, int64_t kslice, float* __restrict__ part) {
   __shared__ Stage st0;
   __shared__ Stage st1;
 
@@ -377,7 +378,8 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
   const bool diag = (ti == tj);
   const int64_t rowA = ti * T, rowB = tj * T;
   const int64_t k0 = uni64(slice * kslice);
-  const int64_t kend = min(m & ~(int64_t)3, k0 + kslice);   // columns [m4, m) go to the reduction
+  // W = 16: columns [m rounded down to 4, m) go to the reduction
+  const int64_t kend = min(W == 16 ? m & ~(int64_t)3 : m, k0 + kslice);
   // a step is KS columns of both panels, or 2 KS columns of a diagonal tile's one panel: the same 16 loads a wave
   const int64_t span = diag ? 2 * KS : KS;
   const int64_t nsteps = (kend > k0) ? (kend - k0 + span - 1) / span : 0;
@@ -388,14 +390,23 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
   const int l32 = lane & 31;
   float* out = part + (slice * ntri + tile) * (int64_t)(T * T);
 
-  // Loads: instruction i of a panel carries rows 8 (wave + 4 i) .. + 7 of 32 columns, lane l row l / 8 and the column chunk
-  // (l % 8) ^ (row & 7). Its buffer begins at the first of these rows (64-bit scalar arithmetic) and ends behind the last
-  // row of S, and a lane whose chunk lies past the slice's end (a multiple of 4: a chunk is wholly inside or wholly past
-  // it) gets an offset outside every buffer: out of range reads nothing and gives zeros. Needs 8 lds * 4 < 2^32.
-  const int chunk = (lane & 7) ^ (lane >> 3);
+  // Loads: piece i of a panel carries rows 8 (wave + 4 i) .. + 7 of 32 columns; lane l of its one 16-byte load row l / 8 and
+  // the column chunk (l % 8) ^ (row & 7), of its four 4-byte loads j row 2 j + l / 32 and the column that belongs to word
+  // l % 32 of the swizzled row. A load's buffer begins at the first of its rows (64-bit scalar arithmetic) and ends behind the
+  // last row of S, and a lane whose columns lie past the slice's end (for W = 16 a multiple of 4: a chunk is wholly inside or
+  // wholly past it) gets an offset outside every buffer: out of range reads nothing and gives zeros. Needs 8 lds * 4 < 2^32.
+  constexpr int NL = 16 / W;             // loads a piece
+  constexpr int RL = 8 / NL;             // rows a load
   const uint32_t rowbytes = (uint32_t)lds * 4;
-  const uint32_t voff = (uint32_t)(lane >> 3) * rowbytes + 16 * chunk;
-  const int64_t limA = kend - k0 - 4 * chunk, limB = diag ? limA - KS : limA;
+  uint32_t voff[NL];
+  int coff[NL];                          // the lanes' (first) columns in a step
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const int r = RL * j + lane / (64 / RL);
+    coff[j] = W == 16 ? 4 * ((lane & 7) ^ r) : 4 * (((lane & 31) >> 2) ^ r) + (lane & 3);
+    voff[j] = (uint32_t)(lane / (64 / RL)) * rowbytes + 4 * coff[j];
+  }
+  const int64_t limA = kend - k0, limB = diag ? limA - KS : limA;
   const float* const baseA = S + (rowA + 8 * wave) * lds + k0;
   const float* const baseB = S + (rowB + 8 * wave) * lds + (diag ? k0 + KS : k0);
   const int leftA = (int)min(n - rowA, (int64_t)T) - 8 * wave, leftB = (int)min(n - rowB, (int64_t)T) - 8 * wave;
@@ -411,26 +422,37 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
   struct Cursor {
     const float* p;
     int left;
-    uint32_t v;
+    int word;   // of the wave's next 8 rows in a panel
+    uint32_t v[NL];
   };
   auto cursor = [&](int64_t off, bool second) __attribute__((always_inline)) {
-    Cursor c{(second ? baseB : baseA) + off, second ? leftB : leftA, off < (second ? limB : limA) ? voff : OUT};
-    asm volatile("" : "+s"(c.p), "+s"(c.left));
+    Cursor c;
+    c.p = (second ? baseB : baseA) + off;
+    c.left = second ? leftB : leftA;
+    c.word = 8 * wave * KS;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) c.v[j] = off + coff[j] < (second ? limB : limA) ? voff[j] : OUT;
+    asm volatile("" : "+s"(c.p), "+s"(c.left), "+s"(c.word));
     return c;
   };
-  // load i of a panel at its cursor, which moves on
-  auto issue = [&](float* panel, int i, Cursor& c) __attribute__((always_inline)) {
-    int rows = max(c.left, 0);
-    asm volatile("" : "+s"(rows));
-    rows = min(rows, 8);
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(c.p), 0, (int)((uint32_t)rows * rowbytes), 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(panel + 8 * (wave + NW * i) * KS), 16, c.v, 0, 0, 0);
-    c.p += 8 * NW * lds;
-    c.left -= 8 * NW;
-    asm volatile("" : "+s"(c.p), "+s"(c.left));
+  // the panel's next piece, at its cursor, which moves on
+  auto issue = [&](float* panel, Cursor& c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      int rows = max(c.left, 0);
+      asm volatile("" : "+s"(rows));
+      rows = min(rows, RL);
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(c.p), 0, (int)((uint32_t)rows * rowbytes), 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(panel + c.word), W, c.v[j], 0, 0, 0);
+      const int step = j + 1 < NL ? RL : 8 * NW - RL * j;   // rows to the next load
+      c.p += step * lds;
+      c.left -= step;
+      c.word += step * KS;
+      asm volatile("" : "+s"(c.p), "+s"(c.left), "+s"(c.word));
+    }
   };
-  static_assert(T / 8 / NW == 8, "16 loads of both panels: four in each of four groups");
+  static_assert(T / 8 / NW == 8, "16 pieces of both panels: four in each of four groups");
   using K0 = std::integral_constant<int, 0>;
   using K1 = std::integral_constant<int, 1>;
   // LDS word of row l32, chunk u (0 .. 3) of this lane's half of the 32 columns
@@ -442,8 +464,8 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
     Cursor ca = cursor(0, false), cb = cursor(0, true);
 #pragma unroll
     for (int i = 0; i < T / 8 / NW; ++i) {
-      issue(st0.a, i, ca);
-      issue(st0.b, i, cb);
+      issue(st0.a, ca);
+      issue(st0.b, cb);
     }
     __builtin_amdgcn_s_waitcnt(0);
     asm volatile("s_barrier" ::: "memory");
@@ -506,8 +528,8 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
           if constexpr (g < 4) {
             __builtin_amdgcn_sched_barrier(0);
             Stage& nx = stage(std::integral_constant<int, 1 - K>{});
-            if constexpr (e & 1) issue(nx.b, 2 * g + e / 2, cb);
-            else issue(nx.a, 2 * g + e / 2, ca);
+            if constexpr (e & 1) issue(nx.b, cb);
+            else issue(nx.a, ca);
             __builtin_amdgcn_sched_barrier(0);
           }
         });
@@ -602,8 +624,8 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
         if constexpr (g < 4 && (e & 1)) {
           __builtin_amdgcn_sched_barrier(0);
           Stage& nx = stage(std::integral_constant<int, 1 - K>{});
-          if constexpr (e & 2) issue(nx.b, 2 * g + e / 4, cb);
-          else issue(nx.a, 2 * g + e / 4, ca);
+          if constexpr (e & 2) issue(nx.b, cb);
+          else issue(nx.a, ca);
           __builtin_amdgcn_sched_barrier(0);
         }
       });
@@ -627,6 +649,18 @@ gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, i
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           out[(wr * WT + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * T + wc * WT + j * 32 + l32] = acc[i][j][r];
+}
+
+__global__ void __launch_bounds__(NT, 1)
+gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntri, int64_t nslice,
+               int64_t kslice, float* __restrict__ part) {
+  gram_v2_body<16>(S, n, lds, m, ntri, nslice, kslice, part);
+}
+
+__global__ void __launch_bounds__(NT, 1)
+gram_kernel_v2_words(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntri, int64_t nslice,
+                     int64_t kslice, float* __restrict__ part) {
+  gram_v2_body<4>(S, n, lds, m, ntri, nslice, kslice, part);
 }
 
 }  // namespace v2
@@ -1289,6 +1323,9 @@ gram_reduce_kernel(const float* __restrict__ part, int64_t n, int64_t ntri, int6
   }
 }
 
+// FP32 products by gram_kernel_v2: eight rows lie within one buffer of 2^32 bytes.
+bool use_v2(const GramPlan& p) { return p.prec == 0 && p.lds < ((int64_t)1 << 27); }
+
 }  // namespace
 
 GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, int q_override, int split_mode) {
@@ -1329,14 +1366,14 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
     // work item writes and the reduction reads 256 KB of partials. (The base plan leaves most of the chip
     // idle for small n, and a round nearly empty where ntri is a little over a multiple of 32: at
     // n = 256, m = 1e5 FP32 48 workgroups took 550 us with the reduction, 241 take 140; at n = 2048, m = 1e4
-    // split-BF16 288 took 220, 504 take 167; at n = 4096, m = 1e5 FP8 32 slices took 1200, 9 take 905.) Measured rates, us a column and tile: FP32 0.27
-    // (0.34 unaligned), split-BF16 from planes 0.075, inside the kernel 0.16, FP8 0.0141.
+    // split-BF16 288 took 220, 504 take 167; at n = 4096, m = 1e5 FP8 32 slices took 1200, 9 take 905.) Measured rates, us a column and tile: FP32 0.227
+    // (0.258 unaligned rows; 0.34 in gram_kernel), split-BF16 from planes 0.075, inside the kernel 0.16, FP8 0.0141.
     // FP32 and split-BF16 never get fewer slices than the base plan: a slice is summed in FP32, and longer
     // ones would round more. (The FP8 codes' own rounding is 1e4 times that of their sums.) Split-BF16
     // keeps an even count: odd slices are negated against the accumulation's bias.
-    // An aligned FP32 diagonal tile costs 9 / 16 of another.
+    // An FP32 diagonal tile costs 9 / 16 of another in gram_kernel_v2.
     const double mix = (double)(p.ntri - p.ntile) / (double)p.ntri + 0.5625 * (double)p.ntile / (double)p.ntri;
-    const double rate = prec == 2 ? 0.0141 : prec == 0 ? (aligned16 ? 0.227 * mix : 0.34) : (p.ldh > 0 ? 0.075 : 0.16);
+    const double rate = prec == 2 ? 0.0141 : prec == 0 ? (use_v2(p) ? (aligned16 ? 0.227 : 0.258) * mix : 0.34) : (p.ldh > 0 ? 0.075 : 0.16);
     auto cost = [&](int64_t ns) {
       const int64_t ks = columns(ns), items = p.ntri * ((cap + ks - 1) / ks);
       return (double)((items + 255) / 256) * ((double)ks * rate + 3.0) + 0.145 * (double)items;
@@ -1404,28 +1441,30 @@ hipError_t gram_launch_split(const GramPlan& p, const uint16_t* hi, const uint16
 }
 
 // Which tile kernel runs for an FP32 input S, and the first column it leaves to the reduction:
-//   * FP32 products, 16-byte aligned rows: v2 (direct-to-LDS), columns [0, m rounded down to 4);
-//   * split-BF16, or unaligned rows: v1 (register staging, conversion on the LDS store), all columns.
+//   * FP32 products: v2 (direct-to-LDS), 16-byte aligned rows by 16 bytes, columns [0, m rounded down to 4); other rows by
+//     4 bytes (four times the loads: 1024 x 99999 1030 us, aligned 905, v1 1340), all columns;
+//   * split-BF16 without planes, or rows of 2^27 columns: v1 (register staging, conversion on the LDS store), all columns.
 // (For split-BF16 the register-staged kernel converts each element once per workgroup; v2 would
 // convert it once per reading wave, which measured slower.)
-static bool use_v2(const GramPlan& p, const float* S) {
-  const bool vec = ((p.lds & 3) == 0) && ((reinterpret_cast<uintptr_t>(S) & 15) == 0);
-  return vec && p.prec == 0 && p.lds < ((int64_t)1 << 27);   // eight rows lie within one buffer of 2^32 bytes
+static bool vec_rows(const GramPlan& p, const float* S) {
+  return ((p.lds & 3) == 0) && ((reinterpret_cast<uintptr_t>(S) & 15) == 0);
 }
 
 static int64_t tail_start(const GramPlan& p, const float* S) {
   if (p.prec == 2) return p.m;   // the FP8 kernel covers every column (zero codes past m)
   if (p.prec == 1 && p.ldh > 0) return p.m;   // the plane kernel covers every column (zeros past m)
-  return use_v2(p, S) ? (p.m & ~(int64_t)3) : p.m;
+  return use_v2(p) && vec_rows(p, S) ? (p.m & ~(int64_t)3) : p.m;
 }
 
 int64_t gram_tail_start(const GramPlan& p, const float* S) { return tail_start(p, S); }
 
 hipError_t gram_launch(const GramPlan& p, const float* S, float* part, hipStream_t st) {
-  const bool vec = ((p.lds & 3) == 0) && ((reinterpret_cast<uintptr_t>(S) & 15) == 0);
+  const bool vec = vec_rows(p, S);
   const dim3 grid((unsigned)(8 * items_per_xcd(p.ntri, p.nslice)));
-  if (use_v2(p, S)) {
+  if (use_v2(p) && vec) {
     hipLaunchKernelGGL(v2::gram_kernel_v2, grid, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
+  } else if (use_v2(p)) {
+    hipLaunchKernelGGL(v2::gram_kernel_v2_words, grid, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
   } else if (p.prec == 0) {
     hipLaunchKernelGGL((gram_kernel<0, false>), grid, dim3(NTHR), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
   } else if (vec) {
