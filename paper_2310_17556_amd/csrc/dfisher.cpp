@@ -645,7 +645,9 @@ dfisher_status final_residual(dfisher_ctx* ctx, const float* S, int64_t n, int64
 // x = (v_r - S^T y) / lambda_f. Needs nfac * nrhs <= 65535.
 struct MultiBufs {
   uint32_t* ticket;
-  double *Bs, *Bexp, *Y, *R, *D, *T, *T1, *Yi, *part, *part1;   // T1, part1: a second group
+  double *Bs, *Bexp, *Y, *R, *D, *Yi;
+  double *T[dfi::MULTI_GROUPS], *part[dfi::MULTI_GROUPS];   // per group of vectors that shares a pass
+  int groups = 1;                    // at most
   double *Zc, *P, *NQ, *zero, *rz;   // refinement: M^-1 R, directions, -(W P), n zeros, r.z per vector
   // the final step through the FP8 codes (apply8.hip), when planned: S^T y carried per vector (Tacc)
   // and S^T p of the last directions (Uacc), both in the passes' T layout; step lengths; the
@@ -667,7 +669,8 @@ struct MultiF8 {
 };
 
 MultiBufs carve_multi(Carver& c, int64_t n, int64_t m, int64_t nrhs, int64_t nvec, const dfi::RowMultiPlan& rm,
-                      bool need_t, bool final8 = false, bool centered = false, int64_t nfac = 1) {
+                      bool need_t, bool final8 = false, bool centered = false, int64_t nfac = 1,
+                      int most = dfi::MULTI_GROUPS) {
   MultiBufs b{};
   b.Bs = c.take<double>((size_t)(nrhs * n));
   b.Bexp = c.take<double>((size_t)(nvec * n));
@@ -675,12 +678,13 @@ MultiBufs carve_multi(Carver& c, int64_t n, int64_t m, int64_t nrhs, int64_t nve
   b.R = c.take<double>((size_t)(nvec * n));
   b.D = c.take<double>((size_t)(nvec * n));
   b.ticket = c.take<uint32_t>(2);
-  const bool two = nvec > dfi::MULTI_VECS;   // passes take two groups of vectors at a time
-  b.T = need_t ? c.take<double>((size_t)(m * dfi::MULTI_VECS)) : nullptr;
-  b.T1 = need_t && two ? c.take<double>((size_t)(m * dfi::MULTI_VECS)) : nullptr;
-  b.Yi = c.take<double>((size_t)(n * 2 * dfi::MULTI_VECS));
-  b.part = c.take<double>(rm.part_bytes / sizeof(double) + 1);
-  b.part1 = need_t && two ? c.take<double>(rm.part_bytes / sizeof(double) + 1) : nullptr;
+  // groups that share a pass: as many as there are, two without the memory for more
+  b.groups = (int)std::min<int64_t>(most, (nvec + dfi::MULTI_VECS - 1) / dfi::MULTI_VECS);
+  for (int g = 0; g < b.groups; ++g) {
+    b.T[g] = need_t ? c.take<double>((size_t)(m * dfi::MULTI_VECS)) : nullptr;
+    b.part[g] = need_t || g == 0 ? c.take<double>(rm.part_bytes / sizeof(double) + 1) : nullptr;
+  }
+  b.Yi = c.take<double>((size_t)(n * std::max(2, b.groups) * dfi::MULTI_VECS));
   b.Zc = c.take<double>((size_t)(nvec * n));
   b.P = c.take<double>((size_t)(nvec * n));
   b.NQ = c.take<double>((size_t)(nvec * n));
@@ -722,8 +726,8 @@ dfisher_status multi_solve(const float* S, int64_t n, int64_t m, int64_t lds, in
       vs.f[c] = V + (r0 + c) * ldv;
       mo.b[c] = b.Bs + (r0 + c) * n;
     }
-    HIP_TRY(dfi::rowpass_multi_launch(rm, S, vs, nullptr, nv, b.part, st));
-    HIP_TRY(dfi::rowpass_multi_reduce(rm, b.part, nv, mo, st));
+    HIP_TRY(dfi::rowpass_multi_launch(rm, S, vs, nv, b.part[0], st));
+    HIP_TRY(dfi::rowpass_multi_reduce(rm, b.part, &nv, 1, &mo, st));
   }
   for (int64_t f = 0; f < nfac; ++f)
     HIP_TRY(hipMemcpyAsync(b.Bexp + f * nrhs * n, b.Bs, (size_t)(nrhs * n) * sizeof(double), hipMemcpyDeviceToDevice, st));
@@ -732,8 +736,15 @@ dfisher_status multi_solve(const float* S, int64_t n, int64_t m, int64_t lds, in
   // refinement: OUT_j = RHS_j - lambda_j U_j - S (S^T U_j), MV vectors per pair of passes (the
   // conjugate-gradient sweeps of solve_y, for every vector at once; RHS = B for the residual of Y,
   // RHS = 0 for -(W P))
-  // (two groups of MV vectors share each pass over S while at least MV + 1 vectors remain: every
-  // load of S then feeds twice the FP64 products)
+  // (up to b.groups groups of MV vectors share each pass over S: its loads and conversions then feed as many
+  // FP64 products)
+  constexpr int MG = dfi::MULTI_GROUPS;
+  // the groups of the pass that begins at vector j0: their sizes, their number and how many vectors in all
+  auto split = [&](int64_t j0, int* nv, int most) {
+    int ng = 0;
+    for (; ng < most && j0 + ng * MV < nvec; ++ng) nv[ng] = (int)std::min<int64_t>(MV, nvec - j0 - ng * MV);
+    return ng;
+  };
   auto group = [&](const double* U, const double* RHS, bool rhs_zero, double* OUT, int64_t j0, int nv,
                    dfi::MultiCols& mc, dfi::MultiOut& mo) {
     for (int c = 0; c < MV; ++c) mc.y[c] = U + (j0 + std::min(c, nv - 1)) * n;
@@ -748,26 +759,20 @@ dfisher_status multi_solve(const float* S, int64_t n, int64_t m, int64_t lds, in
   // tsave (may be null): the passes' T = S^T U of group g goes to tsave + g m MV and stays there
   auto w_pass = [&](const double* U, const double* RHS, bool rhs_zero, double* OUT, double* tsave) -> dfisher_status {
     for (int64_t j0 = 0; j0 < nvec;) {
-      const int nv = (int)std::min<int64_t>(MV, nvec - j0);
-      const int nv1 = b.T1 ? (int)std::min<int64_t>(MV, std::max<int64_t>(0, nvec - j0 - MV)) : 0;
-      double* T0 = tsave ? tsave + (j0 / MV) * m * MV : b.T;
-      double* T1 = tsave ? tsave + (j0 / MV + 1) * m * MV : b.T1;
-      dfi::MultiCols mc{}, mc1{};
-      dfi::MultiOut mo{}, mo1{};
-      group(U, RHS, rhs_zero, OUT, j0, nv, mc, mo);
-      if (nv1 > 0) {
-        group(U, RHS, rhs_zero, OUT, j0 + MV, nv1, mc1, mo1);
-        HIP_TRY(dfi::colpass_multi_launch2(S, n, m, lds, mc, nv, mc1, nv1, 2, T0, T1, b.Yi, st));
-        HIP_TRY(dfi::rowpass_multi_launch2(rm, S, T0, nv, T1, nv1, b.part, b.part1, st));
-        HIP_TRY(dfi::rowpass_multi_reduce(rm, b.part, nv, mo, st));
-        HIP_TRY(dfi::rowpass_multi_reduce(rm, b.part1, nv1, mo1, st));
-      } else {
-        HIP_TRY(dfi::colpass_multi_launch(S, n, m, lds, mc, nv, 2, T0, b.Yi, st));
-        dfi::MultiVecs none{};
-        HIP_TRY(dfi::rowpass_multi_launch(rm, S, none, T0, nv, b.part, st));
-        HIP_TRY(dfi::rowpass_multi_reduce(rm, b.part, nv, mo, st));
+      int nv[MG];
+      const int ng = split(j0, nv, b.groups);
+      dfi::MultiCols mc[MG]{};
+      dfi::MultiOut mo[MG]{};
+      double* T[MG];
+      for (int g = 0; g < ng; ++g) {
+        T[g] = tsave ? tsave + (j0 / MV + g) * m * MV : b.T[g];
+        group(U, RHS, rhs_zero, OUT, j0 + g * MV, nv[g], mc[g], mo[g]);
       }
-      j0 += nv + nv1;
+      const dfi::RowMultiPlan rg = dfi::rowmulti_groups(rm, ng);
+      HIP_TRY(dfi::colpass_multi_groups(S, n, m, lds, mc, nv, ng, 2, T, b.Yi, st));
+      HIP_TRY(dfi::rowpass_multi_groups(rg, S, T, nv, ng, b.part, st));
+      HIP_TRY(dfi::rowpass_multi_reduce(rg, b.part, nv, ng, mo, st));
+      j0 += ng * MV;
     }
     return DFISHER_OK;
   };
@@ -798,7 +803,7 @@ dfisher_status multi_solve(const float* S, int64_t n, int64_t m, int64_t lds, in
                               sweeps >= 2 ? b.Uacc : nullptr, b.alpha8, b.cs, V, ldv, X, ldx, x_fp64, st));
     skip = b.flag8;
   }
-  // x = (v - S^T y) / lambda, up to 2 MV vectors per pass
+  // x = (v - S^T y) / lambda, as many groups per pass
   const size_t xel = x_fp64 ? sizeof(double) : sizeof(float);
   auto apply_group = [&](int64_t j0, int nv, dfi::MultiCols& mc) {
     for (int c = 0; c < MV; ++c) {
@@ -810,18 +815,12 @@ dfisher_status multi_solve(const float* S, int64_t n, int64_t m, int64_t lds, in
     }
   };
   for (int64_t j0 = 0; j0 < nvec;) {
-    const int nv = (int)std::min<int64_t>(MV, nvec - j0);
-    const int nv1 = (int)std::min<int64_t>(MV, std::max<int64_t>(0, nvec - j0 - MV));
-    dfi::MultiCols mc{}, mc1{};
-    apply_group(j0, nv, mc);
-    if (nv1 > 0) {
-      apply_group(j0 + MV, nv1, mc1);
-      HIP_TRY(dfi::colpass_multi_launch2(S, n, m, lds, mc, nv, mc1, nv1, x_fp64 ? 1 : 0, nullptr, nullptr, b.Yi, st,
-                                         skip));
-    } else {
-      HIP_TRY(dfi::colpass_multi_launch(S, n, m, lds, mc, nv, x_fp64 ? 1 : 0, nullptr, b.Yi, st, skip));
-    }
-    j0 += nv + nv1;
+    int nv[MG];
+    const int ng = split(j0, nv, std::min(std::max(2, b.groups), MG));
+    dfi::MultiCols mc[MG]{};
+    for (int g = 0; g < ng; ++g) apply_group(j0 + g * MV, nv[g], mc[g]);
+    HIP_TRY(dfi::colpass_multi_groups(S, n, m, lds, mc, nv, ng, x_fp64 ? 1 : 0, nullptr, b.Yi, st, skip));
+    j0 += ng * MV;
   }
   return DFISHER_OK;
 }
@@ -2029,12 +2028,19 @@ dfisher_status dfisher_factor_solve(dfisher_factor* f, const float* V, int64_t n
   const int64_t n = f->n, m = f->m;
   if (nrhs > 65535) return fail(DFISHER_E_UNSUPPORTED, "nrhs = %lld > 65535", (long long)nrhs);
   const dfi::RowMultiPlan rm = dfi::rowmulti_plan(n, m, f->lds);
-  Carver c;
-  MultiBufs mb = carve_multi(c, n, m, nrhs, nrhs, rm, f->opt.sweeps > 0);
-  DF_TRY(ensure_ws(ctx, c.off));
-  c = Carver{};
-  c.base = static_cast<char*>(ctx->ws);
-  mb = carve_multi(c, n, m, nrhs, nrhs, rm, f->opt.sweeps > 0);
+  int most = dfi::MULTI_GROUPS;
+  MultiBufs mb;
+  auto lay = [&](char* base) {
+    Carver c;
+    c.base = base;
+    mb = carve_multi(c, n, m, nrhs, nrhs, rm, f->opt.sweeps > 0, false, false, 1, most);
+    return c.off;
+  };
+  if (ensure_ws(ctx, lay(nullptr)) != DFISHER_OK) {   // without the memory, two groups of vectors a pass
+    most = 2;
+    DF_TRY(ensure_ws(ctx, lay(nullptr)));
+  }
+  lay(static_cast<char*>(ctx->ws));
   const double lam = f->lambda;
   DF_TRY(multi_solve(f->S, n, m, f->lds, 1, f->L, f->Dinv, &lam, V, nrhs, ldv, X, ldx, f->opt.x_fp64, f->opt.sweeps, rm,
                      mb, st));
@@ -2373,6 +2379,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
   }
   HIP_TRY(dfi::complex_embed(X.G, n, lambda, B.W, st));
   // b = E v = [A vr - B vi; B vr + A vi] from Z vr and Z vi (one pass over Z)
+  const int two = 2;
   HIP_TRY(dfi::deinterleave(v, m, X.vp, st));
   {
     dfi::MultiVecs vs{};
@@ -2381,8 +2388,8 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
     dfi::MultiOut mo{};
     mo.b[0] = X.P;
     mo.b[1] = X.Q;
-    HIP_TRY(dfi::rowpass_multi_launch(rm, Z, vs, nullptr, 2, X.mpart, st));
-    HIP_TRY(dfi::rowpass_multi_reduce(rm, X.mpart, 2, mo, st));
+    HIP_TRY(dfi::rowpass_multi_launch(rm, Z, vs, two, X.mpart, st));
+    HIP_TRY(dfi::rowpass_multi_reduce(rm, &X.mpart, &two, 1, &mo, st));
     HIP_TRY(dfi::complex_combine(X.P, X.Q, n, 1.0, nullptr, nullptr, 0.0, B.b, st));
   }
   // E^T u for u = [u1; u2]: t1 = Z^T [u1; u2], t2 = Z^T [u2; -u1], into T columns 0 and 1
@@ -2390,18 +2397,17 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
     HIP_TRY(dfi::complex_colvecs(u, n, X.U1, X.U2, st));
     dfi::MultiCols mc{};
     for (int c = 0; c < MV; ++c) mc.y[c] = c == 1 ? X.U2 : X.U1;
-    HIP_TRY(dfi::colpass_multi_launch(Z, N, m, lds, mc, 2, 2, X.T, X.Yi, st));
+    HIP_TRY(dfi::colpass_multi_groups(Z, N, m, lds, &mc, &two, 1, 2, &X.T, X.Yi, st));
     return DFISHER_OK;
   };
   // out = rhs - lambda u - E (E^T u)
   const WOp wop = [&](const double* u, const double* rhs, double* out, double*, double*) -> dfisher_status {
     DF_TRY(et(u));
-    dfi::MultiVecs none{};
     dfi::MultiOut mo{};
     mo.b[0] = X.P;
     mo.b[1] = X.Q;
-    HIP_TRY(dfi::rowpass_multi_launch(rm, Z, none, X.T, 2, X.mpart, st));
-    HIP_TRY(dfi::rowpass_multi_reduce(rm, X.mpart, 2, mo, st));
+    HIP_TRY(dfi::rowpass_multi_groups(rm, Z, &X.T, &two, 1, &X.mpart, st));
+    HIP_TRY(dfi::rowpass_multi_reduce(rm, &X.mpart, &two, 1, &mo, st));
     HIP_TRY(dfi::complex_combine(X.P, X.Q, n, -1.0, rhs, u, lambda, out, st));
     return DFISHER_OK;
   };
@@ -2483,6 +2489,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   // inverses and statuses, and the multi-vector buffers
   // (packed: the factors' packed copies too, in the Gram partials where they fit)
   bool packed = true;
+  int most = dfi::MULTI_GROUPS;   // groups of vectors a pass
   double* packs = nullptr;
   auto layout = [&](char* base, SolveBufs& B, double*& Lall, double*& Dall, double*& dkk, int64_t*& dinfo,
                     int32_t*& dflag, MultiBufs& mb) {
@@ -2499,7 +2506,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
                   ? reinterpret_cast<double*>(B.gpart) : c.take<double>(chol_scratch_bytes(n, nlam) / sizeof(double));
     dinfo = c.take<int64_t>((size_t)nlam);
     dflag = c.take<int32_t>((size_t)nlam);
-    mb = carve_multi(c, n, m, nrhs, nvec, rm, o.sweeps != 0, final8, is_centered(o), nlam);
+    mb = carve_multi(c, n, m, nrhs, nvec, rm, o.sweeps != 0, final8, is_centered(o), nlam, most);
     return c.off;
   };
   SolveBufs B;
@@ -2511,7 +2518,11 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   // without the memory (or, in a capture, the workspace of the call before it) for the packed copies the
   // factorisations run in place
   auto no_room = [&]() { return capturing ? need > ctx->ws_bytes : ensure_ws(ctx, need) != DFISHER_OK; };
-  if (no_room()) {
+  if (no_room()) {   // two groups of vectors a pass
+    most = 2;
+    need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
+  }
+  if (most == 2 && no_room()) {
     packed = false;
     need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
   }

@@ -167,6 +167,7 @@ hipError_t refine_reduce_grouped(const ReduceJob* jobs_dev, int njobs, int64_t n
 // ----------------------------------------------------------------------------- multi-vector passes
 // One pass over S for up to MULTI_VECS vectors (batched right-hand sides / damping values).
 constexpr int MULTI_VECS = 16;
+constexpr int MULTI_GROUPS = 4;       // groups of MULTI_VECS vectors a pass takes at most
 struct MultiVecs {                 // FP32 input vectors of length m (row pass)
   const float* f[MULTI_VECS];
 };
@@ -188,27 +189,23 @@ struct RowMultiPlan {
   size_t part_bytes;               // nchunk * MULTI_VECS * n * 8
 };
 RowMultiPlan rowmulti_plan(int64_t n, int64_t m, int64_t lds);
-// part <- per-group partials of S V_c, c < nv. V_c = vs.f[c] (FP32) or, with T != nullptr, the FP64
-// interleaved T[k * MULTI_VECS + c] written by colpass_multi_launch mode 2.
-hipError_t rowpass_multi_launch(const RowMultiPlan& p, const float* S, const MultiVecs& vs, const double* T, int nv,
-                                double* part, hipStream_t st);
-hipError_t rowpass_multi_reduce(const RowMultiPlan& p, const double* part, int nv, const MultiOut& out,
+// The plan a pass of ng groups of vectors and its reduction use (no more column groups than p has).
+RowMultiPlan rowmulti_groups(const RowMultiPlan& p, int ng);
+// part <- per-group partials of S V_c, c < nv, for FP32 vectors V_c = vs.f[c].
+hipError_t rowpass_multi_launch(const RowMultiPlan& p, const float* S, const MultiVecs& vs, int nv, double* part,
                                 hipStream_t st);
-// t_c = S^T y_c (c < nc). mode 2: T[k * MULTI_VECS + c] = t_c[k] (T: m * MULTI_VECS doubles); mode 0 / 1:
-// x_c = (v_c - t_c) / lam_c as FP32 / FP64. Yi: scratch of n * MULTI_VECS doubles (the y_c
-// interleaved by row).
-hipError_t colpass_multi_launch(const float* S, int64_t n, int64_t m, int64_t lds, const MultiCols& mc, int nc,
-                                int mode, double* T, double* Yi, hipStream_t st, const int* skip = nullptr);
-// Two groups of vectors (mc0: nc0, mc1: nc1, each 1 .. MULTI_VECS) in one pass over S: every load
-// of S feeds both groups' products. mode 2 writes T0 and T1 (each m * MULTI_VECS); Yi: scratch of
-// n * 2 * MULTI_VECS doubles.
-hipError_t colpass_multi_launch2(const float* S, int64_t n, int64_t m, int64_t lds, const MultiCols& mc0, int nc0,
-                                 const MultiCols& mc1, int nc1, int mode, double* T0, double* T1, double* Yi,
-                                 hipStream_t st, const int* skip = nullptr);
-// The row pass over two groups' T (T0: nv0, T1: nv1 vectors) in one pass over S; partials into
-// part0 and part1 (each of the plan's part_bytes), reduced with rowpass_multi_reduce per group.
-hipError_t rowpass_multi_launch2(const RowMultiPlan& p, const float* S, const double* T0, int nv0, const double* T1,
-                                 int nv1, double* part0, double* part1, hipStream_t st);
+// The same for ng groups of FP64 vectors T[g][k * MULTI_VECS + c], c < nv[g], as written by colpass_multi_groups
+// mode 2, in one pass over S: part[g] <- group g's partials (p from rowmulti_groups).
+hipError_t rowpass_multi_groups(const RowMultiPlan& p, const float* S, const double* const* T, const int* nv, int ng,
+                                double* const* part, hipStream_t st);
+hipError_t rowpass_multi_reduce(const RowMultiPlan& p, const double* const* part, const int* nv, int ng,
+                                const MultiOut* out, hipStream_t st);
+// t_c = S^T y_c for ng groups of nc[g] vectors, in one pass over S. mode 2: T[g][k * MULTI_VECS + c] = t_c[k] (T[g]:
+// m * MULTI_VECS doubles); mode 0 / 1: x_c = (v_c - t_c) / lam_c as FP32 / FP64. Yi: scratch of n * ng * MULTI_VECS
+// doubles (the y_c interleaved by row).
+hipError_t colpass_multi_groups(const float* S, int64_t n, int64_t m, int64_t lds, const MultiCols* mc, const int* nc,
+                                int ng, int mode, double* const* T, double* Yi, hipStream_t st,
+                                const int* skip = nullptr);
 // y += d over len entries
 hipError_t axpy_many(double* y, const double* d, int64_t len, hipStream_t st);
 
