@@ -37,10 +37,26 @@ __global__ void t_axpy_kernel(double* __restrict__ T, const double* __restrict__
   if (j < m) T[j] = fma(alpha[0], U[j], T[j]);
 }
 
-__global__ void __launch_bounds__(DT)
-final_decide_kernel(int64_t n, double* __restrict__ y, const double* __restrict__ z, const double* __restrict__ b,
-                    const double* __restrict__ d, double lambda, const int* __restrict__ cflag, double est_max,
-                    float* __restrict__ zf, double* __restrict__ abar_out, int* __restrict__ use) {
+// T_p += alpha_p U_p for many problems in one launch, four columns a thread
+constexpr int AXPY_COLS = 1024;
+__global__ void __launch_bounds__(256) t_axpy_jobs_kernel(JobList<AxpyJob> l) {
+  const int k = job_of(l, blockIdx.x);
+  const AxpyJob& j = l.job[k];
+  if (*j.skip) return;
+  const double a = *j.alpha;
+  const int64_t c0 = (blockIdx.x - l.blk0[k]) * AXPY_COLS + threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < AXPY_COLS / 256; ++u) {
+    const int64_t c = c0 + 256 * u;
+    if (c < j.m) j.T[c] = fma(a, j.U[c], j.T[c]);
+  }
+}
+
+__device__ __forceinline__ void final_decide_body(int64_t n, double* __restrict__ y, const double* __restrict__ z,
+                                                  const double* __restrict__ b, const double* __restrict__ d,
+                                                  double lambda, const int* __restrict__ cflag, double est_max,
+                                                  float* __restrict__ zf, double* __restrict__ abar_out,
+                                                  int* __restrict__ use) {
   __shared__ double red[DT];
   const int tid = threadIdx.x;
   const int centered = cflag ? *cflag : 0;   // uniform
@@ -69,20 +85,31 @@ final_decide_kernel(int64_t n, double* __restrict__ y, const double* __restrict_
   }
 }
 
+__global__ void __launch_bounds__(DT)
+final_decide_kernel(int64_t n, double* __restrict__ y, const double* __restrict__ z, const double* __restrict__ b,
+                    const double* __restrict__ d, double lambda, const int* __restrict__ cflag, double est_max,
+                    float* __restrict__ zf, double* __restrict__ abar_out, int* __restrict__ use) {
+  final_decide_body(n, y, z, b, d, lambda, cflag, est_max, zf, abar_out, use);
+}
+
+__global__ void __launch_bounds__(DT) final_decide_jobs_kernel(JobList<Final8Job> l, double est_max) {
+  const Final8Job& j = l.job[blockIdx.x];
+  final_decide_body(j.n, j.y, j.z, j.b, j.d, j.lambda, j.centered, est_max, j.zf, j.abar, j.use);
+}
+
 // One workgroup per 64-column block: thread (row slot g, quarter c) takes 16 columns (one 16-byte
 // load of codes per row) of the rows g, g + 64, ..., with FP32 products and sums (the term is a
 // small correction: 1e-6 relative is far below what it needs); the 64 row slots are then added in
 // a fixed order.
-__global__ void __launch_bounds__(AT)
-fp8_apply_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ sc, int64_t n, int64_t m,
-                 const float* __restrict__ zf, const double* __restrict__ T, const double* __restrict__ cs,
-                 const double* __restrict__ abar, const float* __restrict__ v, double lambda, void* __restrict__ x,
-                 int x64, const int* __restrict__ use) {
+__device__ __forceinline__ void fp8_apply_body(const uint8_t* __restrict__ q, const uint8_t* __restrict__ sc, int64_t n,
+                                               int64_t m, const float* __restrict__ zf, const double* __restrict__ T,
+                                               const double* __restrict__ cs, const double* __restrict__ abar,
+                                               const float* __restrict__ v, double lambda, void* __restrict__ x,
+                                               int x64, const int* __restrict__ use, int64_t jb) {
   if (!*use) return;
   __shared__ float red[64][65];
   const int tid = threadIdx.x;
   const int g = tid >> 2, cq = tid & 3;
-  const int64_t jb = blockIdx.x;
   const int64_t j0 = jb * 64 + cq * 16;   // this thread's first column
   const uint8_t* qb = q + jb * n * 64 + cq * 16;                     // row i at qb + 64 i
   const uint8_t* sb = sc + (j0 >> 7) * n * 4 + ((j0 >> 5) & 3);      // row i at sb + 4 i
@@ -126,6 +153,20 @@ fp8_apply_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ sc, 
       else static_cast<float*>(x)[j] = (float)xv;
     }
   }
+}
+
+__global__ void __launch_bounds__(AT)
+fp8_apply_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ sc, int64_t n, int64_t m,
+                 const float* __restrict__ zf, const double* __restrict__ T, const double* __restrict__ cs,
+                 const double* __restrict__ abar, const float* __restrict__ v, double lambda, void* __restrict__ x,
+                 int x64, const int* __restrict__ use) {
+  fp8_apply_body(q, sc, n, m, zf, T, cs, abar, v, lambda, x, x64, use, blockIdx.x);
+}
+
+__global__ void __launch_bounds__(AT) fp8_apply_jobs_kernel(JobList<Final8Job> l, int x64) {
+  const int k = job_of(l, blockIdx.x);
+  const Final8Job& j = l.job[k];
+  fp8_apply_body(j.q, j.sc, j.n, j.m, j.zf, j.T, j.cs, j.abar, j.v, j.lambda, j.x, x64, j.use, blockIdx.x - l.blk0[k]);
 }
 
 // ---------------------------------------------------------------- many vectors (batched call)
@@ -408,6 +449,27 @@ hipError_t fp8_apply(const uint8_t* q, const uint8_t* sc, int64_t ldq, int64_t n
   return hipGetLastError();
 }
 
+
+hipError_t t_axpy_jobs(const AxpyJob* jobs, int count, hipStream_t st) {
+  return launch_jobs(jobs, count, [](const AxpyJob& j) { return (j.m + AXPY_COLS - 1) / AXPY_COLS; },
+                     [&](const JobList<AxpyJob>& l, unsigned b) {
+                       hipLaunchKernelGGL(t_axpy_jobs_kernel, dim3(b), dim3(256), 0, st, l);
+                     });
+}
+
+hipError_t final8_jobs(const Final8Job* jobs, int count, double est_max, int x64, hipStream_t st) {
+  for (int k = 0; k < count; ++k)
+    if ((jobs[k].ldq & 127) != 0 || jobs[k].ldq < jobs[k].m) return hipErrorInvalidValue;
+  const hipError_t e = launch_jobs(jobs, count, [](const Final8Job&) { return (int64_t)1; },
+                                   [&](const JobList<Final8Job>& l, unsigned b) {
+                                     hipLaunchKernelGGL(final_decide_jobs_kernel, dim3(b), dim3(DT), 0, st, l, est_max);
+                                   });
+  if (e != hipSuccess) return e;
+  return launch_jobs(jobs, count, [](const Final8Job& j) { return (j.m + 63) / 64; },
+                     [&](const JobList<Final8Job>& l, unsigned b) {
+                       hipLaunchKernelGGL(fp8_apply_jobs_kernel, dim3(b), dim3(AT), 0, st, l, x64);
+                     });
+}
 
 hipError_t t_axpy_multi(double* T, const double* U, const double* alpha, int64_t m, int64_t nvec, hipStream_t st) {
   const int64_t tot = (nvec + 15) / 16 * m * 16;

@@ -1156,25 +1156,29 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
   // work items, then each problem's reduction, projection and shift; else the whole stage per
   // problem.
   if (G.ngram > 0) {
+    std::vector<dfi::PrepJob> prep;
+    std::vector<dfi::GramReduceJob> red;
+    std::vector<dfi::ProjectJob> proj;
     for (int32_t p : order) {
       const size_t q = (size_t)p;
-      double* rpart = U.shared.rpart;
-      HIP_TRY(dfi::rowpass_launch(U.rp[q], S[p], v[p], nullptr, true, true, rpart, st, U.q8all + U.qoff[q],
-                                  U.sc8all + U.soff[q], dfi::fp8_ldq(m[p]), true));
-      HIP_TRY(dfi::rowpass_reduce(U.rp[q], rpart, true, true, U.b + U.voff[q], U.d + U.voff[q], nullptr, nullptr, 0.0,
-                                  st));
+      float* gp = U.gall + U.goff[q];   // in turn the row pass's partials, the partial tiles, the projection's tile sums
+      const dfi::GramPlan& g = U.gpg[q];
+      if (g.part_bytes < U.rp[q].part_bytes || g.part_bytes < dfi::gram_project_work_bytes(n[p]))
+        return fail(DFISHER_E_DEVICE, "the partial tiles of problem %d are too small to share", (int)p);
+      prep.push_back(dfi::PrepJob{U.rp[q], S[p], v[p], reinterpret_cast<double*>(gp), U.q8all + U.qoff[q],
+                                  U.sc8all + U.soff[q], dfi::fp8_ldq(m[p]), U.b + U.voff[q], U.d + U.voff[q]});
+      red.push_back(dfi::GramReduceJob{gp, U.d + U.voff[q], U.W + U.woff[q], lambda[p], n[p], g.ntri, g.nslice});
+      proj.push_back(dfi::ProjectJob{U.W + U.woff[q], reinterpret_cast<double*>(gp), U.zc + U.voff[q],
+                                     U.cs8 ? U.use8 + np + p : nullptr, lambda[p], n[p]});
     }
+    HIP_TRY(dfi::rowpass_prep_jobs(prep.data(), np, st));
     HIP_TRY(dfi::gram_launch_fp8_grouped(G.gram, G.ngram, G.gram_nwg, st));
+    HIP_TRY(dfi::gram_reduce_jobs(red.data(), np, st));
+    if (is_centered(o)) HIP_TRY(dfi::gram_project_jobs(proj.data(), np, st));
   }
   for (int32_t p : order) {
     if (G.ngram > 0) {
-      const size_t q = (size_t)p;
-      double* Wp = U.W + U.woff[q];
-      float* gp = U.gall + U.goff[q];
-      HIP_TRY(dfi::gram_reduce(U.gpg[q], S[p], gp, U.d + U.voff[q], lambda[p], Wp, 0, st));
-      if (is_centered(o))   // the partial tiles are free again: they hold the projection's tile sums
-        HIP_TRY(dfi::gram_project(Wp, n[p], 1, lambda[p], 0, reinterpret_cast<double*>(gp), U.zc + U.voff[q], st,
-                                  U.cs8 ? U.use8 + np + p : nullptr));
+      double* Wp = U.W + U.woff[(size_t)p];
       if (o.shift_policy == DFISHER_SHIFT_ALWAYS) {
         const double scale = 2.0 * std::sqrt((double)n[p]) * gram_unit(o.gram_prec, m[p]);
         HIP_TRY(dfi::diag_max(Wp, n[p], U.dmax + p, st));
@@ -1291,12 +1295,15 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
           DF_TRY(w_pass(p, U.p, U.zero, true, U.nq, U.stop + jpos[(size_t)p],
                         U.f8 ? U.U8 + U.moff[(size_t)p] : nullptr));   // -(W_p p_p)
       HIP_TRY(dfi::pcg_step(seg, 0, 0, cont, U.p, U.nq, U.y, U.r, U.rz, U.rr, st, U.stop, U.a8));
-      if (U.f8)   // T_p += alpha_p S^T p_p for the problems that took this step
+      if (U.f8) {   // T_p += alpha_p S^T p_p for the problems that took this step
+        std::vector<dfi::AxpyJob> ax;
         for (int32_t p : order)
           if (sw[(size_t)p] > s) {
             const int64_t mo = U.moff[(size_t)p];
-            HIP_TRY(dfi::t_axpy(U.T8 + mo, U.U8 + mo, U.a8 + jpos[(size_t)p], m[p], st, U.stop + jpos[(size_t)p]));
+            ax.push_back(dfi::AxpyJob{U.T8 + mo, U.U8 + mo, U.a8 + jpos[(size_t)p], U.stop + jpos[(size_t)p], m[p]});
           }
+        HIP_TRY(dfi::t_axpy_jobs(ax.data(), (int)ax.size(), st));
+      }
     }
   }
   if (o.final_resid) {   // the returned iterate's residual, per problem (not applied)
@@ -1309,21 +1316,34 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
   // x_p = (v_p - S_p^T y_p) / lambda_p: with the FP8 final step, the last correction (left in zc)
   // through the problem's codes when the device finds that accurate enough, else y_p += zc_p and
   // the exact column pass (one of the two returns at once)
+  std::vector<dfi::Final8Job> fin;
+  std::vector<dfi::ColJob> col;
+  int64_t blocks = 0;
   for (int32_t p : order) {
-    const int64_t off = U.voff[(size_t)p];
+    const size_t q = (size_t)p;
+    const int64_t off = U.voff[q];
     const int* use = nullptr;
-    if (U.f8 && sw[(size_t)p] > 0) {
-      const int64_t mo = U.moff[(size_t)p];
+    if (U.f8 && sw[q] > 0) {
+      const int64_t mo = U.moff[q];
       use = U.use8 + p;
-      HIP_TRY(dfi::final_decide(n[p], U.y + off, U.zc + off, U.b + off, U.d + off, lambda[p],
-                                U.cs8 ? U.use8 + np + p : nullptr, FINAL8_EST_MAX, U.zf8 + off, U.a8 + np + p, U.use8 + p,
-                                st));
-      HIP_TRY(dfi::fp8_apply(U.q8all + U.qoff[(size_t)p], U.sc8all + U.soff[(size_t)p], dfi::fp8_ldq(m[p]), n[p], m[p],
-                             U.zf8 + off, U.T8 + mo, U.cs8 ? U.cs8 + mo : nullptr, U.a8 + np + p, v[p], lambda[p], x[p],
-                             o.x_fp64, U.use8 + p, st));
+      fin.push_back(dfi::Final8Job{U.y + off, U.zc + off, U.b + off, U.d + off, U.cs8 ? U.use8 + np + p : nullptr,
+                                   U.zf8 + off, U.a8 + np + p, U.use8 + p, U.q8all + U.qoff[q], U.sc8all + U.soff[q],
+                                   U.T8 + mo, U.cs8 ? U.cs8 + mo : nullptr, v[p], x[p], lambda[p], n[p], m[p],
+                                   dfi::fp8_ldq(m[p])});
     }
-    HIP_TRY(dfi::colpass_launch(U.cp[(size_t)p], S[p], n[p], m[p], lds[p], U.y + off, v[p], lambda[p], x[p], o.x_fp64,
-                                U.shared.cpart, st, use));
+    col.push_back(dfi::ColJob{S[p], U.y + off, v[p], x[p], use, lambda[p], n[p], m[p], lds[p]});
+    blocks += dfi::colpass_blocks(m[p]);
+  }
+  HIP_TRY(dfi::final8_jobs(fin.data(), (int)fin.size(), FINAL8_EST_MAX, o.x_fp64, st));
+  // one launch where the column blocks fill the device (256 compute units x 8 workgroups) without a split of the rows;
+  // else per problem
+  if (blocks >= 2048) {
+    HIP_TRY(dfi::colpass_jobs(col.data(), np, o.x_fp64 ? 1 : 0, st));
+  } else {
+    for (const dfi::ColJob& j : col) {
+      const dfi::ColPassPlan cp = dfi::colpass_plan(j.n, j.m);
+      HIP_TRY(dfi::colpass_launch(cp, j.S, j.n, j.m, j.lds, j.y, j.v, j.lam, j.x, o.x_fp64, U.shared.cpart, st, j.skip));
+    }
   }
   return DFISHER_OK;
 }

@@ -150,6 +150,113 @@ struct LineJob {
 };
 hipError_t refine_line_grouped_launch(const LineJob* jobs_dev, int njobs, int nch, bool cs, int64_t nwg,
                                       hipStream_t st);
+// The same step for many problems in one launch, the jobs by value; job k owns workgroups [blk0[k], blk0[k + 1]). (A launch and
+// its gap cost as much as a small step, and a large one alone ends with part of the chip idle: 24 problems of 5.9 GB, row passes
+// 2065 -> 1530 us, the small steps 1400 -> 400, the whole call 9.2 -> 7.9 ms with 97 launches instead of 429.)
+template <class J>
+struct JobList {
+  static constexpr int CAP = (int)(3584 / (sizeof(J) + sizeof(int64_t)));
+  J job[CAP];
+  int64_t blk0[CAP + 1];
+  int count;
+};
+template <class J>
+__device__ __forceinline__ int job_of(const JobList<J>& l, int64_t w) {   // w uniform
+  int lo = 0, hi = l.count - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (l.blk0[mid] <= w) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+// launch(list) for the jobs in order, as many as a list holds at a time; blocks(job): its workgroups.
+template <class J, class B, class F>
+hipError_t launch_jobs(const J* jobs, int count, B blocks, F launch) {
+  for (int k0 = 0; k0 < count;) {
+    JobList<J> l;
+    l.count = 0;
+    l.blk0[0] = 0;
+    for (; k0 < count && l.count < JobList<J>::CAP; ++k0, ++l.count) {
+      l.job[l.count] = jobs[k0];
+      l.blk0[l.count + 1] = l.blk0[l.count] + blocks(jobs[k0]);
+    }
+    launch(l, (unsigned)l.blk0[l.count]);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// Row passes with the scaled-FP8 codes (rowpass_launch with `blocked`), and their reductions to b and d.
+struct PrepJob {
+  RowPassPlan p;
+  const float* S;
+  const float* v;
+  double* part;
+  uint8_t* q;
+  uint8_t* sc;
+  int64_t ldq;
+  double* b;
+  double* d;
+};
+hipError_t rowpass_prep_jobs(const PrepJob* jobs, int count, hipStream_t st);
+// Column passes x = (v - S^T y) / lambda (mode 0 FP32, 1 FP64), rows not split.
+struct ColJob {
+  const float* S;
+  const double* y;
+  const float* v;
+  void* x;
+  const int* skip;
+  double lam;
+  int64_t n, m, lds;
+};
+int64_t colpass_blocks(int64_t m);
+hipError_t colpass_jobs(const ColJob* jobs, int count, int mode, hipStream_t st);
+
+// Reductions of scaled-FP8 Grams (gram_reduce without mirror), projections (gram_project of one segment), the
+// T += alpha U steps (skip: device int) and the final steps through the codes (final_decide, fp8_apply).
+struct GramReduceJob {
+  const float* part;
+  const double* d;
+  double* W;
+  double lambda;
+  int64_t n, ntri, nslice;
+};
+hipError_t gram_reduce_jobs(const GramReduceJob* jobs, int count, hipStream_t st);
+struct ProjectJob {
+  double* W;
+  double* work;
+  double* r;
+  int* applied;
+  double lambda;
+  int64_t n;
+};
+hipError_t gram_project_jobs(const ProjectJob* jobs, int count, hipStream_t st);
+struct AxpyJob {
+  double* T;
+  const double* U;
+  const double* alpha;
+  const int* skip;
+  int64_t m;
+};
+hipError_t t_axpy_jobs(const AxpyJob* jobs, int count, hipStream_t st);
+struct Final8Job {
+  double* y;
+  const double *z, *b, *d;
+  const int* centered;
+  float* zf;
+  double* abar;
+  int* use;
+  const uint8_t *q, *sc;
+  const double *T, *cs;
+  const float* v;
+  void* x;
+  double lambda;
+  int64_t n, m, ldq;
+};
+hipError_t final8_jobs(const Final8Job* jobs, int count, double est_max, int x64, hipStream_t st);
+
 // Their residuals in one launch: job j owns blocks [blk0, blk0 + ceil(n / 16)) and forms
 // out = rhs - lam u - sum of its ngroups partials (refine_pass_reduce's arithmetic). nblk = the last
 // blk0 + ceil(n / 16).

@@ -275,13 +275,13 @@ __device__ __forceinline__ void colpass_store(void* out, const float* v, double 
 // Grid: x = column blocks of CP_COLS, y = row splits of `rps` rows. nsplit == 1 stores the final
 // result; otherwise FP64 partial sums go to part[split * m + col].
 template <int MODE>
-__global__ void __launch_bounds__(CP_THREADS)
-colpass_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, const double* __restrict__ y,
-               const float* v, double lam, void* out, double* __restrict__ part, int64_t rps,
-               const int* __restrict__ skip) {
+__device__ __forceinline__ void colpass_body(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds,
+                                             const double* __restrict__ y, const float* v, double lam, void* out,
+                                             double* __restrict__ part, int64_t rps, const int* __restrict__ skip,
+                                             int64_t colblock, int64_t split) {
   if (skip && *skip) return;
-  const int64_t col = (int64_t)blockIdx.x * CP_COLS + 4 * threadIdx.x;
-  const int64_t r0 = (int64_t)blockIdx.y * rps;
+  const int64_t col = colblock * CP_COLS + 4 * threadIdx.x;
+  const int64_t r0 = split * rps;
   const int64_t r1 = min(n, r0 + rps);
   double t[4] = {0.0, 0.0, 0.0, 0.0};
   const bool full = col + 4 <= m;
@@ -322,11 +322,27 @@ colpass_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, c
   if (part == nullptr) {
     colpass_store<MODE>(out, v, lam, col, m, t);
   } else {
-    double* pp = part + (int64_t)blockIdx.y * m;
+    double* pp = part + split * m;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (col + e < m) pp[col + e] = t[e];
   }
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(CP_THREADS)
+colpass_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, const double* __restrict__ y,
+               const float* v, double lam, void* out, double* __restrict__ part, int64_t rps,
+               const int* __restrict__ skip) {
+  colpass_body<MODE>(S, n, m, lds, y, v, lam, out, part, rps, skip, blockIdx.x, blockIdx.y);
+}
+
+// many problems in one launch: enough column blocks between them, so that no rows are split
+template <int MODE>
+__global__ void __launch_bounds__(CP_THREADS) colpass_jobs_kernel(JobList<ColJob> l) {
+  const int k = job_of(l, blockIdx.x);
+  const ColJob& j = l.job[k];
+  colpass_body<MODE>(j.S, j.n, j.m, j.lds, j.y, j.v, j.lam, j.x, nullptr, j.n, j.skip, blockIdx.x - l.blk0[k], 0);
 }
 
 template <int MODE>
@@ -360,17 +376,15 @@ constexpr int RPREP_COLS = 256;
 constexpr int RPREP_STAGE = RP_RPW * RPREP_COLS * 4;   // bytes per wave: 8 rows x 256 columns x (hi + lo)
 
 template <bool WANT_B, int QM>
-__global__ void __launch_bounds__(64 * RP_WAVES)
-rowpass_prep_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, const float* __restrict__ v,
-                    int64_t cg, double* __restrict__ part, uint8_t* __restrict__ q, uint8_t* __restrict__ sc,
-                    int64_t ldq) {
+__device__ __forceinline__ void rowpass_prep_body(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds,
+                                                  const float* __restrict__ v, int64_t cg, double* __restrict__ part,
+                                                  uint8_t* __restrict__ q, uint8_t* __restrict__ sc, int64_t ldq,
+                                                  int64_t rowblock, int64_t g, int64_t ngroups) {
   __shared__ __align__(16) uint8_t stage_all[RP_WAVES][RPREP_STAGE];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   uint8_t* stg = stage_all[wave];
-  const int64_t row0 = ((int64_t)blockIdx.x * RP_WAVES + wave) * RP_RPW;
-  const int64_t g = blockIdx.y;
-  const int64_t ngroups = gridDim.y;
+  const int64_t row0 = (rowblock * RP_WAVES + wave) * RP_RPW;
   const int64_t c0 = g * cg;
   const int64_t c1 = min(m, c0 + cg);
   if (row0 >= n) return;
@@ -473,6 +487,31 @@ rowpass_prep_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t l
       if (lane == 0) part[(ngroups + g) * n + row0 + r] = t;
     }
   }
+}
+
+template <bool WANT_B, int QM>
+__global__ void __launch_bounds__(64 * RP_WAVES)
+rowpass_prep_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, const float* __restrict__ v,
+                    int64_t cg, double* __restrict__ part, uint8_t* __restrict__ q, uint8_t* __restrict__ sc,
+                    int64_t ldq) {
+  rowpass_prep_body<WANT_B, QM>(S, n, m, lds, v, cg, part, q, sc, ldq, blockIdx.x, blockIdx.y, gridDim.y);
+}
+
+__device__ __forceinline__ int64_t prep_rowblocks(int64_t n) { return (n + RP_WAVES * RP_RPW - 1) / (RP_WAVES * RP_RPW); }
+
+// many problems in one launch
+__global__ void __launch_bounds__(64 * RP_WAVES) rowpass_prep_jobs_kernel(JobList<PrepJob> l) {
+  const int k = job_of(l, blockIdx.x);
+  const PrepJob& j = l.job[k];
+  const int64_t w = blockIdx.x - l.blk0[k], rb = prep_rowblocks(j.p.n);
+  rowpass_prep_body<true, 3>(j.S, j.p.n, j.p.m, j.p.lds, j.v, j.p.chunk, j.part, j.q, j.sc, j.ldq, w % rb, w / rb,
+                             j.p.nchunk);
+}
+
+__global__ void __launch_bounds__(256) rowpass_reduce_jobs_kernel(JobList<PrepJob> l) {
+  const int k = job_of(l, blockIdx.x);
+  const PrepJob& j = l.job[k];
+  reduce_body(j.part, j.p.n, j.p.nchunk, 1, 1, j.b, j.d, nullptr, nullptr, 0.0, nullptr, blockIdx.x - l.blk0[k]);
 }
 
 // ---------------------------------------------------------------------------- fused refinement pass
@@ -1035,6 +1074,33 @@ hipError_t colpass_launch(const ColPassPlan& p, const float* S, int64_t n, int64
     default: hipLaunchKernelGGL(colpass_finalize_kernel<2>, g2, dim3(256), 0, st, part, p.nsplit, m, v, lambda, out, skip); break;
   }
   return hipGetLastError();
+}
+
+hipError_t rowpass_prep_jobs(const PrepJob* jobs, int count, hipStream_t st) {
+  for (int k = 0; k < count; ++k)
+    if ((jobs[k].ldq & 127) != 0 || jobs[k].ldq < jobs[k].p.m) return hipErrorInvalidValue;
+  hipError_t e = launch_jobs(
+      jobs, count,
+      [](const PrepJob& j) { return (j.p.n + RP_WAVES * RP_RPW - 1) / (RP_WAVES * RP_RPW) * j.p.nchunk; },
+      [&](const JobList<PrepJob>& l, unsigned blocks) {
+        hipLaunchKernelGGL(rowpass_prep_jobs_kernel, dim3(blocks), dim3(64 * RP_WAVES), 0, st, l);
+      });
+  if (e != hipSuccess) return e;
+  return launch_jobs(jobs, count, [](const PrepJob& j) { return (j.p.n + 15) / 16; },
+                     [&](const JobList<PrepJob>& l, unsigned blocks) {
+                       hipLaunchKernelGGL(rowpass_reduce_jobs_kernel, dim3(blocks), dim3(256), 0, st, l);
+                     });
+}
+
+int64_t colpass_blocks(int64_t m) { return (m + CP_COLS - 1) / CP_COLS; }
+
+hipError_t colpass_jobs(const ColJob* jobs, int count, int mode, hipStream_t st) {
+  if (mode != 0 && mode != 1) return hipErrorInvalidValue;
+  return launch_jobs(jobs, count, [](const ColJob& j) { return colpass_blocks(j.m); },
+                     [&](const JobList<ColJob>& l, unsigned blocks) {
+                       if (mode == 0) hipLaunchKernelGGL(colpass_jobs_kernel<0>, dim3(blocks), dim3(CP_THREADS), 0, st, l);
+                       else hipLaunchKernelGGL(colpass_jobs_kernel<1>, dim3(blocks), dim3(CP_THREADS), 0, st, l);
+                     });
 }
 
 RefinePassPlan refine_pass_plan(int64_t n, int64_t m, int64_t lds, const float* S, bool split_ok) {

@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <vector>
 
 namespace dfi {
 namespace {
@@ -1261,16 +1262,16 @@ gram_kernel_split(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ 
 // tiles) both take 20 us, at n = 2048 (36) split takes 47, unsplit 34.
 constexpr int RED_ROWS = 16;
 template <bool SPLIT>
-__global__ void __launch_bounds__(SPLIT ? 256 : 64 * RED_ROWS)
-gram_reduce_kernel(const float* __restrict__ part, int64_t n, int64_t ntri, int64_t nslice,
-                   const double* __restrict__ d, double lambda, double* __restrict__ W, int mirror,
-                   const float* __restrict__ S, int64_t lds, int64_t ktail, int64_t m) {
+__device__ __forceinline__ void gram_reduce_body(const float* __restrict__ part, int64_t n, int64_t ntri, int64_t nslice,
+                                                 const double* __restrict__ d, double lambda, double* __restrict__ W,
+                                                 int mirror, const float* __restrict__ S, int64_t lds, int64_t ktail,
+                                                 int64_t m, int64_t w) {
   constexpr int ROWS = SPLIT ? 1 : RED_ROWS;
   __shared__ double sums[SPLIT ? 4 : ROWS][T];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t tile = blockIdx.x / (T / ROWS);
-  const int r = (int)(blockIdx.x - tile * (T / ROWS)) * ROWS + (SPLIT ? 0 : wave);
+  const int64_t tile = w / (T / ROWS);
+  const int r = (int)(w - tile * (T / ROWS)) * ROWS + (SPLIT ? 0 : wave);
   int64_t ti, tj;
   tri_index(tile, ti, tj);
   ti = uni64(ti);
@@ -1321,6 +1322,22 @@ gram_reduce_kernel(const float* __restrict__ part, int64_t n, int64_t ntri, int6
     W[i * n + j] = v;
     if (mirror && i != j) W[j * n + i] = v;
   }
+}
+
+template <bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 256 : 64 * RED_ROWS)
+gram_reduce_kernel(const float* __restrict__ part, int64_t n, int64_t ntri, int64_t nslice,
+                   const double* __restrict__ d, double lambda, double* __restrict__ W, int mirror,
+                   const float* __restrict__ S, int64_t lds, int64_t ktail, int64_t m) {
+  gram_reduce_body<SPLIT>(part, n, ntri, nslice, d, lambda, W, mirror, S, lds, ktail, m, blockIdx.x);
+}
+
+// many problems' reductions in one launch (lower triangles, no columns left out)
+template <bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 256 : 64 * RED_ROWS) gram_reduce_jobs_kernel(JobList<GramReduceJob> l) {
+  const int k = job_of(l, blockIdx.x);
+  const GramReduceJob& j = l.job[k];
+  gram_reduce_body<SPLIT>(j.part, j.n, j.ntri, j.nslice, j.d, j.lambda, j.W, 0, nullptr, 0, 0, 0, blockIdx.x - l.blk0[k]);
 }
 
 // FP32 products by gram_kernel_v2: eight rows lie within one buffer of 2^32 bytes.
@@ -1485,6 +1502,21 @@ hipError_t gram_reduce(const GramPlan& p, const float* S, const float* part, con
     hipLaunchKernelGGL(gram_reduce_kernel<false>, dim3((unsigned)(p.ntri * (T / RED_ROWS))), dim3(64 * RED_ROWS), 0, st,
                        part, p.n, p.ntri, p.nslice, d, lambda, W, mirror, S, p.lds, ktail, p.m);
   return hipGetLastError();
+}
+
+hipError_t gram_reduce_jobs(const GramReduceJob* jobs, int count, hipStream_t st) {
+  using L = JobList<GramReduceJob>;
+  std::vector<GramReduceJob> small, large;   // the form of gram_reduce
+  for (int k = 0; k < count; ++k) (jobs[k].ntri <= 16 ? small : large).push_back(jobs[k]);
+  const hipError_t e = launch_jobs(small.data(), (int)small.size(), [](const GramReduceJob& j) { return j.ntri * T; },
+                                   [&](const L& l, unsigned b) {
+                                     hipLaunchKernelGGL(gram_reduce_jobs_kernel<true>, dim3(b), dim3(256), 0, st, l);
+                                   });
+  if (e != hipSuccess) return e;
+  return launch_jobs(large.data(), (int)large.size(), [](const GramReduceJob& j) { return j.ntri * (T / RED_ROWS); },
+                     [&](const L& l, unsigned b) {
+                       hipLaunchKernelGGL(gram_reduce_jobs_kernel<false>, dim3(b), dim3(64 * RED_ROWS), 0, st, l);
+                     });
 }
 
 }  // namespace dfi

@@ -150,10 +150,9 @@ __global__ void complex_apply_kernel(const float* __restrict__ v, const double* 
 // its rows (over its columns j <= i) and of its columns (over its rows i > j, the transposed
 // half); seg_reduce_kernel then adds, for row i of tile row I, the row sums of tiles (I, 0 .. I)
 // and the column sums of tiles (I .. T - 1, I), in that order.
-__global__ void __launch_bounds__(256) tile_sums_kernel(const double* __restrict__ W, int64_t n, int64_t l,
-                                                        double* __restrict__ part) {
+__device__ __forceinline__ void tile_sums_body(const double* __restrict__ W, int64_t n, int64_t l,
+                                               double* __restrict__ part, int64_t t) {
   __shared__ double tile[64][65];
-  const int64_t t = blockIdx.x;
   int64_t ti = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
   while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
   while (ti * (ti + 1) / 2 > t) --ti;
@@ -185,9 +184,9 @@ __global__ void __launch_bounds__(256) tile_sums_kernel(const double* __restrict
   }
 }
 
-__global__ void __launch_bounds__(256) seg_reduce_kernel(const double* __restrict__ part, int64_t n, int64_t T,
-                                                         int nseg, double* __restrict__ r) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void seg_reduce_body(const double* __restrict__ part, int64_t n, int64_t T, int nseg,
+                                                double* __restrict__ r, int64_t blk) {
+  const int64_t i = blk * 256 + threadIdx.x;
   if (i >= n) return;
   const int64_t I = i >> 6;
   const int a = (int)(i & 63);
@@ -213,8 +212,8 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
   return t;
 }
 
-__global__ void __launch_bounds__(256) seg_total_kernel(const double* __restrict__ W, const double* __restrict__ r,
-                                                        int64_t n, int64_t l, int nseg, double* __restrict__ c) {
+__device__ __forceinline__ void seg_total_body(const double* __restrict__ W, const double* __restrict__ r, int64_t n,
+                                               int64_t l, int nseg, double* __restrict__ c) {
   __shared__ double red[256];
   for (int s = 0; s < nseg; ++s)
     for (int u = 0; u < nseg; ++u) {
@@ -236,24 +235,69 @@ __global__ void __launch_bounds__(256) seg_total_kernel(const double* __restrict
 // non-centered S would otherwise get a factor that is exact nowhere near W along it.
 constexpr double CENTER_GUARD = 0.01;
 
-__global__ void __launch_bounds__(256) project_update_kernel(double* __restrict__ W, int64_t n, int64_t l, int nseg,
-                                                             const double* __restrict__ r, const double* __restrict__ c,
-                                                             double lambda, int full, int64_t nb,
-                                                             int* __restrict__ applied) {
+__device__ __forceinline__ void project_update_body(double* __restrict__ W, int64_t n, int64_t l, int nseg,
+                                                    const double* __restrict__ r, const double* __restrict__ c,
+                                                    double lambda, int full, int64_t nb, int* __restrict__ applied,
+                                                    int64_t blk) {
   const double dbar = c[nseg * nseg] / (double)n - lambda;
   bool ok = true;
   for (int s = 0; s < nseg; ++s)
     if (!(c[s * nseg + s] / (double)l - lambda <= CENTER_GUARD * dbar)) ok = false;
-  if (applied && blockIdx.x == 0 && threadIdx.x == 0) *applied = ok ? 1 : 0;
+  if (applied && blk == 0 && threadIdx.x == 0) *applied = ok ? 1 : 0;
   if (!ok) return;
-  const int64_t i = (int64_t)blockIdx.x / nb;
-  const int64_t j = ((int64_t)blockIdx.x - i * nb) * 256 + threadIdx.x;
+  const int64_t i = blk / nb;
+  const int64_t j = (blk - i * nb) * 256 + threadIdx.x;
   if (j >= n || (!full && j > i)) return;
   const int64_t si = i < l ? 0 : 1, sj = j < l ? 0 : 1;   // nseg <= 2
   const double inv = 1.0 / (double)l;
   double w = W[i * n + j] - (r[sj * n + i] + r[si * n + j]) * inv + c[si * nseg + sj] * (inv * inv);
   if (si == sj) w += lambda * inv;
   W[i * n + j] = w;
+}
+
+__global__ void __launch_bounds__(256) tile_sums_kernel(const double* __restrict__ W, int64_t n, int64_t l,
+                                                        double* __restrict__ part) {
+  tile_sums_body(W, n, l, part, blockIdx.x);
+}
+__global__ void __launch_bounds__(256) seg_reduce_kernel(const double* __restrict__ part, int64_t n, int64_t T,
+                                                         int nseg, double* __restrict__ r) {
+  seg_reduce_body(part, n, T, nseg, r, blockIdx.x);
+}
+__global__ void __launch_bounds__(256) seg_total_kernel(const double* __restrict__ W, const double* __restrict__ r,
+                                                        int64_t n, int64_t l, int nseg, double* __restrict__ c) {
+  seg_total_body(W, r, n, l, nseg, c);
+}
+__global__ void __launch_bounds__(256) project_update_kernel(double* __restrict__ W, int64_t n, int64_t l, int nseg,
+                                                             const double* __restrict__ r, const double* __restrict__ c,
+                                                             double lambda, int full, int64_t nb,
+                                                             int* __restrict__ applied) {
+  project_update_body(W, n, l, nseg, r, c, lambda, full, nb, applied, blockIdx.x);
+}
+
+// the same for many problems in one launch (one segment, the lower triangle)
+__device__ __forceinline__ int64_t project_tiles(int64_t n) {
+  const int64_t T = (n + 63) / 64;
+  return T * (T + 1) / 2;
+}
+__global__ void __launch_bounds__(256) tile_sums_jobs_kernel(JobList<ProjectJob> l) {
+  const int k = job_of(l, blockIdx.x);
+  const ProjectJob& j = l.job[k];
+  tile_sums_body(j.W, j.n, j.n, j.work, blockIdx.x - l.blk0[k]);
+}
+__global__ void __launch_bounds__(256) seg_reduce_jobs_kernel(JobList<ProjectJob> l) {
+  const int k = job_of(l, blockIdx.x);
+  const ProjectJob& j = l.job[k];
+  seg_reduce_body(j.work, j.n, (j.n + 63) / 64, 1, j.r, blockIdx.x - l.blk0[k]);
+}
+__global__ void __launch_bounds__(256) seg_total_jobs_kernel(JobList<ProjectJob> l) {
+  const ProjectJob& j = l.job[blockIdx.x];
+  seg_total_body(j.W, j.r, j.n, j.n, 1, j.work + project_tiles(j.n) * 4 * 64);
+}
+__global__ void __launch_bounds__(256) project_update_jobs_kernel(JobList<ProjectJob> l) {
+  const int k = job_of(l, blockIdx.x);
+  const ProjectJob& j = l.job[k];
+  project_update_body(j.W, j.n, j.n, 1, j.r, j.work + project_tiles(j.n) * 4 * 64, j.lambda, 0, (j.n + 255) / 256,
+                      j.applied, blockIdx.x - l.blk0[k]);
 }
 
 unsigned blocks(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
@@ -289,6 +333,27 @@ hipError_t gram_project(double* W, int64_t n, int nseg, double lambda, int full,
   hipLaunchKernelGGL(project_update_kernel, dim3((unsigned)(nb * n)), dim3(256), 0, st, W, n, l, nseg, r, c, lambda,
                      full, nb, applied);
   return hipGetLastError();
+}
+
+hipError_t gram_project_jobs(const ProjectJob* jobs, int count, hipStream_t st) {
+  using L = JobList<ProjectJob>;
+  auto tiles = [](const ProjectJob& j) { const int64_t T = (j.n + 63) / 64; return T * (T + 1) / 2; };
+  hipError_t e = launch_jobs(jobs, count, tiles, [&](const L& l, unsigned b) {
+    hipLaunchKernelGGL(tile_sums_jobs_kernel, dim3(b), dim3(256), 0, st, l);
+  });
+  if (e == hipSuccess)
+    e = launch_jobs(jobs, count, [](const ProjectJob& j) { return (j.n + 255) / 256; }, [&](const L& l, unsigned b) {
+      hipLaunchKernelGGL(seg_reduce_jobs_kernel, dim3(b), dim3(256), 0, st, l);
+    });
+  if (e == hipSuccess)
+    e = launch_jobs(jobs, count, [](const ProjectJob&) { return (int64_t)1; }, [&](const L& l, unsigned b) {
+      hipLaunchKernelGGL(seg_total_jobs_kernel, dim3(b), dim3(256), 0, st, l);
+    });
+  if (e == hipSuccess)
+    e = launch_jobs(jobs, count, [](const ProjectJob& j) { return (j.n + 255) / 256 * j.n; }, [&](const L& l, unsigned b) {
+      hipLaunchKernelGGL(project_update_jobs_kernel, dim3(b), dim3(256), 0, st, l);
+    });
+  return e;
 }
 
 hipError_t fill_value(double* y, int64_t n, double value, hipStream_t st) {
