@@ -282,18 +282,19 @@ __device__ __forceinline__ void factor16(f64x4 t, f64x4& l, f64x4& d, double (&p
   }
 }
 
-// -A_IJ of this wave's strip (rows 64 I + 16 w ..), transposed sums' layout: lane l, register q of
+// -W_IJ (with add on the diagonal) of this wave's strip (rows 64 I + 16 w ..), transposed sums' layout: lane l, register q of
 // block p holds row l % 16, column 16 p + l / 16 + 4 q. Rows past n are zero; on the diagonal tile the
 // strict upper triangle is zero and rows past n are the identity's.
-__device__ __forceinline__ void load_strip(f64x4 (&acc)[4], const double* A, int64_t n, int I, int J, int w, int lane) {
+__device__ __forceinline__ void load_strip(f64x4 (&acc)[4], const double* W, double add, int64_t n, int I, int J, int w,
+                                           int lane) {
   const int64_t row = (int64_t)I * NB + 16 * w + (lane & 15);
-  const double* ar = A + (row < n ? row : n - 1) * n;
+  const double* ar = W + (row < n ? row : n - 1) * n;
 #pragma unroll
   for (int p = 0; p < 4; ++p)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int64_t col = (int64_t)J * NB + 16 * p + (lane >> 4) + 4 * q;
-      const double v = ar[col < n ? col : n - 1];
+      const double v = ar[col < n ? col : n - 1] + (row == col ? add : 0.0);
       acc[p][q] = (row >= n) ? (row == col ? -1.0 : 0.0) : (col > row ? 0.0 : -v);
     }
 }
@@ -418,7 +419,7 @@ __device__ __forceinline__ void await(int* word) {   // every wave of the task r
 // products with those from their other blocks. The chain from wave p to wave p + 1 is thus one LDS
 // round trip and eight products; everything else is kept behind it, the stores and flags above all. A panel is published as soon as it is finished, so
 // the tasks that wait for it solve their panels 0 .. 2 while the later ones are still being factored.
-__device__ void diag_task(double* A, int64_t n, int J, int nb, double* pack, uint32_t* ready, int64_t* info, int32_t* flag,
+__device__ void diag_task(double* A, const double* W, double add, int64_t n, int J, int nb, double* pack, uint32_t* ready, int64_t* info, int32_t* flag,
                           uint32_t* ticket, CholLds& sm, int w, int lane) {
   const double* rowJ = pack + (int64_t)J * (J + 1) / 2 * TD;
   uint32_t* fJ = ready + (int64_t)J * nb;
@@ -426,7 +427,7 @@ __device__ void diag_task(double* A, int64_t n, int J, int nb, double* pack, uin
   if (threadIdx.x < 4) sm.have_x[threadIdx.x] = sm.have_bad[threadIdx.x] = 0;
   if (threadIdx.x < 16) sm.have_l[threadIdx.x >> 2][threadIdx.x & 3] = 0;
   f64x4 t1[4], t2[4];
-  load_strip(t2, A, n, J, J, w, lane);
+  load_strip(t2, W, add, n, J, J, w, lane);
   __builtin_amdgcn_s_setprio(3);   // ahead of the tile task that shares the compute unit's matrix cores
   __syncthreads();
   if (J > 0) {
@@ -434,7 +435,7 @@ __device__ void diag_task(double* A, int64_t n, int J, int nb, double* pack, uin
     const double* rowP = pack + (int64_t)(J - 1) * J / 2 * TD;
     const uint32_t* fP = ready + (int64_t)(J - 1) * nb;
     double* tileX = const_cast<double*>(rowJ) + (int64_t)(J - 1) * TD;
-    load_strip(t1, A, n, J, J - 1, w, lane);
+    load_strip(t1, W, 0.0, n, J, J - 1, w, lane);
     for (int k = 0; k < J - 1;) {
       const int cnt = wait_tiles(fJ, fP, k, J - 1, ticket, lane);
       if (cnt == 0) {
@@ -581,14 +582,14 @@ __device__ void diag_task(double* A, int64_t n, int J, int nb, double* pack, uin
 }
 
 // The off-diagonal task of tile (I, J), I >= J + 2.
-__device__ void tile_task(double* A, int64_t n, int I, int J, int nb, double* pack, uint32_t* ready, int64_t* info,
+__device__ void tile_task(double* A, const double* W, int64_t n, int I, int J, int nb, double* pack, uint32_t* ready, int64_t* info,
                           int32_t* flag, uint32_t* ticket, int w, int lane) {
   const double* rowI = pack + (int64_t)I * (I + 1) / 2 * TD;
   const double* rowJ = pack + (int64_t)J * (J + 1) / 2 * TD;
   uint32_t* fI = ready + (int64_t)I * nb;
   const uint32_t* fJ = ready + (int64_t)J * nb;
   f64x4 t[4];
-  load_strip(t, A, n, I, J, w, lane);
+  load_strip(t, W, 0.0, n, I, J, w, lane);
   for (int k = 0; k < J;) {
     const int cnt = wait_tiles(fI, fJ, k, J, ticket, lane);
     if (cnt == 0) return gave_up(info, flag, lane);
@@ -611,13 +612,14 @@ __device__ void tile_task(double* A, int64_t n, int I, int J, int nb, double* pa
 // diagonal c (with tile (c, c - 1)) followed by the tiles (c + 1 .. nb - 1, c - 1).
 __host__ __device__ inline int64_t chol_tasks(int64_t nb) { return 1 + nb * (nb - 1) / 2; }
 
-// nbatch matrices (matrix b at A + b sA, pack + b sP, ready + b sR): ticket t is task t / nbatch of
+// nbatch matrices (matrix b at A + b sA, pack + b sP, ready + b sR; with src.W all read src.W, its diagonal shifted by
+// each matrix's own term, and A is only written): ticket t is task t / nbatch of
 // matrix t % nbatch. With jobs / tasks: ticket t is entry t of the task table. 256 threads; two
 // workgroups per compute unit (50 KB of LDS, at most 256 registers).
 __global__ void __launch_bounds__(256, 2)
 chol_kernel(double* A, int64_t n, int64_t sA, double* pack, int64_t sP, uint32_t* ready, int64_t sR, int64_t* info,
             int32_t* flag, uint32_t* ticket, int nbatch, const FactorJob* __restrict__ jobs,
-            const FactorTask* __restrict__ tasks) {
+            const FactorTask* __restrict__ tasks, CholSource src) {
   __shared__ CholLds sm;
   __shared__ uint32_t my;
   if (threadIdx.x == 0) my = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -626,6 +628,8 @@ chol_kernel(double* A, int64_t n, int64_t sA, double* pack, int64_t sP, uint32_t
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int c, i, nb;
+  const double* W = src.W;
+  double add = 0.0;
   if (tasks) {
     const FactorTask t = tasks[tk];
     const FactorJob& j = jobs[t.job];
@@ -642,6 +646,7 @@ chol_kernel(double* A, int64_t n, int64_t sA, double* pack, int64_t sP, uint32_t
     const int b = (int)(tk % (uint32_t)nbatch);
     const int s = (int)(tk / (uint32_t)nbatch);
     A += b * sA;
+    if (W) add = src.lam[b] + (src.scale != 0.0 ? src.scale * src.dmax[0] : 0.0);
     pack += b * sP;
     ready += b * sR;
     info += b;
@@ -660,8 +665,9 @@ chol_kernel(double* A, int64_t n, int64_t sA, double* pack, int64_t sP, uint32_t
   }
   c = __builtin_amdgcn_readfirstlane(c);
   i = __builtin_amdgcn_readfirstlane(i);
-  if (i == 0) diag_task(A, n, c, nb, pack, ready, info, flag, ticket, sm, w, lane);
-  else tile_task(A, n, c + i, c - 1, nb, pack, ready, info, flag, ticket, w, lane);
+  if (!W) W = A;
+  if (i == 0) diag_task(A, W, add, n, c, nb, pack, ready, info, flag, ticket, sm, w, lane);
+  else tile_task(A, W, n, c + i, c - 1, nb, pack, ready, info, flag, ticket, w, lane);
 }
 
 // Statuses, flags and the ticket start at zero, the diagonal tiles' last panels unset. Grid (x, y): y = matrix.
@@ -712,7 +718,8 @@ uint32_t* chol_ready_at(double* pack, int64_t n) {
 }
 
 hipError_t chol_launch_batched(double* A, int64_t n, int64_t nbatch, int64_t sA, int64_t* info_dev, int32_t* flag_dev,
-                               double* pack, uint32_t* ticket, hipStream_t st) {
+                               double* pack, uint32_t* ticket, hipStream_t st, const CholSource& src) {
+  if (src.W && nbatch > CHOL_LAMS) return hipErrorInvalidValue;
   const int64_t nb = (n + NB - 1) / NB;
   const int64_t wgs = chol_tasks(nb) * nbatch;
   if (n < 1 || nbatch < 1 || nbatch > 65535 || wgs > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -722,7 +729,7 @@ hipError_t chol_launch_batched(double* A, int64_t n, int64_t nbatch, int64_t sA,
   hipLaunchKernelGGL(chol_clear_kernel, dim3((unsigned)std::min<int64_t>(32, nb), (unsigned)nbatch), dim3(256), 0, st,
                      n, pack, sP, ready, 2 * sP, info_dev, flag_dev, ticket, nj);
   hipLaunchKernelGGL(chol_kernel, dim3((unsigned)wgs), dim3(256), 0, st, A, n, sA, pack, sP, ready, 2 * sP, info_dev,
-                     flag_dev, ticket, (int)nbatch, nj, (const FactorTask*)nullptr);
+                     flag_dev, ticket, (int)nbatch, nj, (const FactorTask*)nullptr, src);
   return hipGetLastError();
 }
 
@@ -735,7 +742,7 @@ hipError_t chol_launch_grouped(const FactorJob* jobs_dev, int64_t njobs, int64_t
                      (int32_t*)nullptr, ticket, jobs_dev);
   hipLaunchKernelGGL(chol_kernel, dim3((unsigned)ntasks), dim3(256), 0, st, (double*)nullptr, (int64_t)0, (int64_t)0,
                      (double*)nullptr, (int64_t)0, (uint32_t*)nullptr, (int64_t)0, (int64_t*)nullptr,
-                     (int32_t*)nullptr, ticket, 1, jobs_dev, tasks_dev);
+                     (int32_t*)nullptr, ticket, 1, jobs_dev, tasks_dev, CholSource{});
   return hipGetLastError();
 }
 

@@ -322,13 +322,26 @@ size_t chol_scratch_bytes(int64_t n, int64_t nbatch) {
 // nbatch matrices factored (L below the diagonal, L^T above it), in one launch when pack (chol_scratch_bytes) is there, else in place in a
 // chain of launches.
 hipError_t factor_launch(double* A, int64_t n, int64_t nbatch, int64_t sA, int64_t* info, int32_t* flag, double* dkk,
-                         double* pack, hipStream_t st) {
+                         double* pack, hipStream_t st, const double* W = nullptr, const double* lams = nullptr,
+                         double scale = 0.0, const double* dmax = nullptr) {
+  dfi::CholSource src;
+  if (W && pack && nbatch <= dfi::CHOL_LAMS) {
+    src.W = W;
+    src.dmax = dmax;
+    src.scale = scale;
+    for (int64_t b = 0; lams && b < nbatch; ++b) src.lam[b] = lams[b];
+  } else if (W) {
+    for (int64_t b = 0; b < nbatch; ++b) {
+      const hipError_t e = dfi::shift_add_copy(W, A + b * sA, n, scale, dmax, lams ? lams[b] : 0.0, st);
+      if (e != hipSuccess) return e;
+    }
+  }
   if (!pack) {
     const hipError_t e = dfi::potrf_launch_batched(A, n, nbatch, sA, info, flag, dkk, st);
     return e != hipSuccess ? e : dfi::tri_mirror_batched(A, n, nbatch, sA, st);
   }
   auto* ticket = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(pack) + (size_t)nbatch * dfi::chol_pack_bytes(n));
-  return dfi::chol_launch_batched(A, n, nbatch, sA, info, flag, pack, ticket, st);
+  return dfi::chol_launch_batched(A, n, nbatch, sA, info, flag, pack, ticket, st, src);
 }
 
 // Everything one factorisation + solve needs, carved from the workspace.
@@ -433,24 +446,32 @@ dfisher_status factor_with_policy(dfisher_ctx* ctx, const double* W, double* L, 
   if (policy == DFISHER_SHIFT_ALWAYS) scale = 2.0 * base_scale;
   int attempts = 0;
   int64_t info = 0;
-  if (policy != DFISHER_SHIFT_NONE) HIP_TRY(dfi::diag_max(W, n, ctx->d_scalar, st));
+  bool have_max = false;   // h_scalar[0] = max_i W_ii: only a shift needs it
+  auto diag_max = [&]() -> dfisher_status {
+    HIP_TRY(dfi::diag_max(W, n, ctx->d_scalar, st));
+    HIP_TRY(hipMemcpyAsync(ctx->h_scalar, ctx->d_scalar, sizeof(double), hipMemcpyDeviceToHost, st));
+    have_max = true;
+    return DFISHER_OK;
+  };
   for (;;) {
-    HIP_TRY(dfi::shift_copy(W, L, n, scale, ctx->d_scalar, st));
-    HIP_TRY(factor_launch(L, n, 1, n * n, ctx->d_info, ctx->d_flag, dkk, pack, st));
+    if (scale != 0.0 && !have_max) DF_TRY(diag_max());
+    HIP_TRY(factor_launch(L, n, 1, n * n, ctx->d_info, ctx->d_flag, dkk, pack, st, W, nullptr, scale, ctx->d_scalar));
     if (attempts == 0 && spec) DF_TRY(spec());
     HIP_TRY(hipMemcpyAsync(ctx->h_status, ctx->d_info, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    if (policy != DFISHER_SHIFT_NONE)
-      HIP_TRY(hipMemcpyAsync(ctx->h_scalar, ctx->d_scalar, sizeof(double), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     ++attempts;
     info = ctx->h_status[0];
     if (info < 0) return fail(DFISHER_E_DEVICE, "the Cholesky gave up waiting for one of its own tiles");
     if (info == 0 || policy == DFISHER_SHIFT_NONE || attempts >= MAX_SHIFT_ATTEMPTS) break;
+    if (!have_max) {
+      DF_TRY(diag_max());
+      HIP_TRY(hipStreamSynchronize(st));
+    }
     if (!std::isfinite(ctx->h_scalar[0])) break;  // NaN/Inf in W: shifting cannot help
     scale = (scale == 0.0) ? base_scale : 8.0 * scale;
   }
   if (spec_ok) *spec_ok = attempts == 1 && info == 0;
-  *shift_out = (info == 0 && policy != DFISHER_SHIFT_NONE) ? scale * ctx->h_scalar[0] : 0.0;
+  *shift_out = (info == 0 && have_max) ? scale * ctx->h_scalar[0] : 0.0;
   *info_out = info;
   *attempts_out = attempts;
   if (info != 0)
@@ -2592,9 +2613,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   const double unit = gram_unit(o.gram_prec, m);
   const double scale0 = (o.shift_policy == DFISHER_SHIFT_ALWAYS) ? 2.0 * std::sqrt((double)n) * unit : 0.0;
   if (scale0 != 0.0) HIP_TRY(dfi::diag_max(B.W, n, ctx->d_scalar, st));
-  for (int32_t l = 0; l < nlam; ++l)
-    HIP_TRY(dfi::shift_add_copy(B.W, Lall + (int64_t)l * n * n, n, scale0, ctx->d_scalar, lambdas[l], st));
-  HIP_TRY(factor_launch(Lall, n, nlam, n * n, dinfo, dflag, dkk, packs, st));
+  HIP_TRY(factor_launch(Lall, n, nlam, n * n, dinfo, dflag, dkk, packs, st, B.W, lambdas, scale0, ctx->d_scalar));
   if (async) {   // nothing read back: the sweep count is fixed a priori, the statuses go to infos on the device
     const int sweeps = o.sweeps == DFISHER_SWEEPS_AUTO ? auto_sweeps(o.gram_prec, n, m, scale0, is_centered(o))
                                                        : o.sweeps;

@@ -346,8 +346,17 @@ hipError_t potrf_launch_grouped(const FactorJob* jobs_dev, int64_t njobs, int64_
 constexpr size_t CHOL_TICKET_BYTES = 256;
 size_t chol_pack_bytes(int64_t n);
 uint32_t* chol_ready_at(double* pack, int64_t n);
+// src.W set: matrix b is W + (lam[b] + scale dmax[0]) I (dmax on the device, unused at scale 0), nbatch <= CHOL_LAMS, and A is
+// only written (a copy of W per matrix and attempt took 5 us for n = 1024 and 52 us for n = 4096).
+constexpr int CHOL_LAMS = 32;
+struct CholSource {
+  const double* W = nullptr;
+  const double* dmax = nullptr;
+  double scale = 0.0;
+  double lam[CHOL_LAMS] = {};
+};
 hipError_t chol_launch_batched(double* A, int64_t n, int64_t nbatch, int64_t sA, int64_t* info_dev, int32_t* flag_dev,
-                               double* pack, uint32_t* ticket, hipStream_t st);
+                               double* pack, uint32_t* ticket, hipStream_t st, const CholSource& src = CholSource{});
 // Grouped: tasks_dev lists every job's tasks (chol_task of s = 0 .. chol_task_count(n) - 1 of each job), any
 // interleaving that keeps each job's order.
 struct FactorTask {
@@ -463,8 +472,6 @@ hipError_t complex_apply(const float* v, const double* T, int64_t m, double lamb
                          hipStream_t st);
 
 // ----------------------------------------------------------------------------- small helpers
-// dst = src + scale * dmax[0] * I (n x n, row-major; dmax a device scalar, unread if scale == 0).
-hipError_t shift_copy(const double* src, double* dst, int64_t n, double scale, const double* dmax, hipStream_t st);
 // dst = src + lam * I
 hipError_t add_diag_copy(const double* src, double* dst, int64_t n, double lam, hipStream_t st);
 // dst = src + (lam + scale * dmax[0]) * I (dmax unread if scale == 0)

@@ -543,13 +543,6 @@ hipError_t zero_upper(double* A, int64_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t shift_copy(const double* src, double* dst, int64_t n, double scale, const double* dmax, hipStream_t st) {
-  const int64_t tot = n * n;
-  hipLaunchKernelGGL(shift_copy_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, src, dst, n, scale, dmax,
-                     0.0);
-  return hipGetLastError();
-}
-
 hipError_t add_diag_copy(const double* src, double* dst, int64_t n, double lam, hipStream_t st) {
   const int64_t tot = n * n;
   hipLaunchKernelGGL(shift_copy_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, src, dst, n, 0.0,

@@ -76,3 +76,20 @@ def test_two_groups_without_the_memory():
         check(X, reference(S, lams, V))
     del g
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 65, 200])
+@pytest.mark.parametrize("nlam", [1, 32, 33])
+@pytest.mark.parametrize("policy", [dfl.DFISHER_SHIFT_NONE, dfl.DFISHER_SHIFT_ALWAYS])
+def test_many_dampings(n, nlam, policy):
+    """The factorisations read one shared Gram, each with its own damping (and shift), up to 32 at a time."""
+    ctx = dfl.dfisher_ctx_create(0)
+    S, V = problem(n, 700, 0, 1)
+    lams = [0.05 * 1.05 ** k for k in range(nlam)]
+    X, infos = dfl.dfisher_solve_batched(ctx, S, lams, V, **{**KW, "shift_policy": policy})
+    assert all(i["potrf_info"] == 0 and (i["shift"] > 0) == (policy == dfl.DFISHER_SHIFT_ALWAYS) for i in infos)
+    check(X, reference(S, lams, V))
+    x, info = dfl.dfisher_solve(ctx, S, V[0], lams[-1], **{**KW, "shift_policy": policy})
+    assert (info["shift"] > 0) == (policy == dfl.DFISHER_SHIFT_ALWAYS)
+    check(x, X[-1, 0])
+    ctx.close()
