@@ -427,10 +427,12 @@ SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const
 }
 
 // y = L^-T L^-1 b (scratch B.z).
+// (ready: the kernel before it had tri_prep(B, y))
 hipError_t apply_factor(const double* L, const double* Dinv, int64_t n, const double* b, const SolveBufs& B, double* y,
-                        hipStream_t st) {
-  return dfi::tri_solve_batched(L, n * n, Dinv, n, 1, 1, b, B.z, y, reinterpret_cast<uint32_t*>(B.tw), st);
+                        hipStream_t st, bool ready = false) {
+  return dfi::tri_solve_batched(L, n * n, Dinv, n, 1, 1, b, B.z, y, reinterpret_cast<uint32_t*>(B.tw), st, ready);
 }
+dfi::TriPrep tri_prep(const SolveBufs& B, double* y) { return dfi::TriPrep{B.z, y, reinterpret_cast<uint32_t*>(B.tw)}; }
 
 // Cholesky of W (+ tau I) into L following the shift policy. Synchronises once per attempt.
 // `spec`, if given, is enqueued right after the first attempt's factorisation and before the wait
@@ -515,19 +517,21 @@ dfisher_status gram_stage(const float* S, const float* v, const dfi::GramPlan& g
 // out = rhs - lambda u - S (S^T u) for an n-vector u (FP64 accumulation): one read of S through the
 // fused pass when `fp` allows it, else a column pass (t = S^T u into B.t) and a row pass. With
 // rhs = b and u = y it is the residual of y; with rhs = 0 and u = p it is -(W p).
-// tout / csout (the whole-line pass only, may be null): S^T u and S^T 1 from the same read of S.
+// tout / csout (the whole-line pass only, may be null): S^T u and S^T 1 from the same read of S. Also readies the
+// triangular solve for B.zc that follows.
 dfisher_status w_pass(const float* S, int64_t n, int64_t m, int64_t lds, double lambda, const double* u,
                       const double* rhs, double* out, const SolveBufs& B, const dfi::RowPassPlan& rp,
                       const dfi::ColPassPlan& cp, const dfi::RefinePassPlan* fp, hipStream_t st,
                       double* tout = nullptr, double* csout = nullptr) {
+  const dfi::TriPrep prep = tri_prep(B, B.zc);   // a solve for zc follows
   if (fp && fp->usable) {
     HIP_TRY(dfi::refine_pass_launch(*fp, S, n, m, lds, u, B.rpart, st, nullptr, -1, tout, csout));
-    HIP_TRY(dfi::refine_pass_reduce(*fp, B.rpart, out, rhs, u, lambda, st));
+    HIP_TRY(dfi::refine_pass_reduce(*fp, B.rpart, out, rhs, u, lambda, st, nullptr, prep));
   } else {
     if (tout || csout) return fail(DFISHER_E_DEVICE, "S^T u requested from a pass that does not form it");
     HIP_TRY(dfi::colpass_launch(cp, S, n, m, lds, u, nullptr, 1.0, B.t, 2, B.cpart, st));
     HIP_TRY(dfi::rowpass_launch(rp, S, nullptr, B.t, true, false, B.rpart, st));
-    HIP_TRY(dfi::rowpass_reduce(rp, B.rpart, true, false, out, nullptr, rhs, u, lambda, st));
+    HIP_TRY(dfi::rowpass_reduce(rp, B.rpart, true, false, out, nullptr, rhs, u, lambda, st, prep));
   }
   return DFISHER_OK;
 }
@@ -571,7 +575,8 @@ struct Final8 {
 dfisher_status solve_y_op(int64_t n, const double* L, const double* Dinv, const SolveBufs& B, int sweeps,
                           hipStream_t st, const WOp& wop, StageClock* clk = nullptr, dfisher_ctx* ctx = nullptr,
                           double tol = 0.0, int* done = nullptr, double* resid = nullptr, bool initial = true,
-                          double predict = 0.0, bool* met = nullptr, const Final8* f8 = nullptr) {
+                          double predict = 0.0, bool* met = nullptr, const Final8* f8 = nullptr, bool ready = false,
+                          bool* deferred = nullptr) {
   if (initial) {   // (else the caller has formed y = L^-T L^-1 b already)
     HIP_TRY(apply_factor(L, Dinv, n, B.b, B, B.y, st));
     if (clk) clk->mark(5);
@@ -585,7 +590,6 @@ dfisher_status solve_y_op(int64_t n, const double* L, const double* Dinv, const 
     double* rz = ctx->d_scalar + 4;
     double* rr = ctx->d_scalar + 3;
     if (measure) HIP_TRY(dfi::sumsq(B.b, n, ctx->d_scalar + 2, st));
-    HIP_TRY(dfi::fill_zero(B.zero, n, st));
     DF_TRY(wop(B.y, B.b, B.r, f8 ? f8->T : nullptr, f8 ? f8->cs : nullptr));   // sweep 1: r = b - W y
     if (measure) HIP_TRY(dfi::sumsq(B.r, n, rr, st));
     double prev = 1.0;
@@ -598,7 +602,7 @@ dfisher_status solve_y_op(int64_t n, const double* L, const double* Dinv, const 
         rho = bb > 0.0 ? std::sqrt(rrh / bb) : (rrh > 0.0 ? INFINITY : 0.0);
         if (resid) *resid = rho;
       }
-      HIP_TRY(apply_factor(L, Dinv, n, B.r, B, B.zc, st));
+      HIP_TRY(apply_factor(L, Dinv, n, B.r, B, B.zc, st, ready));
       bool stop = s >= sweeps;
       if (measure) {
         const double expect =
@@ -610,10 +614,12 @@ dfisher_status solve_y_op(int64_t n, const double* L, const double* Dinv, const 
         }
       }
       if (stop) {
-        if (!f8) HIP_TRY(dfi::pcg_finish(nullptr, n, 0, 1, B.zc, B.y, st));   // else the final step takes zc
+        if (!f8 && deferred) *deferred = true;   // the caller's last pass takes y + zc
+        else if (!f8) HIP_TRY(dfi::pcg_finish(nullptr, n, 0, 1, B.zc, B.y, st));   // (f8: the final step takes zc)
         if (done) *done = s;
         break;
       }
+      if (s == 1) HIP_TRY(dfi::fill_zero(B.zero, n, st));
       if (s == 1) HIP_TRY(dfi::pcg_init(nullptr, n, 0, 1, B.r, B.zc, B.p, rz, st));
       else HIP_TRY(dfi::pcg_dir(nullptr, n, 0, 1, B.r, B.zc, B.p, rz, st));
       DF_TRY(wop(B.p, B.zero, B.nq, f8 ? f8->U : nullptr, nullptr));   // -(W p)
@@ -630,11 +636,12 @@ dfisher_status solve_y(const float* S, int64_t n, int64_t m, int64_t lds, double
                        const double* Dinv, const SolveBufs& B, const dfi::RowPassPlan& rp, const dfi::ColPassPlan& cp,
                        int sweeps, hipStream_t st, StageClock* clk = nullptr, const dfi::RefinePassPlan* fp = nullptr,
                        dfisher_ctx* ctx = nullptr, double tol = 0.0, int* done = nullptr, double* resid = nullptr,
-                       bool initial = true, double predict = 0.0, bool* met = nullptr, const Final8* f8 = nullptr) {
+                       bool initial = true, double predict = 0.0, bool* met = nullptr, const Final8* f8 = nullptr,
+                       bool* deferred = nullptr) {
   const WOp wop = [&](const double* u, const double* rhs, double* out, double* tout, double* csout) {
     return w_pass(S, n, m, lds, lambda, u, rhs, out, B, rp, cp, fp, st, tout, csout);
   };
-  return solve_y_op(n, L, Dinv, B, sweeps, st, wop, clk, ctx, tol, done, resid, initial, predict, met, f8);
+  return solve_y_op(n, L, Dinv, B, sweeps, st, wop, clk, ctx, tol, done, resid, initial, predict, met, f8, true, deferred);
 }
 
 // r = b - lambda y - S (S^T y) for the current y (FP64), then w = |r| / |b| read back to the host
@@ -2090,8 +2097,11 @@ dfisher_status dfisher_factor_solve(dfisher_factor* f, const float* V, int64_t n
       const SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, nullptr, rp, cp, false, need_t, &fp);
       HIP_TRY(dfi::rowpass_launch(rp, f->S, V, nullptr, true, false, B.rpart, st));
       HIP_TRY(dfi::rowpass_reduce(rp, B.rpart, true, false, B.b, nullptr, nullptr, nullptr, 0.0, st));
-      DF_TRY(solve_y(f->S, n, m, f->lds, f->lambda, f->L, f->Dinv, B, rp, cp, sweeps, st, nullptr, &fp, ctx));
-      HIP_TRY(dfi::colpass_launch(cp, f->S, n, m, f->lds, B.y, V, f->lambda, X, f->opt.x_fp64, B.cpart, st));
+      bool deferred = false;
+      DF_TRY(solve_y(f->S, n, m, f->lds, f->lambda, f->L, f->Dinv, B, rp, cp, sweeps, st, nullptr, &fp, ctx, 0.0, nullptr,
+                     nullptr, true, 0.0, nullptr, nullptr, &deferred));
+      HIP_TRY(dfi::colpass_launch(cp, f->S, n, m, f->lds, B.y, V, f->lambda, X, f->opt.x_fp64, B.cpart, st, nullptr,
+                                  deferred ? B.zc : nullptr));
       answer();
       return DFISHER_OK;
     }
@@ -2234,8 +2244,8 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
   // the host waits for its status, and repeated only if that attempt was not the final one.
   auto first_solve = [&]() -> dfisher_status {
     clk.mark(4);
-    HIP_TRY(dfi::tri_inv_batched(B.L, n * n, n, 1, B.Dinv, st));
-    HIP_TRY(apply_factor(B.L, B.Dinv, n, B.b, B, B.y, st));
+    HIP_TRY(dfi::tri_inv_batched(B.L, n * n, n, 1, B.Dinv, st, tri_prep(B, B.y)));
+    HIP_TRY(apply_factor(B.L, B.Dinv, n, B.b, B, B.y, st, true));
     clk.mark(5);
     return DFISHER_OK;
   };
@@ -2250,9 +2260,10 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
   int done = 0;
   double resid = -1.0;
   bool met = false;
+  bool deferred = false;
   const Final8 f8{B.T8, B.U8, B.cs8, B.a8, m};
   DF_TRY(solve_y(S, n, m, lds, lambda, B.L, B.Dinv, B, rp, cp, sweeps, st, &clk, &fp, ctx, tol, &done, &resid,
-                 false, autos ? auto_floor(o) : 0.0, &met, final8 ? &f8 : nullptr));
+                 false, autos ? auto_floor(o) : 0.0, &met, final8 ? &f8 : nullptr, o.final_resid ? nullptr : &deferred));
   inf.w_resid = -1.0;
   if (o.final_resid) DF_TRY(final_residual(ctx, S, n, m, lds, lambda, B, rp, cp, fp, st, &inf.w_resid));
   if (final8) {
@@ -2266,7 +2277,8 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
     HIP_TRY(dfi::fp8_apply(B.q8, B.sc8, B.ldq, n, m, B.zf8, B.T8, B.cs8, B.a8 + 1, v, lambda, x, o.x_fp64, B.use8, st));
     HIP_TRY(dfi::colpass_launch(cp, S, n, m, lds, B.y, v, lambda, x, o.x_fp64, B.cpart, st, B.use8));
   } else {
-    HIP_TRY(dfi::colpass_launch(cp, S, n, m, lds, B.y, v, lambda, x, o.x_fp64, B.cpart, st));
+    HIP_TRY(dfi::colpass_launch(cp, S, n, m, lds, B.y, v, lambda, x, o.x_fp64, B.cpart, st, nullptr,
+                                deferred ? B.zc : nullptr));
   }
   clk.mark(7);
   inf.sweeps_done = done;
@@ -2310,8 +2322,8 @@ dfisher_status dfisher_solve_rowspace(dfisher_ctx* ctx, const float* S, int64_t 
   inf.resid = -1.0;
   auto first_solve = [&]() -> dfisher_status {
     clk.mark(4);
-    HIP_TRY(dfi::tri_inv_batched(B.L, n * n, n, 1, B.Dinv, st));
-    HIP_TRY(apply_factor(B.L, B.Dinv, n, B.b, B, B.y, st));
+    HIP_TRY(dfi::tri_inv_batched(B.L, n * n, n, 1, B.Dinv, st, tri_prep(B, B.y)));
+    HIP_TRY(apply_factor(B.L, B.Dinv, n, B.b, B, B.y, st, true));
     clk.mark(5);
     return DFISHER_OK;
   };
@@ -2324,13 +2336,14 @@ dfisher_status dfisher_solve_rowspace(dfisher_ctx* ctx, const float* S, int64_t 
   const double tol = autos && !(o.tol > 0.0) ? AUTO_TOL : o.tol;
   int done = 0;
   double resid = -1.0;
-  bool met = false;
+  bool met = false, deferred = false;
   DF_TRY(solve_y(S, n, m, lds, lambda, B.L, B.Dinv, B, rp, cp, sweeps, st, &clk, &fp, ctx, tol, &done, &resid,
-                 false, autos ? auto_floor(o) : 0.0, &met));
+                 false, autos ? auto_floor(o) : 0.0, &met, nullptr, o.final_resid ? nullptr : &deferred));
   inf.w_resid = -1.0;
   if (o.final_resid) DF_TRY(final_residual(ctx, S, n, m, lds, lambda, B, rp, cp, fp, st, &inf.w_resid));
   // x = S^T y, rounded once (FP32) or kept in FP64
-  HIP_TRY(dfi::colpass_launch(cp, S, n, m, lds, B.y, nullptr, 1.0, x, o.x_fp64 ? 2 : 3, B.cpart, st));
+  HIP_TRY(dfi::colpass_launch(cp, S, n, m, lds, B.y, nullptr, 1.0, x, o.x_fp64 ? 2 : 3, B.cpart, st, nullptr,
+                              deferred ? B.zc : nullptr));
   clk.mark(7);
   inf.sweeps_done = done;
   inf.resid = resid;

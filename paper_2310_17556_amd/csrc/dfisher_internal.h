@@ -64,6 +64,15 @@ hipError_t gram_reduce(const GramPlan& p, const float* S, const float* part, con
 // Row pass: b = S v (if v != nullptr) and d_i = |s_i|^2 (if d != nullptr), FP64 accumulation.
 // `vd` (FP64 vector) may replace `v` (FP32) for the refinement residual; at most one is set.
 // Partials per (row, column chunk) go to `part`, then are reduced in fixed order.
+// What a triangular solve (tri.hip) needs before it starts: its two outputs unset (a signalling NaN, which no arithmetic gives)
+// and its tickets at zero. The kernel before it does it on the way where it can (a launch less).
+constexpr uint64_t TRI_UNSET = 0x7FF4D15EA5ED0001ull;
+struct TriPrep {
+  double* z = nullptr;   // null: nothing to do
+  double* y = nullptr;
+  uint32_t* ticket = nullptr;
+};
+
 struct RowPassPlan {
   int64_t n, m, lds;
   int64_t nchunk;     // column chunks
@@ -87,7 +96,8 @@ hipError_t rowpass_launch_split(const RowPassPlan& p, const float* S, const floa
                                 uint16_t* lo, int64_t ldh, hipStream_t st);
 // Reduce: b_i = sum_c part_b[c][i]; when r0 != nullptr: b_i = r0_i - lam * y_i - sum_c part_b[c][i]
 hipError_t rowpass_reduce(const RowPassPlan& p, const double* part, bool want_b, bool want_d, double* b,
-                          double* d, const double* r0, const double* y, double lam, hipStream_t st);
+                          double* d, const double* r0, const double* y, double lam, hipStream_t st,
+                          const TriPrep& prep = TriPrep{});
 
 // Column pass: t_k = sum_i S_ik y_i (FP64). mode 0: x = (v - t)/lambda as FP32,
 // mode 1: same as FP64, mode 2: store t itself as FP64 (for the refinement residual), mode 3:
@@ -100,10 +110,11 @@ struct ColPassPlan {
   size_t part_bytes;  // nsplit * m * 8 when nsplit > 1, else 0
 };
 ColPassPlan colpass_plan(int64_t n, int64_t m);
-// skip (device int, may be null): when *skip != 0 at run time the kernels return at once.
+// skip (device int, may be null): when *skip != 0 at run time the kernels return at once. y2 (may be null): y + y2 in
+// y's place.
 hipError_t colpass_launch(const ColPassPlan& p, const float* S, int64_t n, int64_t m, int64_t lds, const double* y,
                           const float* v, double lambda, void* out, int mode, double* part, hipStream_t st,
-                          const int* skip = nullptr);
+                          const int* skip = nullptr, const double* y2 = nullptr);
 
 // Fused refinement pass: part[g][i] = per-workgroup partials of (S S^T y)_i with one read of S
 // (n <= 4096, m >= 16; `usable` is false otherwise and
@@ -134,7 +145,8 @@ hipError_t refine_pass_launch(const RefinePassPlan& p, const float* S, int64_t n
                               const double* y, double* part, hipStream_t st, const int* skip = nullptr,
                               int spin = -1, double* tout = nullptr, double* csout = nullptr);
 hipError_t refine_pass_reduce(const RefinePassPlan& p, const double* part, double* r, const double* b,
-                              const double* y, double lam, hipStream_t st, const int* skip = nullptr);
+                              const double* y, double lam, hipStream_t st, const int* skip = nullptr,
+                              const TriPrep& prep = TriPrep{});
 // Many problems' whole-line passes in one launch (plans with line && !split, all of one lnch):
 // job j runs workgroups [wg0, wg0 + ngroups) of its own plan (R blocks each) on its S, writing its
 // partials to part (ngroups x n doubles), S^T u to tout and S^T 1 to csout (cs launches) when set;
@@ -379,9 +391,10 @@ hipError_t trsv_launch(const double* L, const double* Dinv, int64_t n, int trans
 // transposes, once per factor. tri_solve: y = L^-T L^-1 b for nvec vectors (vector j at j n, factor j / nper at
 // L + (j / nper) sL); z: nvec n doubles of scratch, ticket: 2 words of scratch; b must not alias z or y.
 size_t tri_dinv_bytes(int64_t n);
-hipError_t tri_inv_batched(const double* L, int64_t sL, int64_t n, int64_t nfac, double* Dinv, hipStream_t st);
+hipError_t tri_inv_batched(const double* L, int64_t sL, int64_t n, int64_t nfac, double* Dinv, hipStream_t st,
+                           const TriPrep& prep = TriPrep{});
 hipError_t tri_solve_batched(const double* L, int64_t sL, const double* Dinv, int64_t n, int64_t nvec, int64_t nper,
-                             const double* b, double* z, double* y, uint32_t* ticket, hipStream_t st);
+                             const double* b, double* z, double* y, uint32_t* ticket, hipStream_t st, bool ready = false);
 // Systems of different sizes in the same launches (device job table, njobs <= 65535; nmax = the
 // largest n); a job whose skip (device int, may be null) is set is left alone.
 struct TriJob {

@@ -225,7 +225,15 @@ __device__ __forceinline__ void reduce_body(const double* __restrict__ part, int
 __global__ void __launch_bounds__(256)
 rowpass_reduce_kernel(const double* __restrict__ part, int64_t n, int64_t ngroups, int want_b, int want_d,
                       double* __restrict__ b, double* __restrict__ d, const double* __restrict__ r0,
-                      const double* __restrict__ y, double lam, const int* __restrict__ skip) {
+                      const double* __restrict__ y, double lam, const int* __restrict__ skip, TriPrep prep) {
+  if (prep.z) {   // for the triangular solve behind it
+    const int64_t i = (int64_t)blockIdx.x * 16 + threadIdx.x;
+    if (threadIdx.x < 16 && i < n) {
+      reinterpret_cast<uint64_t*>(prep.z)[i] = TRI_UNSET;
+      reinterpret_cast<uint64_t*>(prep.y)[i] = TRI_UNSET;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 2) prep.ticket[threadIdx.x] = 0;
+  }
   reduce_body(part, n, ngroups, want_b, want_d, b, d, r0, y, lam, skip, blockIdx.x);
 }
 
@@ -278,8 +286,9 @@ template <int MODE>
 __device__ __forceinline__ void colpass_body(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds,
                                              const double* __restrict__ y, const float* v, double lam, void* out,
                                              double* __restrict__ part, int64_t rps, const int* __restrict__ skip,
-                                             int64_t colblock, int64_t split) {
+                                             const double* __restrict__ y2, int64_t colblock, int64_t split) {
   if (skip && *skip) return;
+  auto y_at = [&](int64_t i) { return y2 ? y[i] + y2[i] : y[i]; };
   const int64_t col = colblock * CP_COLS + 4 * threadIdx.x;
   const int64_t r0 = split * rps;
   const int64_t r1 = min(n, r0 + rps);
@@ -298,7 +307,7 @@ __device__ __forceinline__ void colpass_body(const float* __restrict__ S, int64_
 #pragma unroll
           for (int e = 0; e < 4; ++e) sv[u][e] = (col + e < m) ? p[e] : 0.f;
         }
-        yy[u] = y[i + u];
+        yy[u] = y_at(i + u);
       }
 #pragma unroll
       for (int u = 0; u < CP_UNROLL; ++u)
@@ -313,7 +322,7 @@ __device__ __forceinline__ void colpass_body(const float* __restrict__ S, int64_
 #pragma unroll
         for (int e = 0; e < 4; ++e) s[e] = (col + e < m) ? p[e] : 0.f;
       }
-      const double yi = y[i];
+      const double yi = y_at(i);
 #pragma unroll
       for (int e = 0; e < 4; ++e) t[e] = fma((double)s[e], yi, t[e]);
     }
@@ -333,8 +342,8 @@ template <int MODE>
 __global__ void __launch_bounds__(CP_THREADS)
 colpass_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, const double* __restrict__ y,
                const float* v, double lam, void* out, double* __restrict__ part, int64_t rps,
-               const int* __restrict__ skip) {
-  colpass_body<MODE>(S, n, m, lds, y, v, lam, out, part, rps, skip, blockIdx.x, blockIdx.y);
+               const int* __restrict__ skip, const double* __restrict__ y2) {
+  colpass_body<MODE>(S, n, m, lds, y, v, lam, out, part, rps, skip, y2, blockIdx.x, blockIdx.y);
 }
 
 // many problems in one launch: enough column blocks between them, so that no rows are split
@@ -342,7 +351,7 @@ template <int MODE>
 __global__ void __launch_bounds__(CP_THREADS) colpass_jobs_kernel(JobList<ColJob> l) {
   const int k = job_of(l, blockIdx.x);
   const ColJob& j = l.job[k];
-  colpass_body<MODE>(j.S, j.n, j.m, j.lds, j.y, j.v, j.lam, j.x, nullptr, j.n, j.skip, blockIdx.x - l.blk0[k], 0);
+  colpass_body<MODE>(j.S, j.n, j.m, j.lds, j.y, j.v, j.lam, j.x, nullptr, j.n, j.skip, nullptr, blockIdx.x - l.blk0[k], 0);
 }
 
 template <int MODE>
@@ -1033,10 +1042,10 @@ hipError_t rowpass_launch_split(const RowPassPlan& p, const float* S, const floa
 }
 
 hipError_t rowpass_reduce(const RowPassPlan& p, const double* part, bool want_b, bool want_d, double* b, double* d,
-                          const double* r0, const double* y, double lam, hipStream_t st) {
+                          const double* r0, const double* y, double lam, hipStream_t st, const TriPrep& prep) {
   const dim3 grid((unsigned)((p.n + 15) / 16));
   hipLaunchKernelGGL(rowpass_reduce_kernel, grid, dim3(256), 0, st, part, p.n, p.nchunk, want_b ? 1 : 0,
-                     want_d ? 1 : 0, b, d, r0, y, lam, (const int*)nullptr);
+                     want_d ? 1 : 0, b, d, r0, y, lam, (const int*)nullptr, prep);
   return hipGetLastError();
 }
 
@@ -1055,14 +1064,14 @@ ColPassPlan colpass_plan(int64_t n, int64_t m) {
 
 hipError_t colpass_launch(const ColPassPlan& p, const float* S, int64_t n, int64_t m, int64_t lds, const double* y,
                           const float* v, double lambda, void* out, int mode, double* part, hipStream_t st,
-                          const int* skip) {
+                          const int* skip, const double* y2) {
   const dim3 grid((unsigned)((m + CP_COLS - 1) / CP_COLS), (unsigned)p.nsplit);
   double* pp = p.nsplit > 1 ? part : nullptr;
   switch (mode) {
-    case 0: hipLaunchKernelGGL(colpass_kernel<0>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip); break;
-    case 1: hipLaunchKernelGGL(colpass_kernel<1>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip); break;
-    case 3: hipLaunchKernelGGL(colpass_kernel<3>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip); break;
-    default: hipLaunchKernelGGL(colpass_kernel<2>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip); break;
+    case 0: hipLaunchKernelGGL(colpass_kernel<0>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2); break;
+    case 1: hipLaunchKernelGGL(colpass_kernel<1>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2); break;
+    case 3: hipLaunchKernelGGL(colpass_kernel<3>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2); break;
+    default: hipLaunchKernelGGL(colpass_kernel<2>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2); break;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.nsplit == 1) return e;
@@ -1212,9 +1221,9 @@ hipError_t refine_pass_launch(const RefinePassPlan& p, const float* S, int64_t n
 }
 
 hipError_t refine_pass_reduce(const RefinePassPlan& p, const double* part, double* r, const double* b,
-                              const double* y, double lam, hipStream_t st, const int* skip) {
+                              const double* y, double lam, hipStream_t st, const int* skip, const TriPrep& prep) {
   hipLaunchKernelGGL(rowpass_reduce_kernel, dim3((unsigned)((p.n + 15) / 16)), dim3(256), 0, st, part, p.n,
-                     p.ngroups + (p.tail ? 1 : 0), 1, 0, r, (double*)nullptr, b, y, lam, skip);
+                     p.ngroups + (p.tail ? 1 : 0), 1, 0, r, (double*)nullptr, b, y, lam, skip, prep);
   return hipGetLastError();
 }
 

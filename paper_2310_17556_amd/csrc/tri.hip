@@ -28,8 +28,7 @@ constexpr int IB = 16;                   // sub-blocks of the inverse
 constexpr int NI = TB / IB;
 constexpr int LDL = TB + 2;              // padded row of the block in LDS (doubles)
 constexpr int SPIN_MAX = 1 << 22;        // polls of a wait (seconds; a wait is microseconds)
-// What a value of z or y holds until it is stored: a signalling NaN, which no arithmetic gives.
-constexpr uint64_t UNSET = 0x7FF4D15EA5ED0001ull;
+constexpr uint64_t UNSET = TRI_UNSET;    // what a value of z or y holds until it is stored
 
 __device__ __forceinline__ f64x4 mfma(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -51,7 +50,7 @@ __device__ __forceinline__ double lane_read(double v, int j) {
 // n, against 42 us for 64-row blocks by one lane per column.
 __global__ void __launch_bounds__(512)
 tri_inv_kernel(const double* __restrict__ L, int64_t n, double* __restrict__ Dinv, int64_t sL, int64_t sD,
-               const TriJob* __restrict__ jobs) {
+               const TriJob* __restrict__ jobs, TriPrep prep) {
   __shared__ double Ls[TB * LDL];          // the block; its diagonal sub-blocks become X_jj
   if (jobs) {
     const TriJob& j = jobs[blockIdx.y];
@@ -67,6 +66,13 @@ tri_inv_kernel(const double* __restrict__ L, int64_t n, double* __restrict__ Din
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nb = (int)min<int64_t>(TB, n - r0);
+  if (prep.z) {   // for the solve behind it
+    if (tid < nb) {
+      reinterpret_cast<uint64_t*>(prep.z)[r0 + tid] = UNSET;
+      reinterpret_cast<uint64_t*>(prep.y)[r0 + tid] = UNSET;
+    }
+    if (J == 0 && tid < 2) prep.ticket[tid] = 0;
+  }
   {   // four rows of 128 columns at a time, all loads in flight first (clamped into the block, not guarded:
       // a branch per load would wait for each)
     const int c = tid & (TB - 1), rr = __builtin_amdgcn_readfirstlane(tid >> 7);
@@ -395,23 +401,24 @@ mirror_kernel(double* __restrict__ A, int64_t n, int64_t sA, const FactorJob* __
 
 size_t tri_dinv_bytes(int64_t n) { return 2 * (size_t)((n + TB - 1) / TB) * TB * TB * sizeof(double); }
 
-hipError_t tri_inv_batched(const double* L, int64_t sL, int64_t n, int64_t nfac, double* Dinv, hipStream_t st) {
-  if (n < 1 || nfac < 1 || nfac > 65535) return hipErrorInvalidValue;
+hipError_t tri_inv_batched(const double* L, int64_t sL, int64_t n, int64_t nfac, double* Dinv, hipStream_t st,
+                           const TriPrep& prep) {
+  if (n < 1 || nfac < 1 || nfac > 65535 || (prep.z && nfac != 1)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(tri_inv_kernel, dim3((unsigned)((n + TB - 1) / TB), (unsigned)nfac), dim3(512), 0, st, L, n, Dinv,
-                     sL, (int64_t)(tri_dinv_bytes(n) / sizeof(double)), (const TriJob*)nullptr);
+                     sL, (int64_t)(tri_dinv_bytes(n) / sizeof(double)), (const TriJob*)nullptr, prep);
   return hipGetLastError();
 }
 
 hipError_t tri_inv_grouped(const TriJob* jobs_dev, int64_t njobs, int64_t nmax, hipStream_t st) {
   if (nmax < 1 || njobs < 1 || njobs > 65535) return hipErrorInvalidValue;
   hipLaunchKernelGGL(tri_inv_kernel, dim3((unsigned)((nmax + TB - 1) / TB), (unsigned)njobs), dim3(512), 0, st,
-                     (const double*)nullptr, (int64_t)0, (double*)nullptr, (int64_t)0, (int64_t)0, jobs_dev);
+                     (const double*)nullptr, (int64_t)0, (double*)nullptr, (int64_t)0, (int64_t)0, jobs_dev, TriPrep{});
   return hipGetLastError();
 }
 
 // Several vectors of one factor share a workgroup's reads of the factor, four at a time.
 hipError_t tri_solve_batched(const double* L, int64_t sL, const double* Dinv, int64_t n, int64_t nvec, int64_t nper,
-                             const double* b, double* z, double* y, uint32_t* ticket, hipStream_t st) {
+                             const double* b, double* z, double* y, uint32_t* ticket, hipStream_t st, bool ready) {
   if (n < 1 || nvec < 1 || nvec > 65535 || nper < 1 || nvec % nper != 0) return hipErrorInvalidValue;
   const int64_t sD = (int64_t)(tri_dinv_bytes(n) / sizeof(double));
   if (n <= TB) {
@@ -421,8 +428,9 @@ hipError_t tri_solve_batched(const double* L, int64_t sL, const double* Dinv, in
   const int64_t nblk = (n + TB - 1) / TB, nfac = nvec / nper;
   const int64_t R = nper == 1 ? 1 : 4, gpf = (nper + R - 1) / R, ng = nfac * gpf, tot = n * nvec;
   if (nblk * ng > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(tri_prep_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, z, y, tot, ticket,
-                     (const TriJob*)nullptr);
+  if (!ready)
+    hipLaunchKernelGGL(tri_prep_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, z, y, tot, ticket,
+                       (const TriJob*)nullptr);
   const dim3 grid((unsigned)(nblk * ng));
   const TriJob* nj = nullptr;
   for (int t = 0; t < 2; ++t) {
