@@ -323,7 +323,7 @@ gram_kernel(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int6
 //     they alone need 6.83, a diagonal one of 64 columns and 288 products 7.89 (7.68). With 16 products' worth of idle
 //     diagonal blocks, sign multiplications of A between the products (they change nothing: these sums round
 //     symmetrically) and the loads' addresses in vector registers these took 7.97 and 15.9. Gram of 1024 x 10^6: 8.45 ms
-//     (10.44 before), 256 x 10^5: 87 us (129), 2048 x 2 10^5: 6.1 ms (7.4), of that 0.4 ms the uneven end of the launch.
+//     (10.44 before), 256 x 10^5: 77 us (129), 2048 x 2 10^5: 6.1 ms (7.4), of that 0.4 ms the uneven end of the launch.
 // vmcnt(N) with the other counters left alone (gfx9 encoding: vmcnt bits [3:0] and [15:14]).
 #define DFI_WAIT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
 // lgkmcnt(0) with the other counters left alone (lgkmcnt bits [11:8]).
@@ -539,10 +539,12 @@ __device__ __forceinline__ void gram_v2_body(const float* __restrict__ S, int64_
     };
     if (nsteps > 0) {
       read_f(st0, K0{});
-      for (int64_t s = 0; s < nsteps; s += 2) {   // an odd count ends with a step of zeros
+      int64_t s = 0;
+      for (; s + 1 < nsteps; s += 2) {
         body(K0{}, s);
         body(K1{}, s + 1);
       }
+      if (s < nsteps) body(K0{}, s);
     }
     __builtin_amdgcn_s_waitcnt(0);   // no load into LDS outlives the workgroup
 #pragma unroll
@@ -635,7 +637,7 @@ __device__ __forceinline__ void gram_v2_body(const float* __restrict__ S, int64_
   };
   if (nsteps > 0) {
     head(st0);
-    for (int64_t s = 0; s < nsteps; s += 2) {
+    for (int64_t s = 0; s < nsteps; s += 2) {   // (an odd count ends with a step of zeros: the body alone once more spills)
       body(K0{}, s);
       body(K1{}, s + 1);
     }
