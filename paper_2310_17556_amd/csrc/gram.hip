@@ -322,8 +322,8 @@ gram_kernel(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int6
 //   * Bound by the FP32 matrix rate, 64 cycles a product and SIMD. A 32-column step of 256 products takes 6.96 us where
 //     they alone need 6.83, a diagonal one of 64 columns and 288 products 7.89 (7.68). With 16 products' worth of idle
 //     diagonal blocks, sign multiplications of A between the products (they change nothing: these sums round
-//     symmetrically) and the loads' addresses in vector registers these took 7.97 and 15.9. Gram of 1024 x 10^6: 8.45 ms
-//     (10.44 before), 256 x 10^5: 77 us (129), 2048 x 2 10^5: 6.1 ms (7.4), of that 0.4 ms the uneven end of the launch.
+//     symmetrically) and the loads' addresses in vector registers these took 7.97 and 15.9. Gram of 1024 x 10^6: 7.4 ms
+//     (10.44 before), 256 x 10^5: 77 us (129), 2048 x 2 10^5: 5.7 ms (7.4).
 // vmcnt(N) with the other counters left alone (gfx9 encoding: vmcnt bits [3:0] and [15:14]).
 #define DFI_WAIT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
 // lgkmcnt(0) with the other counters left alone (lgkmcnt bits [11:8]).
@@ -354,6 +354,28 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// Work items of this kernel: the off-diagonal tiles of every slice first, then the diagonal ones, each kind in eight equal
+// parts by XCD. The short items come last and fill the end of the launch: 1024 x 10^6 (6 + 4 tiles) 8.4 -> 7.4 ms.
+__host__ __device__ __forceinline__ int64_t v2_per_xcd(int64_t tiles, int64_t nslice) { return (tiles * nslice + 7) >> 3; }
+__device__ __forceinline__ bool v2_item(int64_t w, int64_t ntile, int64_t nslice, int64_t& slice, int64_t& ti, int64_t& tj) {
+  const int64_t noff = ntile * (ntile - 1) / 2, per = v2_per_xcd(noff, nslice);
+  int64_t local = w >> 3;
+  if (local < per) {
+    const int64_t item = (w & 7) * per + local;
+    if (item >= noff * nslice) return false;
+    slice = uni64(item / noff);
+    tri_index(item - slice * noff, ti, tj);
+    ++ti;
+    return true;
+  }
+  local -= per;
+  const int64_t perd = v2_per_xcd(ntile, nslice), item = (w & 7) * perd + local;
+  if (local >= perd || item >= ntile * nslice) return false;
+  slice = uni64(item / ntile);
+  ti = tj = item - slice * ntile;
+  return true;
+}
+
 // A diagonal tile's lower triangle has 36 of the 64 blocks of 32 x 32, as 36 unordered pairs of its 8 block rows. Wave w
 // takes 9 pairs that need each block row once: with F[t] the operand of block row (w + t) & 7, the pairs F[0] x F[0, 7, 6, 5],
 // F[4] x F[4, 3, 2, 1] and F[4] x F[0] (differences 0 .. 3 from rows w and w + 4, and the one pair of w at difference 4).
@@ -364,18 +386,16 @@ constexpr int DIAG_B[NDIAG] = {0, 7, 6, 5, 4, 3, 2, 1, 0};
 
 // W: bytes a lane loads, 16 (16-byte aligned rows) or 4 (any rows).
 template <int W>
-__device__ __forceinline__ void gram_v2_body(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntri,
+__device__ __forceinline__ void gram_v2_body(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntile,
                                              int64_t nslice, int64_t kslice, float* __restrict__ part) {
   __shared__ Stage st0;
   __shared__ Stage st1;
 
-  int64_t slice, tile;
-  if (!work_item(blockIdx.x, ntri, nslice, slice, tile)) return;
-
-  int64_t ti, tj;
-  tri_index(tile, ti, tj);
+  int64_t slice, ti, tj;
+  if (!v2_item(blockIdx.x, ntile, nslice, slice, ti, tj)) return;
   ti = uni64(ti);
   tj = uni64(tj);
+  const int64_t ntri = ntile * (ntile + 1) / 2, tile = ti * (ti + 1) / 2 + tj;
   const bool diag = (ti == tj);
   const int64_t rowA = ti * T, rowB = tj * T;
   const int64_t k0 = uni64(slice * kslice);
@@ -655,15 +675,15 @@ __device__ __forceinline__ void gram_v2_body(const float* __restrict__ S, int64_
 }
 
 __global__ void __launch_bounds__(NT, 1)
-gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntri, int64_t nslice,
+gram_kernel_v2(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntile, int64_t nslice,
                int64_t kslice, float* __restrict__ part) {
-  gram_v2_body<16>(S, n, lds, m, ntri, nslice, kslice, part);
+  gram_v2_body<16>(S, n, lds, m, ntile, nslice, kslice, part);
 }
 
 __global__ void __launch_bounds__(NT, 1)
-gram_kernel_v2_words(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntri, int64_t nslice,
+gram_kernel_v2_words(const float* __restrict__ S, int64_t n, int64_t lds, int64_t m, int64_t ntile, int64_t nslice,
                      int64_t kslice, float* __restrict__ part) {
-  gram_v2_body<4>(S, n, lds, m, ntri, nslice, kslice, part);
+  gram_v2_body<4>(S, n, lds, m, ntile, nslice, kslice, part);
 }
 
 }  // namespace v2
@@ -1390,12 +1410,19 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
     // FP32 and split-BF16 never get fewer slices than the base plan: a slice is summed in FP32, and longer
     // ones would round more. (The FP8 codes' own rounding is 1e4 times that of their sums.) Split-BF16
     // keeps an even count: odd slices are negated against the accumulation's bias.
-    // An FP32 diagonal tile costs 9 / 16 of another in gram_kernel_v2.
-    const double mix = (double)(p.ntri - p.ntile) / (double)p.ntri + 0.5625 * (double)p.ntile / (double)p.ntri;
-    const double rate = prec == 2 ? 0.0141 : prec == 0 ? (use_v2(p) ? (aligned16 ? 0.227 : 0.258) * mix : 0.34) : (p.ldh > 0 ? 0.075 : 0.16);
+    const double rate =
+        prec == 2 ? 0.0141 : prec == 0 ? (use_v2(p) ? (aligned16 ? 0.227 : 0.258) : 0.34) : (p.ldh > 0 ? 0.075 : 0.16);
     auto cost = [&](int64_t ns) {
-      const int64_t ks = columns(ns), items = p.ntri * ((cap + ks - 1) / ks);
-      return (double)((items + 255) / 256) * ((double)ks * rate + 3.0) + 0.145 * (double)items;
+      const int64_t ks = columns(ns), slices = (cap + ks - 1) / ks, items = p.ntri * slices;
+      const double u = (double)ks * rate + 3.0;
+      double t = (double)((items + 255) / 256) * u;
+      if (use_v2(p)) {   // a diagonal tile costs 9 / 16 of another, and they come last
+        const int64_t off = (p.ntri - p.ntile) * slices, dia = p.ntile * slices;
+        const double d = 0.5625 * (double)ks * rate + 3.0;
+        t = off == 0 ? (double)((dia + 255) / 256) * d
+                     : std::max((double)((off + 255) / 256) * u, ((double)off * u + (double)dia * d) / 256.0 + 0.5 * d);
+      }
+      return t + 0.145 * (double)items;
     };
     const int64_t lo = prec == 2 ? 8 : p.nslice;
     double best = cost(p.nslice);
@@ -1411,6 +1438,8 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
     consider(lo);
     for (int64_t r = 1; r < 8; ++r) consider(32 * r / p.ntri);   // (an eighth of the chip, ...)
     for (int64_t r = 1; r <= 17; ++r) consider(256 * r / p.ntri);
+    if (use_v2(p) && p.ntile > 1)
+      for (int64_t r = 1; r <= 17; ++r) consider(256 * r / (p.ntri - p.ntile));
   }
   p.kslice = columns(p.nslice);
   if (q_override <= 0) {   // no slice past the last column
@@ -1480,10 +1509,11 @@ int64_t gram_tail_start(const GramPlan& p, const float* S) { return tail_start(p
 hipError_t gram_launch(const GramPlan& p, const float* S, float* part, hipStream_t st) {
   const bool vec = vec_rows(p, S);
   const dim3 grid((unsigned)(8 * items_per_xcd(p.ntri, p.nslice)));
+  const dim3 grid2((unsigned)(8 * (v2::v2_per_xcd(p.ntri - p.ntile, p.nslice) + v2::v2_per_xcd(p.ntile, p.nslice))));
   if (use_v2(p) && vec) {
-    hipLaunchKernelGGL(v2::gram_kernel_v2, grid, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
+    hipLaunchKernelGGL(v2::gram_kernel_v2, grid2, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntile, p.nslice, p.kslice, part);
   } else if (use_v2(p)) {
-    hipLaunchKernelGGL(v2::gram_kernel_v2_words, grid, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
+    hipLaunchKernelGGL(v2::gram_kernel_v2_words, grid2, dim3(v2::NT), 0, st, S, p.n, p.lds, p.m, p.ntile, p.nslice, p.kslice, part);
   } else if (p.prec == 0) {
     hipLaunchKernelGGL((gram_kernel<0, false>), grid, dim3(NTHR), 0, st, S, p.n, p.lds, p.m, p.ntri, p.nslice, p.kslice, part);
   } else if (vec) {
