@@ -168,11 +168,11 @@ GRAM_KERNEL = {"fp32": "gram_kernel_v2", "bf16x3": "gram_kernel_split", "mxfp8":
 # valid only for the kernel source they were taken on (sha256 of csrc/gram.hip); see profiles/.
 GRAM_TRAFFIC = {
     ("mxfp8", 4096, 4_000_000): {
-        "gram_hip_sha256": "ed0e1b1b8a2c47d60e3da9db03f4f431d44327d15ac2ab86941abdc907a295a7",
+        "gram_hip_sha256": "454000540df86551ca60627f02d9e75ea906bf9985d082f61d3dbcb044930056",
         # FETCH_SIZE x 2 + WRITE_SIZE x 1 (KiB -> bytes), mean of 12 launches in the latest pair of
         # counter runs; the re-reads vary from box to box and run to run (75.8 to 116.5 GB over
-        # four pairs)
-        "bytes_per_launch": 116.47e9 + 1.14e9,
+        # five pairs)
+        "bytes_per_launch": 109.66e9 + 0.51e9,
     },
 }
 
