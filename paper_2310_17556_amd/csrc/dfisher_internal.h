@@ -61,6 +61,13 @@ hipError_t gram_reduce(const GramPlan& p, const float* S, const float* part, con
                        double* W, int mirror, hipStream_t st);
 
 // ----------------------------------------------------------------------------- streaming GEMVs
+// Bytes of a buffer over `rows` rows of S whose first has `cols` columns left: it ends behind column m - 1 of the last row,
+// since S is (n - 1) lds + m floats and behind those there may be no memory (a slice big[:, c:] ends with its storage). A
+// load that begins inside it and reaches past it gets its last words as zeros. (16 lds * 4 < 2^31, rows <= 16.)
+__host__ __device__ __forceinline__ int row_records(int rows, int lds, int cols) {
+  return rows > 0 ? ((rows - 1) * lds + cols) * 4 : 0;
+}
+
 // Row pass: b = S v (if v != nullptr) and d_i = |s_i|^2 (if d != nullptr), FP64 accumulation.
 // `vd` (FP64 vector) may replace `v` (FP32) for the refinement residual; at most one is set.
 // Partials per (row, column chunk) go to `part`, then are reduced in fixed order.

@@ -732,16 +732,14 @@ __device__ __forceinline__ void refine_line_body(const float* __restrict__ S, in
   };
   const int64_t b0 = pair * R, b1 = min(nblk, b0 + R);
   const uint32_t loff = (uint32_t)(((lane >> 3) * lds + 4 * q) * 4);
-  const int rowbytes = (int)(lds * 4);
   // load c of block blk for the rows [base, base + cnt): rows past cnt read zeros (buffer records)
   auto load = [&](int64_t blk, int64_t base, int64_t cnt, int c, bool any) -> f32x4 {
     const int r0 = c * ROWS + wave * 8;
     const int rin = any ? (int)min<int64_t>(8, cnt - r0) : 0;
     const bool in = rin > 0;
     const float* bp = S + (in ? base + r0 : 0) * lds + blk * FS_COLS;
-    // the records end with the last of these rows: behind the last row of S there may be no memory
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(bp), 0, in ? rin * rowbytes - (int)(blk * FS_COLS * 4) : 0, 0x00020000);
+        const_cast<float*>(bp), 0, row_records(rin, (int)lds, (int)(m - blk * FS_COLS)), 0x00020000);
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)loff, 0, 0));
   };
   // column partials of one half from per-lane sums tq (4 columns per lane; with the column sums,

@@ -289,12 +289,12 @@ rowpass_multi_tm_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64
     }
   };
   // The wave's 16 rows of S as one buffer from a wave-uniform base (row rbase, column c0) with a
-  // 32-bit lane offset (the launcher checks 16 lds * 4 < 2^31): the records end at row n, so lanes
+  // 32-bit lane offset (the launcher checks 16 lds * 4 < 2^31): the records end with S, so lanes
   // of rows past n read zeros, and a wave with no rows below n has no records and touches no memory.
   const int rin = (int)max<int64_t>(0, min<int64_t>(16, n - rbase));
   const float* sbase = S + (rin > 0 ? rbase : 0) * lds + c0;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float*>(sbase), 0, rin > 0 ? (int)((int64_t)rin * lds * 4 - c0 * 4) : 0, 0x00020000);
+      const_cast<float*>(sbase), 0, row_records(rin, (int)lds, (int)(m - c0)), 0x00020000);
   const uint32_t qoff = (uint32_t)((int64_t)q * lds * 4);
   // NA independent accumulators per group (product j of each load into accumulator j % NA), added
   // in a fixed order at the end: a single chain of dependent products per group would, with few groups,
