@@ -1410,10 +1410,11 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
     // work item writes and the reduction reads 256 KB of partials. (The base plan leaves most of the chip
     // idle for small n, and a round nearly empty where ntri is a little over a multiple of 32: at
     // n = 256, m = 1e5 FP32 48 workgroups took 550 us with the reduction, 241 take 140; at n = 2048, m = 1e4
-    // split-BF16 288 took 220, 504 take 167; at n = 4096, m = 1e5 FP8 32 slices took 1200, 9 take 905.) Measured rates, us a column and tile: FP32 0.227
+    // split-BF16 288 took 220, 504 take 167.) Measured rates, us a column and tile: FP32 0.227
     // (0.258 unaligned rows; 0.34 in gram_kernel), split-BF16 from planes 0.075, inside the kernel 0.16, FP8 0.0141.
-    // FP32 and split-BF16 never get fewer slices than the base plan: a slice is summed in FP32, and longer
-    // ones would round more. (The FP8 codes' own rounding is 1e4 times that of their sums.) Split-BF16
+    // Never fewer slices than the base plan: a slice is summed in FP32 and the slices in FP64. (FP8 at n = 4096, m = 1e5:
+    // 9 slices would take 905 us where 32 take 1200, but with 3.5 times as many products a sum in FP32; the codes of a
+    // one-signed S, n = 300, m = 1e5, miss their exact Gram by 1.67e-6 with 8 slices, 1.65e-6 with 32.) Split-BF16
     // keeps an even count: odd slices are negated against the accumulation's bias.
     const double rate =
         prec == 2 ? 0.0141 : prec == 0 ? (use_v2(p) ? (aligned16 ? 0.227 : 0.258) : 0.34) : (p.ldh > 0 ? 0.075 : 0.16);
@@ -1429,18 +1430,17 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
       }
       return t + 0.145 * (double)items;
     };
-    const int64_t lo = prec == 2 ? 8 : p.nslice;
+    const int64_t lo = p.nslice;
     double best = cost(p.nslice);
     auto consider = [&](int64_t ns) {
       if (prec == 1) ns &= ~(int64_t)1;
-      if (ns < lo || (ns > lo && columns(ns) < 256) || p.ntri * ns > 4352) return;
+      if (ns <= lo || columns(ns) < 256 || p.ntri * ns > 4352) return;
       const double c = cost(ns);
       if (c < best - 1e-9) {
         best = c;
         p.nslice = ns;
       }
     };
-    consider(lo);
     for (int64_t r = 1; r < 8; ++r) consider(32 * r / p.ntri);   // (an eighth of the chip, ...)
     for (int64_t r = 1; r <= 17; ++r) consider(256 * r / p.ntri);
     if (use_v2(p) && p.ntile > 1)

@@ -54,3 +54,35 @@ def test_row_passes_stay_inside_S(rules, n, m, lds):
                     seen[w] = True
         inside = np.arange(end) % lds < m
         assert seen[inside].all()
+
+
+def base_slices(n, m):
+    """The slice count that fills 256 compute units best with at least 2048 columns a slice: a multiple of 8."""
+    ntri = (n + 255) // 256 * ((n + 255) // 256 + 1) // 2
+    best, score = 1, -1.0
+    for q in range(1, max(1, min(64, m // (8 * 2048))) + 1):
+        rounds = (8 * q * ntri + 255) // 256
+        s = 8 * q * ntri / (rounds * 256) * (1.0 if rounds >= 4 else 0.5 + 0.125 * rounds)
+        if s > score + 1e-9:
+            best, score = q, s
+    return 8 * best
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("aligned", [1, 0])
+def test_gram_slices_are_no_longer_than_the_base_plans(rules, prec, aligned):
+    """A slice is summed in FP32 and slices are added in FP64, so no plan may take longer slices than the base plan."""
+    ns, ks = ctypes.c_int64(), ctypes.c_int64()
+    L = [ctypes.c_int64] * 3 + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int64)] * 2
+    rules.rules_gram_plan.argtypes = L
+    step = {0: 32, 1: 32, 2: 64}[prec]
+    for n in (1, 32, 250, 257, 520, 1000, 1500, 2048, 3001, 4096, 8192):
+        for m in (40, 1000, 10_000, 40_000, 99_999, 250_000, 1_000_000, 4_000_000):
+            if prec == 2 and not aligned:
+                continue
+            rules.rules_gram_plan(n, m, m, prec, aligned, 0, -1, ns, ks)
+            cap = {0: m, 1: (m + 63) // 64 * 64, 2: (m + 127) // 128 * 128}[prec]
+            b = base_slices(n, m)
+            most = max(1, ((cap + b - 1) // b + step - 1) // step) * step
+            assert ks.value <= most, (n, m, ns.value, ks.value, b, most)
+            assert ns.value * ks.value >= cap and ks.value % step == 0
