@@ -27,8 +27,10 @@
  *              validated on the host before any device call: null pointers, n < 1, m < 1,
  *              lds < m, lambda not finite or not > 0, and unknown enum values return
  *              DFISHER_E_INVALID_ARG. A missing device or any HIP runtime error returns
- *              DFISHER_E_DEVICE. dfisher_last_error() gives a per-thread message for the
- *              last failure.
+ *              DFISHER_E_DEVICE, and so does a wait inside a kernel that gave up (seconds, where a
+ *              wait takes microseconds): for one inside a solve that returned without
+ *              synchronising (its x is NaN) the next call on the context that synchronises.
+ *              dfisher_last_error() gives a per-thread message for the last failure.
  *   Threads    Calls on one context must not overlap. Different contexts are independent.
  */
 #ifndef DFISHER_H
@@ -129,7 +131,8 @@ typedef struct dfisher_options {
  * (stream capture on `stream`, any capture mode) and replay it. With the flag:
  *   - infos is a DEVICE pointer to nlam records (or NULL), written by the call's last kernel;
  *     read them after the stream has finished. A failed factorisation shows there only
- *     (potrf_info != 0, that lambda's x unspecified): the return value reports argument,
+ *     (potrf_info != 0, that lambda's x unspecified; -1: a wait inside the factorisation, or for
+ *     every record inside a triangular solve, gave up): the return value reports argument,
  *     workspace and HIP errors, never DFISHER_E_NOT_SPD.
  *   - shift_policy must be DFISHER_SHIFT_NONE or DFISHER_SHIFT_ALWAYS; DFISHER_SHIFT_ON_FAILURE
  *     refactors after a host-side decision and returns DFISHER_E_UNSUPPORTED. DFISHER_SWEEPS_AUTO

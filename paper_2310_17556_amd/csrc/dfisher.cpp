@@ -81,11 +81,15 @@ struct dfisher_ctx {
   void* ws = nullptr;
   size_t ws_bytes = 0;
   bool ws_frozen = false;       // a call captured into a caller's graph holds ws: never reallocated
-  int64_t* h_status = nullptr;  // pinned: [0] potrf info
-  double* h_scalar = nullptr;   // pinned: [0] diagonal max
-  int64_t* d_info = nullptr;
-  int32_t* d_flag = nullptr;
-  double* d_scalar = nullptr;
+  // one device block of 8-byte slots, the first of them mirrored in pinned host memory: the triangular solves' tickets, their
+  // word that a wait gave up (raised until a call reports it), the Cholesky's status, scalars ([0] diagonal max)
+  uint32_t* d_tick = nullptr;   // slot 0; d_tick[2], slot 1: gave up
+  int64_t* d_info = nullptr;    // slot 2
+  double* d_scalar = nullptr;   // slots 3 ..
+  int32_t* d_flag = nullptr;    // the last slot
+  int64_t* h_gave_up = nullptr;
+  int64_t* h_status = nullptr;
+  double* h_scalar = nullptr;
   // uneven batches: job tables (own buffer, never carved from ws) and the captured graph of the
   // last call, replayed when the next call has the same arguments and buffers
   bool graphs = true;
@@ -267,6 +271,21 @@ dfisher_status check_no_tol(const dfisher_options& o) {
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
+constexpr int STATUS_SLOTS = 32;
+constexpr int HOST_SLOTS = 6;   // gave up, status, scalars 0 .. 3
+// The status slots 1 .. count to the host, for the call's next synchronisation; check_waits after it.
+dfisher_status fetch_status(dfisher_ctx* ctx, int count, hipStream_t st) {
+  HIP_TRY(hipMemcpyAsync(ctx->h_gave_up, ctx->d_tick + 2, (size_t)count * 8, hipMemcpyDeviceToHost, st));
+  return DFISHER_OK;
+}
+// A triangular solve whose wait gave up left unset values (NaN) in its result.
+dfisher_status check_waits(dfisher_ctx* ctx, hipStream_t st) {
+  if (ctx->h_gave_up[0] == 0) return DFISHER_OK;
+  HIP_TRY(dfi::fill_zero(reinterpret_cast<double*>(ctx->d_tick + 2), 1, st));
+  return fail(DFISHER_E_DEVICE, "a triangular solve of this call, or of an earlier one on this context that did not wait for "
+              "its result, gave up waiting for one of its own blocks: that result is NaN");
+}
+
 bool rows_aligned16(const float* S, int64_t lds) {
   return (lds % 4) == 0 && (reinterpret_cast<uintptr_t>(S) & 15) == 0;
 }
@@ -364,7 +383,7 @@ struct SolveBufs {
   double* Dinv;    // inverses of L's 128 x 128 diagonal blocks
   double* dkk;     // Cholesky scratch: current diagonal block inverse
   double* pack;    // Cholesky scratch: the packed factor, then its ticket (in the Gram partials, free by then)
-  double* tw;      // the triangular solves' tickets
+  uint32_t* tick;  // the triangular solves' tickets (the context's)
   uint8_t* q8;     // scaled-FP8 codes of S (n x ldq), when the Gram is MXFP8
   uint8_t* sc8;    // their E8M0 scales (n x ldq/32)
   int64_t ldq;
@@ -408,7 +427,6 @@ SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const
   s.pack = !need_L && !s.W ? nullptr
            : gp && gp->part_bytes >= chol_scratch_bytes(n, 1)
                ? reinterpret_cast<double*>(s.gpart) : c.take<double>(chol_scratch_bytes(n, 1) / sizeof(double));
-  s.tw = c.take<double>(1);
   s.ldq = dfi::fp8_ldq(m);
   const bool fp8 = gp && gp->prec == DFISHER_GRAM_MXFP8;
   s.q8 = fp8 ? c.take<uint8_t>((size_t)(n * s.ldq)) : nullptr;
@@ -430,9 +448,9 @@ SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const
 // (ready: the kernel before it had tri_prep(B, y))
 hipError_t apply_factor(const double* L, const double* Dinv, int64_t n, const double* b, const SolveBufs& B, double* y,
                         hipStream_t st, bool ready = false) {
-  return dfi::tri_solve_batched(L, n * n, Dinv, n, 1, 1, b, B.z, y, reinterpret_cast<uint32_t*>(B.tw), st, ready);
+  return dfi::tri_solve_batched(L, n * n, Dinv, n, 1, 1, b, B.z, y, B.tick, st, ready);
 }
-dfi::TriPrep tri_prep(const SolveBufs& B, double* y) { return dfi::TriPrep{B.z, y, reinterpret_cast<uint32_t*>(B.tw)}; }
+dfi::TriPrep tri_prep(const SolveBufs& B, double* y) { return dfi::TriPrep{B.z, y, B.tick}; }
 
 // Cholesky of W (+ tau I) into L following the shift policy. Synchronises once per attempt.
 // `spec`, if given, is enqueued right after the first attempt's factorisation and before the wait
@@ -459,10 +477,11 @@ dfisher_status factor_with_policy(dfisher_ctx* ctx, const double* W, double* L, 
     if (scale != 0.0 && !have_max) DF_TRY(diag_max());
     HIP_TRY(factor_launch(L, n, 1, n * n, ctx->d_info, ctx->d_flag, dkk, pack, st, W, nullptr, scale, ctx->d_scalar));
     if (attempts == 0 && spec) DF_TRY(spec());
-    HIP_TRY(hipMemcpyAsync(ctx->h_status, ctx->d_info, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    DF_TRY(fetch_status(ctx, 2, st));
     HIP_TRY(hipStreamSynchronize(st));
     ++attempts;
     info = ctx->h_status[0];
+    DF_TRY(check_waits(ctx, st));
     if (info < 0) return fail(DFISHER_E_DEVICE, "the Cholesky gave up waiting for one of its own tiles");
     if (info == 0 || policy == DFISHER_SHIFT_NONE || attempts >= MAX_SHIFT_ATTEMPTS) break;
     if (!have_max) {
@@ -596,8 +615,9 @@ dfisher_status solve_y_op(int64_t n, const double* L, const double* Dinv, const 
     for (int s = 1;; ++s) {
       double rho = -1.0;
       if (measure) {
-        HIP_TRY(hipMemcpyAsync(ctx->h_scalar + 2, ctx->d_scalar + 2, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
+        DF_TRY(fetch_status(ctx, HOST_SLOTS, st));
         HIP_TRY(hipStreamSynchronize(st));
+        DF_TRY(check_waits(ctx, st));
         const double bb = ctx->h_scalar[2], rrh = ctx->h_scalar[3];
         rho = bb > 0.0 ? std::sqrt(rrh / bb) : (rrh > 0.0 ? INFINITY : 0.0);
         if (resid) *resid = rho;
@@ -659,8 +679,9 @@ dfisher_status final_residual(dfisher_ctx* ctx, const float* S, int64_t n, int64
   }
   HIP_TRY(dfi::sumsq(B.b, n, ctx->d_scalar + 2, st));
   HIP_TRY(dfi::sumsq(B.r, n, ctx->d_scalar + 3, st));
-  HIP_TRY(hipMemcpyAsync(ctx->h_scalar + 2, ctx->d_scalar + 2, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
+  DF_TRY(fetch_status(ctx, HOST_SLOTS, st));
   HIP_TRY(hipStreamSynchronize(st));
+  DF_TRY(check_waits(ctx, st));
   const double bb = ctx->h_scalar[2], rr = ctx->h_scalar[3];
   *w = bb > 0.0 ? std::sqrt(rr / bb) : (rr > 0.0 ? INFINITY : 0.0);
   return DFISHER_OK;
@@ -672,7 +693,7 @@ dfisher_status final_residual(dfisher_ctx* ctx, const float* S, int64_t n, int64
 // Per vector: y = W_f^-1 S v_r, `sweeps` FP64 refinement sweeps against the exact operator, then
 // x = (v_r - S^T y) / lambda_f. Needs nfac * nrhs <= 65535.
 struct MultiBufs {
-  uint32_t* ticket;
+  uint32_t* ticket;   // the triangular solves' (the context's)
   double *Bs, *Bexp, *Y, *R, *D, *Yi;
   double *T[dfi::MULTI_GROUPS], *part[dfi::MULTI_GROUPS];   // per group of vectors that shares a pass
   int groups = 1;                    // at most
@@ -705,7 +726,6 @@ MultiBufs carve_multi(Carver& c, int64_t n, int64_t m, int64_t nrhs, int64_t nve
   b.Y = c.take<double>((size_t)(nvec * n));
   b.R = c.take<double>((size_t)(nvec * n));
   b.D = c.take<double>((size_t)(nvec * n));
-  b.ticket = c.take<uint32_t>(2);
   // groups that share a pass: as many as there are, two without the memory for more
   b.groups = (int)std::min<int64_t>(most, (nvec + dfi::MULTI_VECS - 1) / dfi::MULTI_VECS);
   for (int g = 0; g < b.groups; ++g) {
@@ -976,7 +996,6 @@ struct UnevenLayout {
   uint32_t* ticket = nullptr;
   int64_t ntask = 0;
   double *b = nullptr, *d = nullptr, *y = nullptr, *z = nullptr, *r = nullptr;
-  uint32_t* tick = nullptr;                // the triangular solves' tickets
   double *zc = nullptr, *p = nullptr, *nq = nullptr, *zero = nullptr, *rz = nullptr;   // refinement (PCG)
   double *bb = nullptr, *rr = nullptr, *prev = nullptr, *resid = nullptr;   // per table entry
   int *stop = nullptr, *done = nullptr, *met = nullptr;
@@ -1118,7 +1137,6 @@ void uneven_layout(const dfisher_ctx* ctx, char* base, int32_t np, const float* 
   U.y = c.take<double>((size_t)U.ntot);
   U.z = c.take<double>((size_t)U.ntot);
   U.r = c.take<double>((size_t)U.ntot);
-  U.tick = c.take<uint32_t>(2);
   U.zc = c.take<double>((size_t)U.ntot);
   U.p = c.take<double>((size_t)U.ntot);
   U.nq = c.take<double>((size_t)U.ntot);
@@ -1178,7 +1196,6 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
                               const int64_t* seg, const int* cap, double tol,
                               bool predict, const std::vector<int32_t>& jpos, const GroupedPasses& G,
                               hipStream_t st) {
-  (void)ctx;
   // Gram stage, largest first: b_p = S_p v_p, d_p, W_p = S_p S_p^T + lambda_p I. With every
   // problem's codes kept (f8): the row passes per problem, then one Gram launch over all problems'
   // work items, then each problem's reduction, projection and shift; else the whole stage per
@@ -1241,7 +1258,7 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
   }
   HIP_TRY(dfi::tri_inv_grouped(tj_y, np, U.nmax, st));
   // y = L^-T L^-1 b for every problem
-  HIP_TRY(dfi::tri_solve_grouped(tj_y, np, U.nmax, U.tick, st));
+  HIP_TRY(dfi::tri_solve_grouped(tj_y, np, U.nmax, ctx->d_tick, st));
   // out_p = rhs_p - lambda_p u_p - S_p (S_p^T u_p) (FP64 accumulation): the residual of y_p
   // (rhs = b, u = y) or -(W_p p_p) (rhs = 0, u = p)
   // (skip: the problem's stop flag; its fused pass then reads nothing. The column pass + row pass
@@ -1306,7 +1323,7 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
       const int64_t act = nactive[(size_t)(s - 1)];
       const int64_t cont = s < max_sw ? nactive[(size_t)s] : 0;
       // zc = L^-T L^-1 r for the problems that may run this sweep
-      HIP_TRY(dfi::tri_solve_grouped(tj_c, act, U.nmax, U.tick, st));
+      HIP_TRY(dfi::tri_solve_grouped(tj_c, act, U.nmax, ctx->d_tick, st));
       HIP_TRY(dfi::pcg_decide(seg, 0, 0, act, s, c, U.zc, U.y, st));      // stop: y += zc
       if (cont == 0) break;
       if (s == 1) HIP_TRY(dfi::pcg_init(seg, 0, 0, cont, U.r, U.zc, U.p, U.rz, st, U.stop));
@@ -1672,7 +1689,9 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
     HIP_TRY(hipMemcpyAsync(hmax.data(), U.dmax, (size_t)np * sizeof(double), hipMemcpyDeviceToHost, st));
   if (o.final_resid)
     HIP_TRY(hipMemcpyAsync(hres.data(), U.res, (size_t)(2 * np) * sizeof(double), hipMemcpyDeviceToHost, st));
+  DF_TRY(fetch_status(ctx, 1, st));
   HIP_TRY(hipStreamSynchronize(st));
+  DF_TRY(check_waits(ctx, st));
   dfisher_status worst = DFISHER_OK;
   bool unmet = false;
   for (int32_t p = 0; p < np; ++p) {
@@ -1709,26 +1728,30 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
 }
 
 // The per-lambda records of an asynchronous batched call, written on the device after its
-// factorisations: status, the up-front shift scale0 * max_i G_ii (dmax from diag_max, read only
-// when scale0 != 0), one attempt, the fixed sweep count, nothing measured.
+// factorisations: status (-1 also where a triangular solve gave up, which is thereby reported), the up-front shift
+// scale0 * max_i G_ii (dmax from diag_max, read only when scale0 != 0), one attempt, the fixed sweep count, nothing
+// measured. One workgroup.
 __global__ void batch_infos_kernel(dfisher_info* __restrict__ out, int64_t nlam, const int64_t* __restrict__ info,
-                                   double scale0, const double* __restrict__ dmax, int32_t sweeps) {
-  const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= nlam) return;
-  dfisher_info r;
-  r.potrf_info = info[l];
-  r.shift = scale0 != 0.0 ? scale0 * dmax[0] : 0.0;
-  r.attempts = 1;
-  r.sweeps_done = sweeps;
-  r.resid = -1.0;
-  r.w_resid = -1.0;
-  out[l] = r;
+                                   double scale0, const double* __restrict__ dmax, int32_t sweeps,
+                                   uint32_t* __restrict__ gave_up) {
+  const bool lost = *gave_up != 0;
+  for (int64_t l = threadIdx.x; l < nlam; l += blockDim.x) {
+    dfisher_info r;
+    r.potrf_info = lost ? -1 : info[l];
+    r.shift = scale0 != 0.0 ? scale0 * dmax[0] : 0.0;
+    r.attempts = 1;
+    r.sweeps_done = sweeps;
+    r.resid = -1.0;
+    r.w_resid = -1.0;
+    out[l] = r;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) *gave_up = 0;
 }
 
 hipError_t write_batch_infos(dfisher_info* out, int64_t nlam, const int64_t* info, double scale0, const double* dmax,
-                             int32_t sweeps, hipStream_t st) {
-  hipLaunchKernelGGL(batch_infos_kernel, dim3((unsigned)((nlam + 255) / 256)), dim3(256), 0, st, out, nlam, info,
-                     scale0, dmax, sweeps);
+                             int32_t sweeps, uint32_t* gave_up, hipStream_t st) {
+  hipLaunchKernelGGL(batch_infos_kernel, dim3(1), dim3(256), 0, st, out, nlam, info, scale0, dmax, sweeps, gave_up);
   return hipGetLastError();
 }
 
@@ -1788,18 +1811,21 @@ dfisher_status dfisher_ctx_create(int device, dfisher_ctx** out) {
   dfisher_ctx* c = new dfisher_ctx();
   c->device = device;
   void* dstat = nullptr;
-  if (hipMalloc(&dstat, 256) != hipSuccess || hipHostMalloc((void**)&c->h_status, 64, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&c->h_scalar, 64, hipHostMallocDefault) != hipSuccess) {
+  if (hipMalloc(&dstat, STATUS_SLOTS * 8) != hipSuccess || hipMemset(dstat, 0, STATUS_SLOTS * 8) != hipSuccess ||
+      hipHostMalloc((void**)&c->h_gave_up, HOST_SLOTS * 8, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     if (dstat) (void)hipFree(dstat);
-    if (c->h_status) (void)hipHostFree(c->h_status);
-    if (c->h_scalar) (void)hipHostFree(c->h_scalar);
     delete c;
     return fail(DFISHER_E_NO_MEMORY, "context allocation failed");
   }
-  c->d_info = reinterpret_cast<int64_t*>(dstat);
-  c->d_flag = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(dstat) + 64);
-  c->d_scalar = reinterpret_cast<double*>(reinterpret_cast<char*>(dstat) + 128);
+  auto* slot = static_cast<int64_t*>(dstat);
+  c->d_tick = reinterpret_cast<uint32_t*>(slot);
+  c->d_info = slot + 2;
+  c->d_scalar = reinterpret_cast<double*>(slot + 3);
+  c->d_flag = reinterpret_cast<int32_t*>(slot + STATUS_SLOTS - 1);
+  c->h_status = c->h_gave_up + 1;
+  c->h_scalar = reinterpret_cast<double*>(c->h_gave_up + 2);
+  std::memset(c->h_gave_up, 0, HOST_SLOTS * 8);
   for (int i = 0; i < NEV; ++i) {
     if (hipEventCreate(&c->ev[i]) != hipSuccess) {
       (void)hipGetLastError();
@@ -1809,8 +1835,7 @@ dfisher_status dfisher_ctx_create(int device, dfisher_ctx** out) {
   dfisher_status si = init_kernels();
   if (si != DFISHER_OK) {
     (void)hipFree(dstat);
-    (void)hipHostFree(c->h_status);
-    (void)hipHostFree(c->h_scalar);
+    (void)hipHostFree(c->h_gave_up);
     delete c;
     return si;
   }
@@ -1828,9 +1853,8 @@ dfisher_status dfisher_ctx_destroy(dfisher_ctx* ctx) {
   if (ctx->ws) (void)hipFree(ctx->ws);
   for (int i = 0; i < NEV; ++i)
     if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
-  if (ctx->d_info) (void)hipFree(ctx->d_info);
-  if (ctx->h_status) (void)hipHostFree(ctx->h_status);
-  if (ctx->h_scalar) (void)hipHostFree(ctx->h_scalar);
+  if (ctx->d_tick) (void)hipFree(ctx->d_tick);
+  if (ctx->h_gave_up) (void)hipHostFree(ctx->h_gave_up);
   delete ctx;
   return DFISHER_OK;
 }
@@ -2094,7 +2118,8 @@ dfisher_status dfisher_factor_solve(dfisher_factor* f, const float* V, int64_t n
     const dfi::RefinePassPlan fp = dfi::refine_pass_plan(n, m, f->lds, f->S);
     const bool need_t = sweeps > 0 && !fp.usable;
     if (ensure_ws(ctx, carve(nullptr, n, m, nullptr, rp, cp, false, need_t, &fp).bytes) == DFISHER_OK) {
-      const SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, nullptr, rp, cp, false, need_t, &fp);
+      SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, nullptr, rp, cp, false, need_t, &fp);
+      B.tick = ctx->d_tick;
       HIP_TRY(dfi::rowpass_launch(rp, f->S, V, nullptr, true, false, B.rpart, st));
       HIP_TRY(dfi::rowpass_reduce(rp, B.rpart, true, false, B.b, nullptr, nullptr, nullptr, 0.0, st));
       bool deferred = false;
@@ -2120,6 +2145,7 @@ dfisher_status dfisher_factor_solve(dfisher_factor* f, const float* V, int64_t n
     DF_TRY(ensure_ws(ctx, lay(nullptr)));
   }
   lay(static_cast<char*>(ctx->ws));
+  mb.ticket = ctx->d_tick;
   const double lam = f->lambda;
   DF_TRY(multi_solve(f->S, n, m, f->lds, 1, f->L, f->Dinv, &lam, V, nrhs, ldv, X, ldx, f->opt.x_fp64, f->opt.sweeps, rm,
                      mb, st));
@@ -2159,7 +2185,6 @@ dfisher_status dfisher_factor_solve_noalloc(const dfisher_factor* f, const float
     B.p = c.take<double>((size_t)n);
     B.nq = c.take<double>((size_t)n);
     B.zero = c.take<double>((size_t)n);
-    B.tw = c.take<double>(1);
     return c.off;
   };
   SolveBufs B;
@@ -2170,6 +2195,7 @@ dfisher_status dfisher_factor_solve_noalloc(const dfisher_factor* f, const float
   char* base = static_cast<char*>(scratch_ptr(ctx->device));
   if (!base) return fail(DFISHER_E_DEVICE, "no-alloc scratch of device %d was not set up", ctx->device);
   lay(base, B);
+  B.tick = ctx->d_tick;
   // b = S v, y = W^-1 b through the factor (+ sweeps), x = (v - S^T y) / lambda
   HIP_TRY(dfi::rowpass_launch(rp, f->S, v, nullptr, true, false, B.rpart, st));
   HIP_TRY(dfi::rowpass_reduce(rp, B.rpart, true, false, B.b, nullptr, nullptr, nullptr, 0.0, st));
@@ -2232,6 +2258,7 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
   };
   DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
   SolveBufs B = lay(static_cast<char*>(ctx->ws));
+  B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
   // one pass over S (b = S v, the exact diagonal |s_i|^2, the FP8 codes if used), then step 1
   DF_TRY(gram_stage(S, v, gp, rp, B, lambda, B.W, 0, st, &clk, is_centered(o), B.cs8 ? B.use8 + 1 : nullptr));
@@ -2313,6 +2340,7 @@ dfisher_status dfisher_solve_rowspace(dfisher_ctx* ctx, const float* S, int64_t 
   const bool need_t = (o.sweeps != 0 || o.final_resid) && !fp.usable;
   DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return carve(nullptr, n, m, &gp, rp, cp, true, need_t, &fp).bytes; }));
   SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, true, need_t, &fp);
+  B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
   // one pass over S for the exact diagonal (and the FP8 codes), then step 1; b = f
   DF_TRY(gram_stage(S, nullptr, gp, rp, B, lambda, B.W, 0, st, &clk, is_centered(o)));
@@ -2443,6 +2471,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
   Extra X;
   DF_TRY(ensure_gram_ws(ctx, Z, gp, [&] { return lay(nullptr, B, X); }));
   lay(static_cast<char*>(ctx->ws), B, X);
+  B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
   // Z Z^T (both triangles, exact FP64 diagonal) and the embedded W
   DF_TRY(gram_stage(Z, nullptr, gp, rp, B, 0.0, X.G, 1, st, &clk));
@@ -2506,8 +2535,9 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
     DF_TRY(wop(B.y, B.b, B.r, nullptr, nullptr));
     HIP_TRY(dfi::sumsq(B.b, N, ctx->d_scalar + 2, st));
     HIP_TRY(dfi::sumsq(B.r, N, ctx->d_scalar + 3, st));
-    HIP_TRY(hipMemcpyAsync(ctx->h_scalar + 2, ctx->d_scalar + 2, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
+    DF_TRY(fetch_status(ctx, HOST_SLOTS, st));
     HIP_TRY(hipStreamSynchronize(st));
+    DF_TRY(check_waits(ctx, st));
     const double bb = ctx->h_scalar[2], rr = ctx->h_scalar[3];
     inf.w_resid = bb > 0.0 ? std::sqrt(rr / bb) : (rr > 0.0 ? INFINITY : 0.0);
   }
@@ -2614,6 +2644,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   }
   DF_TRY(ensure_ws(ctx, need));
   layout(static_cast<char*>(ctx->ws), B, Lall, Dall, dkk, dinfo, dflag, mb);
+  mb.ticket = ctx->d_tick;
 
   // the shared Gram G = S S^T (exact diagonal, no lambda), formed once
   DF_TRY(gram_stage(S, nullptr, gp, rp, B, 0.0, B.W, 0, st, nullptr, is_centered(o), mb.cs ? mb.cflag : nullptr));
@@ -2633,14 +2664,16 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
     HIP_TRY(dfi::tri_inv_batched(Lall, n * n, n, nlam, Dall, st));
     DF_TRY(multi_solve(S, n, m, lds, nlam, Lall, Dall, lambdas, V, nrhs, ldv, X, ldx, o.x_fp64, sweeps, rm, mb, st,
                            final8 ? &mf8 : nullptr));
-    if (infos) HIP_TRY(write_batch_infos(infos, nlam, dinfo, scale0, ctx->d_scalar, sweeps, st));
+    if (infos) HIP_TRY(write_batch_infos(infos, nlam, dinfo, scale0, ctx->d_scalar, sweeps, ctx->d_tick + 2, st));
     return DFISHER_OK;
   }
   std::vector<int64_t> hinfo((size_t)nlam);
   double dmax = 0.0;
   HIP_TRY(hipMemcpyAsync(hinfo.data(), dinfo, (size_t)nlam * sizeof(int64_t), hipMemcpyDeviceToHost, st));
   if (scale0 != 0.0) HIP_TRY(hipMemcpyAsync(&dmax, ctx->d_scalar, sizeof(double), hipMemcpyDeviceToHost, st));
+  DF_TRY(fetch_status(ctx, 1, st));
   HIP_TRY(hipStreamSynchronize(st));
+  DF_TRY(check_waits(ctx, st));
   dfisher_status worst = DFISHER_OK;
   std::vector<dfisher_info> linf((size_t)nlam);
   int sweeps = o.sweeps == DFISHER_SWEEPS_AUTO ? 0 : o.sweeps;   // AUTO: the largest count any lambda needs

@@ -396,7 +396,8 @@ hipError_t trsv_launch(const double* L, const double* Dinv, int64_t n, int trans
 // The same for the library's own factors, which are kept mirrored (L below the diagonal, L^T above it;
 // tri.hip). tri_inv: Dinv (tri_dinv_bytes(n) per factor), the 128 x 128 diagonal blocks' inverses and their
 // transposes, once per factor. tri_solve: y = L^-T L^-1 b for nvec vectors (vector j at j n, factor j / nper at
-// L + (j / nper) sL); z: nvec n doubles of scratch, ticket: 2 words of scratch; b must not alias z or y.
+// L + (j / nper) sL); z: nvec n doubles of scratch, ticket: 2 words of scratch, behind them one that is raised when a wait
+// gave up and otherwise left alone; b must not alias z or y.
 size_t tri_dinv_bytes(int64_t n);
 hipError_t tri_inv_batched(const double* L, int64_t sL, int64_t n, int64_t nfac, double* Dinv, hipStream_t st,
                            const TriPrep& prep = TriPrep{});

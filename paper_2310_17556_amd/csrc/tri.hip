@@ -17,6 +17,7 @@
 #include "dfisher_internal.h"
 
 #include <algorithm>
+#include <cstdlib>
 
 namespace dfi {
 namespace {
@@ -28,6 +29,7 @@ constexpr int IB = 16;                   // sub-blocks of the inverse
 constexpr int NI = TB / IB;
 constexpr int LDL = TB + 2;              // padded row of the block in LDS (doubles)
 constexpr int SPIN_MAX = 1 << 22;        // polls of a wait (seconds; a wait is microseconds)
+constexpr int SPIN_BUSY = 64;            // of them without a pause
 constexpr uint64_t UNSET = TRI_UNSET;    // what a value of z or y holds until it is stored
 
 __device__ __forceinline__ f64x4 mfma(double a, double b, f64x4 c) {
@@ -205,17 +207,19 @@ __device__ __forceinline__ double sum_rows(double x) {
 // products. Two barriers per block; all sums have a fixed order.
 // A workgroup takes its task by ticket, blocks in the chain's order, so it waits for earlier tickets
 // only: whatever part of the grid is resident, the oldest unfinished block can run. Waits are bounded
-// all the same (past the bound the value read counts).
+// all the same: past the bound a wave raises *gave_up, which ends every wait; the unset values it read
+// (NaN) go into the result, and the host reports the word.
 template <int R, bool BWD>
 __global__ void __launch_bounds__(512)
 tri_kernel(const double* __restrict__ M, int64_t n, const double* __restrict__ Dinv, const double* __restrict__ in,
            double* __restrict__ out, uint32_t* __restrict__ ticket, int64_t sL, int64_t sD, int64_t nper,
-           int64_t gpf, int64_t ngroup, const TriJob* __restrict__ jobs) {
+           int64_t gpf, int64_t ngroup, const TriJob* __restrict__ jobs, int spin_max) {
   constexpr int NW = 8, C = TB / NW;
   __shared__ double part[2][R][NW][TB];
   __shared__ uint32_t my;
   const int tid = threadIdx.x;
-  if (tid == 0) my = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  uint32_t* gave_up = ticket + 2;
+  if (tid == 0) my = __hip_atomic_fetch_add(ticket + (BWD ? 1 : 0), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   const uint32_t tk = __builtin_amdgcn_readfirstlane(my);
   const int64_t step = tk / (uint32_t)ngroup, grp = tk % (uint32_t)ngroup;
@@ -275,7 +279,7 @@ tri_kernel(const double* __restrict__ M, int64_t n, const double* __restrict__ D
   auto take = [&](double (&p)[2][C], int s) {
     const int64_t at = (BWD ? nblk - 1 - s : (int64_t)s) * TB + g * C + l16;
     uint64_t b[R];
-    for (int spins = 0; spins < SPIN_MAX; ++spins) {
+    for (int spins = 0;; ++spins) {
       bool ok = true;
 #pragma unroll
       for (int v = 0; v < R; ++v) {
@@ -283,6 +287,14 @@ tri_kernel(const double* __restrict__ M, int64_t n, const double* __restrict__ D
         ok = ok && b[v] != UNSET;
       }
       if (__ballot(ok) == ~0ull) break;
+      if (spins >= spin_max) {
+        if (lane == 0) __hip_atomic_store(gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        break;
+      }
+      if (spins >= SPIN_BUSY) {
+        if ((spins & 255) == 0 && __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
     }
 #pragma unroll
     for (int v = 0; v < R; ++v) {
@@ -416,6 +428,12 @@ hipError_t tri_inv_grouped(const TriJob* jobs_dev, int64_t njobs, int64_t nmax, 
   return hipGetLastError();
 }
 
+// DFISHER_TRI_SPIN overrides the bound on a wait's polls (0: no value that is not there at the first look is waited for).
+static int spin_max() {
+  const char* e = std::getenv("DFISHER_TRI_SPIN");
+  return e ? std::max(0, std::min(SPIN_MAX, std::atoi(e))) : SPIN_MAX;
+}
+
 // Several vectors of one factor share a workgroup's reads of the factor, four at a time.
 hipError_t tri_solve_batched(const double* L, int64_t sL, const double* Dinv, int64_t n, int64_t nvec, int64_t nper,
                              const double* b, double* z, double* y, uint32_t* ticket, hipStream_t st, bool ready) {
@@ -433,14 +451,14 @@ hipError_t tri_solve_batched(const double* L, int64_t sL, const double* Dinv, in
                        (const TriJob*)nullptr);
   const dim3 grid((unsigned)(nblk * ng));
   const TriJob* nj = nullptr;
+  const int spin = spin_max();
   for (int t = 0; t < 2; ++t) {
     const double* in = t ? z : b;
     double* out = t ? y : z;
-    uint32_t* tk = ticket + t;
-    if (R == 1 && t == 0) hipLaunchKernelGGL((tri_kernel<1, false>), grid, dim3(512), 0, st, L, n, Dinv, in, out, tk, sL, sD, nper, gpf, ng, nj);
-    if (R == 1 && t == 1) hipLaunchKernelGGL((tri_kernel<1, true>), grid, dim3(512), 0, st, L, n, Dinv, in, out, tk, sL, sD, nper, gpf, ng, nj);
-    if (R == 4 && t == 0) hipLaunchKernelGGL((tri_kernel<4, false>), grid, dim3(512), 0, st, L, n, Dinv, in, out, tk, sL, sD, nper, gpf, ng, nj);
-    if (R == 4 && t == 1) hipLaunchKernelGGL((tri_kernel<4, true>), grid, dim3(512), 0, st, L, n, Dinv, in, out, tk, sL, sD, nper, gpf, ng, nj);
+    if (R == 1 && t == 0) hipLaunchKernelGGL((tri_kernel<1, false>), grid, dim3(512), 0, st, L, n, Dinv, in, out, ticket, sL, sD, nper, gpf, ng, nj, spin);
+    if (R == 1 && t == 1) hipLaunchKernelGGL((tri_kernel<1, true>), grid, dim3(512), 0, st, L, n, Dinv, in, out, ticket, sL, sD, nper, gpf, ng, nj, spin);
+    if (R == 4 && t == 0) hipLaunchKernelGGL((tri_kernel<4, false>), grid, dim3(512), 0, st, L, n, Dinv, in, out, ticket, sL, sD, nper, gpf, ng, nj, spin);
+    if (R == 4 && t == 1) hipLaunchKernelGGL((tri_kernel<4, true>), grid, dim3(512), 0, st, L, n, Dinv, in, out, ticket, sL, sD, nper, gpf, ng, nj, spin);
   }
   return hipGetLastError();
 }
@@ -453,10 +471,11 @@ hipError_t tri_solve_grouped(const TriJob* jobs_dev, int64_t njobs, int64_t nmax
                      (double*)nullptr, (double*)nullptr, (int64_t)0, ticket, jobs_dev);
   const dim3 grid((unsigned)(nblk * njobs));
   const double* nd = nullptr;
+  const int spin = spin_max();
   hipLaunchKernelGGL((tri_kernel<1, false>), grid, dim3(512), 0, st, nd, (int64_t)0, nd, nd, (double*)nullptr, ticket,
-                     (int64_t)0, (int64_t)0, (int64_t)1, (int64_t)1, njobs, jobs_dev);
-  hipLaunchKernelGGL((tri_kernel<1, true>), grid, dim3(512), 0, st, nd, (int64_t)0, nd, nd, (double*)nullptr,
-                     ticket + 1, (int64_t)0, (int64_t)0, (int64_t)1, (int64_t)1, njobs, jobs_dev);
+                     (int64_t)0, (int64_t)0, (int64_t)1, (int64_t)1, njobs, jobs_dev, spin);
+  hipLaunchKernelGGL((tri_kernel<1, true>), grid, dim3(512), 0, st, nd, (int64_t)0, nd, nd, (double*)nullptr, ticket,
+                     (int64_t)0, (int64_t)0, (int64_t)1, (int64_t)1, njobs, jobs_dev, spin);
   return hipGetLastError();
 }
 
