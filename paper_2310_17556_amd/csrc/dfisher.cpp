@@ -19,6 +19,7 @@
 #include <string>
 
 #include "dfisher_internal.h"
+#include "workspace.h"
 
 // Scratch of dfisher_factor_solve_noalloc: one copy per device, held until the process ends. In
 // host code `scratch` only names the symbol; the device address comes from hipGetSymbolAddress
@@ -78,9 +79,7 @@ struct dfisher_ctx {
   bool timing = false;
   bool ev_used[NEV] = {};
   hipEvent_t ev[NEV] = {};
-  void* ws = nullptr;
-  size_t ws_bytes = 0;
-  bool ws_frozen = false;       // a call captured into a caller's graph holds ws: never reallocated
+  dfi::Workspace ws;
   // one device block of 8-byte slots, the first of them mirrored in pinned host memory: the triangular solves' tickets, their
   // word that a wait gave up (raised until a call reports it), the Cholesky's status, scalars ([0] diagonal max)
   uint32_t* d_tick = nullptr;   // slot 0; d_tick[2], slot 1: gave up
@@ -141,27 +140,45 @@ struct DeviceGuard {
 
 void drop_graph(dfisher_ctx* ctx);
 
-dfisher_status ensure_ws(dfisher_ctx* ctx, size_t bytes) {
-  if (bytes <= ctx->ws_bytes) return DFISHER_OK;
-  if (ctx->ws_frozen)
+struct DeviceMemory {
+  dfisher_ctx* ctx;
+  void* alloc(size_t bytes) {
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  void free(void* p) {
+    drop_graph(ctx);   // a cached graph points into it
+    (void)hipFree(p);
+  }
+  void sync() { (void)hipDeviceSynchronize(); }
+  size_t available() {
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) == hipSuccess) return free_bytes;
+    (void)hipGetLastError();
+    return 0;
+  }
+};
+
+dfisher_status no_ws(const dfisher_ctx* ctx, size_t bytes) {
+  if (ctx->ws.frozen)
     return fail(DFISHER_E_UNSUPPORTED,
                 "the context's workspace (%zu bytes) is held by a captured call and cannot grow to %zu bytes; "
-                "use another context", ctx->ws_bytes, bytes);
-  drop_graph(ctx);   // a cached graph points into the old workspace
-  if (ctx->ws) {
-    HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipFree(ctx->ws));
-    ctx->ws = nullptr;
-    ctx->ws_bytes = 0;
-  }
-  hipError_t e = hipMalloc(&ctx->ws, bytes);
-  if (e != hipSuccess) {
-    ctx->ws = nullptr;
-    (void)hipGetLastError();
-    return fail(DFISHER_E_NO_MEMORY, "workspace allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
-  }
-  ctx->ws_bytes = bytes;
-  return DFISHER_OK;
+                "use another context", ctx->ws.bytes, bytes);
+  return fail(DFISHER_E_NO_MEMORY, "workspace allocation of %zu bytes failed", bytes);
+}
+
+dfisher_status ensure_ws(dfisher_ctx* ctx, size_t bytes) {
+  DeviceMemory mem{ctx};
+  return dfi::ws_need(ctx->ws, bytes, mem) ? DFISHER_OK : no_ws(ctx, bytes);
+}
+
+// A workspace for the first layout that there is the memory for (see ws_levels).
+template <class F>
+dfisher_status ensure_levels(dfisher_ctx* ctx, int levels, F need) {
+  DeviceMemory mem{ctx};
+  return dfi::ws_levels(ctx->ws, levels, true, need, mem) ? DFISHER_OK : no_ws(ctx, need(levels - 1));
 }
 
 // Carves aligned sub-buffers out of one workspace block.
@@ -311,8 +328,8 @@ std::tuple<int, int64_t, int, int> tune_key(int prec, int64_t n, int64_t m, bool
 }
 
 // The Gram plan for a shape: the tuned split-K factor / split mode of its size class if the
-// context has one, else the built-in choice. planes = false: rows that are not 16-byte aligned are split
-// inside the tile kernel (see ensure_gram_ws).
+// context has one, else the built-in choice. With little memory: planes = false, rows that are not 16-byte aligned are
+// split inside the tile kernel.
 dfi::GramPlan make_gram_plan(const dfisher_ctx* ctx, const float* S, int64_t n, int64_t m, int64_t lds, int prec,
                              bool planes = true) {
   const bool al = rows_aligned16(S, lds);
@@ -323,14 +340,14 @@ dfi::GramPlan make_gram_plan(const dfisher_ctx* ctx, const float* S, int64_t n, 
   return dfi::gram_plan(n, m, lds, prec, al, 0, in_kernel ? 0 : -1);
 }
 
-// The workspace of a call, need() bytes under its Gram plan gp. Rows that are not 16-byte aligned do not depend on
-// the memory for their split-BF16 planes (as much as S takes): without it the tile kernel splits them itself.
+// The workspace of a call, need() bytes under its Gram plan gp. It does not depend on the memory for the split-BF16 planes of
+// rows that are not 16-byte aligned (as much as S takes): without it the tile kernel splits them itself.
 template <class F>
 dfisher_status ensure_gram_ws(dfisher_ctx* ctx, const float* S, dfi::GramPlan& gp, F need) {
-  const dfisher_status s = ensure_ws(ctx, need());
-  if (s == DFISHER_OK || gp.ldh == 0 || rows_aligned16(S, gp.lds)) return s;
-  gp = make_gram_plan(ctx, S, gp.n, gp.m, gp.lds, gp.prec, false);
-  return ensure_ws(ctx, need());
+  return ensure_levels(ctx, 2, [&](int l) {
+    gp = make_gram_plan(ctx, S, gp.n, gp.m, gp.lds, gp.prec, l < 1);
+    return need();
+  });
 }
 
 // Scratch of the one-launch Cholesky for nbatch matrices: the packed factors and the ticket.
@@ -887,7 +904,6 @@ dfisher_status tune_gram(dfisher_ctx* ctx, const float* S, int64_t n, int64_t m,
   int nq = 0;
   dfi::gram_q_candidates(n, m, TUNE_MAX_PART_BYTES, qs, &nq, 16);
   std::vector<int> modes = {-1};
-  if (prec == DFISHER_GRAM_BF16X3) modes = {1, 0};
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   auto most = [&]() {
@@ -899,8 +915,10 @@ dfisher_status tune_gram(dfisher_ctx* ctx, const float* S, int64_t n, int64_t m,
       }
     return need;
   };
-  if (!al && modes.size() > 1 && ensure_ws(ctx, most()) != DFISHER_OK) modes = {0};   // see ensure_gram_ws
-  DF_TRY(ensure_ws(ctx, most()));
+  DF_TRY(ensure_levels(ctx, !al && prec == DFISHER_GRAM_BF16X3 ? 2 : 1, [&](int l) {   // see ensure_gram_ws
+    if (prec == DFISHER_GRAM_BF16X3) modes = l == 0 ? std::vector<int>{1, 0} : std::vector<int>{0};
+    return most();
+  }));
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     (void)hipGetLastError();
@@ -913,7 +931,7 @@ dfisher_status tune_gram(dfisher_ctx* ctx, const float* S, int64_t n, int64_t m,
   for (int mode : modes) {
     for (int i = 0; i < nq && rs == DFISHER_OK; ++i) {
       const dfi::GramPlan gp = dfi::gram_plan(n, m, lds, prec, al, qs[i], mode);
-      const SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, false, false);
+      const SolveBufs B = carve(static_cast<char*>(ctx->ws.ptr), n, m, &gp, rp, cp, false, false);
       float tmin = 0.f;
       for (int rep = 0; rep < 3 && rs == DFISHER_OK; ++rep) {
         if (hipEventRecord(e0, st) != hipSuccess) rs = fail(DFISHER_E_DEVICE, "event record failed");
@@ -1416,17 +1434,14 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   UnevenLayout U;
   const int need_t = (max_sw > 0 || o.final_resid) ? 1 : 0;
   const bool want_f8 = o.sweeps != 0 && !o.final_resid && (o.flags & DFISHER_EXACT_APPLY) == 0;
-  uneven_layout(ctx, nullptr, np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
-  if (ensure_ws(ctx, U.bytes) != DFISHER_OK) {   // no room for the packed copies: the factorisations run in place
-    U.packed = false;
+  // without the memory the factorisations run in place, then rows that are not 16-byte aligned go without planes
+  DF_TRY(ensure_levels(ctx, 3, [&](int l) {
+    U.packed = l < 1;
+    U.planes = l < 2;
     uneven_layout(ctx, nullptr, np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
-    if (ensure_ws(ctx, U.bytes) != DFISHER_OK) {   // nor for planes of rows that are not 16-byte aligned
-      U.planes = false;
-      uneven_layout(ctx, nullptr, np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
-      DF_TRY(ensure_ws(ctx, U.bytes));
-    }
-  }
-  uneven_layout(ctx, static_cast<char*>(ctx->ws), np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
+    return U.bytes;
+  }));
+  uneven_layout(ctx, static_cast<char*>(ctx->ws.ptr), np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
   // largest problems first (their Gram kernels fill the device; small ones follow)
   std::vector<int32_t> order((size_t)np);
   for (int32_t p = 0; p < np; ++p) order[(size_t)p] = p;
@@ -1632,7 +1647,7 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   put(lambda, sizeof(double) * (size_t)np);
   put(x, sizeof(void*) * (size_t)np);
   put(&o, sizeof(o));
-  put(&ctx->ws, sizeof(void*));
+  put(&ctx->ws.ptr, sizeof(void*));
   put(&ctx->tbuf, sizeof(void*));
   // the layout moves with the Gram plans (a tuning change alters a problem's partial-tile bytes
   // and with them every later offset), so the plans and the layout size are part of the key
@@ -1850,7 +1865,7 @@ dfisher_status dfisher_ctx_destroy(dfisher_ctx* ctx) {
   drop_graph(ctx);
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
   if (ctx->tbuf) (void)hipFree(ctx->tbuf);
-  if (ctx->ws) (void)hipFree(ctx->ws);
+  if (ctx->ws.ptr) (void)hipFree(ctx->ws.ptr);
   for (int i = 0; i < NEV; ++i)
     if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
   if (ctx->d_tick) (void)hipFree(ctx->d_tick);
@@ -1920,8 +1935,11 @@ dfisher_status dfisher_gram(dfisher_ctx* ctx, const float* S, int64_t n, int64_t
   dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
-  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return carve(nullptr, n, m, &gp, rp, cp, false, false).bytes; }));
-  SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, false, false);
+  auto lay = [&](char* base) {
+    return carve(base, n, m, &gp, rp, cp, false, false);
+  };
+  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
+  SolveBufs B = lay(static_cast<char*>(ctx->ws.ptr));
   StageClock clk(ctx, st);
   DF_TRY(gram_stage(S, nullptr, gp, rp, B, lambda, W, 1, st, &clk));
   clk.mark(3);
@@ -1939,7 +1957,7 @@ dfisher_status dfisher_quantize_mxfp8(dfisher_ctx* ctx, const float* S, int64_t 
   hipStream_t st = as_stream(stream);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   DF_TRY(ensure_ws(ctx, align_up(rp.part_bytes)));
-  HIP_TRY(dfi::rowpass_launch(rp, S, nullptr, nullptr, false, true, static_cast<double*>(ctx->ws), st, codes, scales,
+  HIP_TRY(dfi::rowpass_launch(rp, S, nullptr, nullptr, false, true, static_cast<double*>(ctx->ws.ptr), st, codes, scales,
                               ldq));
   return DFISHER_OK;
 }
@@ -1953,12 +1971,13 @@ dfisher_status dfisher_potrf(dfisher_ctx* ctx, double* W, int64_t n, int64_t* in
   DeviceGuard g(ctx->device);
   hipStream_t st = as_stream(stream);
   const size_t dkk_bytes = align_up(dfi::POTRF_DKK_BYTES);
-  double* pack = nullptr;
-  if (ensure_ws(ctx, dkk_bytes + chol_scratch_bytes(n, 1)) == DFISHER_OK)
-    pack = reinterpret_cast<double*>(static_cast<char*>(ctx->ws) + dkk_bytes);
-  else   // no room for the packed copy: in place
-    DF_TRY(ensure_ws(ctx, dkk_bytes));
-  HIP_TRY(factor_launch(W, n, 1, n * n, ctx->d_info, ctx->d_flag, static_cast<double*>(ctx->ws), pack, st));
+  bool packed = true;   // in place without the memory
+  DF_TRY(ensure_levels(ctx, 2, [&](int l) {
+    packed = l == 0;
+    return dkk_bytes + (packed ? chol_scratch_bytes(n, 1) : 0);
+  }));
+  double* pack = packed ? reinterpret_cast<double*>(static_cast<char*>(ctx->ws.ptr) + dkk_bytes) : nullptr;
+  HIP_TRY(factor_launch(W, n, 1, n * n, ctx->d_info, ctx->d_flag, static_cast<double*>(ctx->ws.ptr), pack, st));
   HIP_TRY(hipMemcpyAsync(ctx->h_status, ctx->d_info, sizeof(int64_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   *info = ctx->h_status[0];
@@ -1980,7 +1999,7 @@ dfisher_status dfisher_gemv(dfisher_ctx* ctx, const float* S, int64_t n, int64_t
   hipStream_t st = as_stream(stream);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   DF_TRY(ensure_ws(ctx, align_up(rp.part_bytes)));
-  double* rpart = static_cast<double*>(ctx->ws);
+  double* rpart = static_cast<double*>(ctx->ws.ptr);
   HIP_TRY(dfi::rowpass_launch(rp, S, v, nullptr, true, false, rpart, st));
   HIP_TRY(dfi::rowpass_reduce(rp, rpart, true, false, b, nullptr, nullptr, nullptr, 0.0, st));
   return DFISHER_OK;
@@ -1999,7 +2018,7 @@ dfisher_status dfisher_trsv(dfisher_ctx* ctx, const double* L, int64_t n, int32_
   double* work = c.take<double>((size_t)n);
   DF_TRY(ensure_ws(ctx, c.off));
   c = Carver{};
-  c.base = static_cast<char*>(ctx->ws);
+  c.base = static_cast<char*>(ctx->ws.ptr);
   Dinv = c.take<double>(dfi::trsv_dinv_bytes(n) / sizeof(double));
   work = c.take<double>((size_t)n);
   HIP_TRY(dfi::trsv_diag_inv(L, n, Dinv, st));
@@ -2017,7 +2036,7 @@ dfisher_status dfisher_apply(dfisher_ctx* ctx, const float* S, int64_t n, int64_
   DeviceGuard g(ctx->device);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   DF_TRY(ensure_ws(ctx, align_up(cp.part_bytes + 8)));
-  HIP_TRY(dfi::colpass_launch(cp, S, n, m, lds, y, v, lambda, x, x_fp64 ? 1 : 0, static_cast<double*>(ctx->ws),
+  HIP_TRY(dfi::colpass_launch(cp, S, n, m, lds, y, v, lambda, x, x_fp64 ? 1 : 0, static_cast<double*>(ctx->ws.ptr),
                               as_stream(stream)));
   return DFISHER_OK;
 }
@@ -2041,8 +2060,11 @@ dfisher_status dfisher_factor_create(dfisher_ctx* ctx, const float* S, int64_t n
   dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
-  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return carve(nullptr, n, m, &gp, rp, cp, false, false).bytes; }));
-  SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, false, false);
+  auto lay = [&](char* base) {
+    return carve(base, n, m, &gp, rp, cp, false, false);
+  };
+  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
+  SolveBufs B = lay(static_cast<char*>(ctx->ws.ptr));
   dfisher_factor* f = new dfisher_factor();
   f->ctx = ctx;
   f->S = S;
@@ -2100,56 +2122,58 @@ dfisher_status dfisher_factor_solve(dfisher_factor* f, const float* V, int64_t n
   const int64_t n = f->n, m = f->m;
   if (nrhs > 65535) return fail(DFISHER_E_UNSUPPORTED, "nrhs = %lld > 65535", (long long)nrhs);
   const int sweeps = f->opt.sweeps;
-  auto answer = [&]() {
-    if (!info) return;
+  // One right-hand side: the single-vector passes of dfisher_solve, whose refinement reads S once a sweep and whose
+  // other passes run at the rate of reading S (2048 x 200000, two sweeps: 1480 us, through the multi-vector passes
+  // 2290; two right-hand sides one after the other would take 2960). Without the memory the multi-vector passes, which
+  // take two groups of vectors at a time instead of four.
+  const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, f->lds);
+  const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
+  const dfi::RefinePassPlan fp = dfi::refine_pass_plan(n, m, f->lds, f->S);
+  const bool need_t = sweeps > 0 && !fp.usable;
+  const dfi::RowMultiPlan rm = dfi::rowmulti_plan(n, m, f->lds);
+  bool single = nrhs == 1;
+  int most = dfi::MULTI_GROUPS;
+  SolveBufs B;
+  MultiBufs mb;
+  auto lay = [&](char* base) {
+    if (single) {
+      B = carve(base, n, m, nullptr, rp, cp, false, need_t, &fp);
+      return B.bytes;
+    }
+    Carver c;
+    c.base = base;
+    mb = carve_multi(c, n, m, nrhs, nrhs, rm, sweeps > 0, false, false, 1, most);
+    return c.off;
+  };
+  DF_TRY(ensure_levels(ctx, 2, [&](int l) {
+    single = nrhs == 1 && l == 0;
+    most = l == 0 ? dfi::MULTI_GROUPS : 2;
+    return lay(nullptr);
+  }));
+  lay(static_cast<char*>(ctx->ws.ptr));
+  if (single) {
+    B.tick = ctx->d_tick;
+    HIP_TRY(dfi::rowpass_launch(rp, f->S, V, nullptr, true, false, B.rpart, st));
+    HIP_TRY(dfi::rowpass_reduce(rp, B.rpart, true, false, B.b, nullptr, nullptr, nullptr, 0.0, st));
+    bool deferred = false;
+    DF_TRY(solve_y(f->S, n, m, f->lds, f->lambda, f->L, f->Dinv, B, rp, cp, sweeps, st, nullptr, &fp, ctx, 0.0, nullptr,
+                   nullptr, true, 0.0, nullptr, nullptr, &deferred));
+    HIP_TRY(dfi::colpass_launch(cp, f->S, n, m, f->lds, B.y, V, f->lambda, X, f->opt.x_fp64, B.cpart, st, nullptr,
+                                deferred ? B.zc : nullptr));
+  } else {
+    mb.ticket = ctx->d_tick;
+    const double lam = f->lambda;
+    DF_TRY(multi_solve(f->S, n, m, f->lds, 1, f->L, f->Dinv, &lam, V, nrhs, ldv, X, ldx, f->opt.x_fp64, sweeps, rm, mb,
+                       st));
+  }
+  if (info) {
     info->potrf_info = 0;
     info->shift = f->shift;
     info->attempts = 0;
     info->sweeps_done = sweeps;
     info->resid = -1.0;
     info->w_resid = -1.0;
-  };
-  // One right-hand side: the single-vector passes of dfisher_solve, whose refinement reads S once a sweep and whose
-  // other passes run at the rate of reading S (2048 x 200000, two sweeps: 1480 us, through the multi-vector passes
-  // 2290; two right-hand sides one after the other would take 2960).
-  if (nrhs == 1) {
-    const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, f->lds);
-    const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
-    const dfi::RefinePassPlan fp = dfi::refine_pass_plan(n, m, f->lds, f->S);
-    const bool need_t = sweeps > 0 && !fp.usable;
-    if (ensure_ws(ctx, carve(nullptr, n, m, nullptr, rp, cp, false, need_t, &fp).bytes) == DFISHER_OK) {
-      SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, nullptr, rp, cp, false, need_t, &fp);
-      B.tick = ctx->d_tick;
-      HIP_TRY(dfi::rowpass_launch(rp, f->S, V, nullptr, true, false, B.rpart, st));
-      HIP_TRY(dfi::rowpass_reduce(rp, B.rpart, true, false, B.b, nullptr, nullptr, nullptr, 0.0, st));
-      bool deferred = false;
-      DF_TRY(solve_y(f->S, n, m, f->lds, f->lambda, f->L, f->Dinv, B, rp, cp, sweeps, st, nullptr, &fp, ctx, 0.0, nullptr,
-                     nullptr, true, 0.0, nullptr, nullptr, &deferred));
-      HIP_TRY(dfi::colpass_launch(cp, f->S, n, m, f->lds, B.y, V, f->lambda, X, f->opt.x_fp64, B.cpart, st, nullptr,
-                                  deferred ? B.zc : nullptr));
-      answer();
-      return DFISHER_OK;
-    }
   }
-  const dfi::RowMultiPlan rm = dfi::rowmulti_plan(n, m, f->lds);
-  int most = dfi::MULTI_GROUPS;
-  MultiBufs mb;
-  auto lay = [&](char* base) {
-    Carver c;
-    c.base = base;
-    mb = carve_multi(c, n, m, nrhs, nrhs, rm, f->opt.sweeps > 0, false, false, 1, most);
-    return c.off;
-  };
-  if (ensure_ws(ctx, lay(nullptr)) != DFISHER_OK) {   // without the memory, two groups of vectors a pass
-    most = 2;
-    DF_TRY(ensure_ws(ctx, lay(nullptr)));
-  }
-  lay(static_cast<char*>(ctx->ws));
-  mb.ticket = ctx->d_tick;
-  const double lam = f->lambda;
-  DF_TRY(multi_solve(f->S, n, m, f->lds, 1, f->L, f->Dinv, &lam, V, nrhs, ldv, X, ldx, f->opt.x_fp64, f->opt.sweeps, rm,
-                     mb, st));
-  answer();
   return DFISHER_OK;
 }
 
@@ -2257,7 +2281,7 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
     return carve(base, n, m, &gp, rp, cp, true, need_t, &fp, final8, is_centered(o));
   };
   DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
-  SolveBufs B = lay(static_cast<char*>(ctx->ws));
+  SolveBufs B = lay(static_cast<char*>(ctx->ws.ptr));
   B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
   // one pass over S (b = S v, the exact diagonal |s_i|^2, the FP8 codes if used), then step 1
@@ -2338,8 +2362,11 @@ dfisher_status dfisher_solve_rowspace(dfisher_ctx* ctx, const float* S, int64_t 
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   const dfi::RefinePassPlan fp = dfi::refine_pass_plan(n, m, lds, S);
   const bool need_t = (o.sweeps != 0 || o.final_resid) && !fp.usable;
-  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return carve(nullptr, n, m, &gp, rp, cp, true, need_t, &fp).bytes; }));
-  SolveBufs B = carve(static_cast<char*>(ctx->ws), n, m, &gp, rp, cp, true, need_t, &fp);
+  auto lay = [&](char* base) {
+    return carve(base, n, m, &gp, rp, cp, true, need_t, &fp);
+  };
+  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
+  SolveBufs B = lay(static_cast<char*>(ctx->ws.ptr));
   B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
   // one pass over S for the exact diagonal (and the FP8 codes), then step 1; b = f
@@ -2414,7 +2441,7 @@ dfisher_status dfisher_sr_center(dfisher_ctx* ctx, const float* O, int64_t n, in
   };
   double *ones, *t, *cpart;
   DF_TRY(ensure_ws(ctx, lay(nullptr, &ones, &t, &cpart)));
-  lay(static_cast<char*>(ctx->ws), &ones, &t, &cpart);
+  lay(static_cast<char*>(ctx->ws.ptr), &ones, &t, &cpart);
   HIP_TRY(dfi::fill_value(ones, n, 1.0, st));
   HIP_TRY(dfi::colpass_launch(cp, O, n, mc, ldc, ones, nullptr, 1.0, t, 2, cpart, st));
   HIP_TRY(dfi::center_write(O, n, m, ldo, is_complex, t, S, lds, st));
@@ -2452,7 +2479,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
     float* vp;
   };
   auto lay = [&](char* base, SolveBufs& B, Extra& X) -> size_t {
-    B = carve(base, N, m, &gp, rp, cp, true, false, nullptr);
+    B = carve(base, N, m, &gp, rp, cp, true, false);
     Carver c;
     c.base = base;
     c.off = B.bytes;
@@ -2470,7 +2497,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
   SolveBufs B;
   Extra X;
   DF_TRY(ensure_gram_ws(ctx, Z, gp, [&] { return lay(nullptr, B, X); }));
-  lay(static_cast<char*>(ctx->ws), B, X);
+  lay(static_cast<char*>(ctx->ws.ptr), B, X);
   B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
   // Z Z^T (both triangles, exact FP64 diagonal) and the embedded W
@@ -2619,31 +2646,27 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   int64_t* dinfo;
   int32_t* dflag;
   MultiBufs mb;
-  size_t need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
-  // without the memory (or, in a capture, the workspace of the call before it) for the packed copies the
-  // factorisations run in place
-  auto no_room = [&]() { return capturing ? need > ctx->ws_bytes : ensure_ws(ctx, need) != DFISHER_OK; };
-  if (no_room()) {   // two groups of vectors a pass
-    most = 2;
-    need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
-  }
-  if (most == 2 && no_room()) {
-    packed = false;
-    need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
-  }
-  if (!packed && gp.ldh > 0 && !rows_aligned16(S, lds) && no_room()) {   // and the planes (see ensure_gram_ws)
-    gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec, false);
-    need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
-  }
+  // without the memory (or, in a capture, the workspace of the call before it): two groups of vectors a pass, then the
+  // factorisations in place, then no planes (see ensure_gram_ws)
+  size_t need = 0;
+  const int levels = 4;
+  auto level = [&](int l) {
+    most = l < 1 ? dfi::MULTI_GROUPS : 2;
+    packed = l < 2;
+    gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec, l < 3);
+    return need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
+  };
   if (capturing) {   // no allocation inside a capture; the graph will hold the workspace's addresses
-    if (need > ctx->ws_bytes)
+    DeviceMemory mem{ctx};
+    if (!dfi::ws_levels(ctx->ws, levels, false, level, mem))
       return fail(DFISHER_E_UNSUPPORTED,
                   "the workspace must grow to %zu bytes, which cannot happen during a capture: make the same call "
                   "once outside the capture first", need);
-    ctx->ws_frozen = true;
+    ctx->ws.frozen = true;
+  } else {
+    DF_TRY(ensure_levels(ctx, levels, level));
   }
-  DF_TRY(ensure_ws(ctx, need));
-  layout(static_cast<char*>(ctx->ws), B, Lall, Dall, dkk, dinfo, dflag, mb);
+  layout(static_cast<char*>(ctx->ws.ptr), B, Lall, Dall, dkk, dinfo, dflag, mb);
   mb.ticket = ctx->d_tick;
 
   // the shared Gram G = S S^T (exact diagonal, no lambda), formed once

@@ -13,3 +13,56 @@ extern "C" __attribute__((visibility("default"))) void rules_gram_plan(int64_t n
   *nslice = p.nslice;
   *kslice = p.kslice;
 }
+
+#include "workspace.h"
+
+// A device of `capacity` bytes that counts what it is asked for.
+struct FakeMemory {
+  size_t capacity, used = 0;
+  std::vector<std::pair<void*, size_t>> blocks;
+  int64_t allocs = 0, refusals = 0, frees = 0, syncs = 0;
+  uintptr_t next = 0x1000;
+  void* alloc(size_t b) {
+    if (used + b > capacity) {
+      ++refusals;
+      return nullptr;
+    }
+    ++allocs;
+    used += b;
+    blocks.push_back({reinterpret_cast<void*>(next += 0x1000), b});
+    return blocks.back().first;
+  }
+  void free(void* p) {
+    ++frees;
+    for (auto& b : blocks)
+      if (b.first == p) {
+        used -= b.second;
+        b.second = 0;
+      }
+  }
+  void sync() { ++syncs; }
+  size_t available() { return capacity - used; }
+};
+struct FakeContext {
+  FakeMemory mem;
+  dfi::Workspace ws;
+};
+
+#define RULES extern "C" __attribute__((visibility("default")))
+RULES FakeContext* rules_ws_new(size_t capacity) { return new FakeContext{FakeMemory{capacity}, {}}; }
+RULES void rules_ws_set(FakeContext* c, size_t capacity, int frozen) {
+  c->mem.capacity = capacity;
+  c->ws.frozen = frozen != 0;
+}
+// the level taken, -1: none
+RULES int rules_ws_levels(FakeContext* c, const size_t* need, int levels, int can_grow) {
+  int at = -1;
+  const bool ok = dfi::ws_levels(c->ws, levels, can_grow != 0, [&](int l) { return need[at = l]; }, c->mem);
+  return ok && need[at] <= c->ws.bytes ? at : -1;
+}
+// bytes held, allocations, refusals, frees, synchronisations
+RULES void rules_ws_counts(FakeContext* c, int64_t* out) {
+  const int64_t v[5] = {(int64_t)c->ws.bytes, c->mem.allocs, c->mem.refusals, c->mem.frees, c->mem.syncs};
+  for (int i = 0; i < 5; ++i) out[i] = v[i];
+}
+RULES void rules_ws_delete(FakeContext* c) { delete c; }

@@ -1,4 +1,4 @@
-"""Rules that the host applies for the kernels, on the CPU: where a buffer over rows of S ends."""
+"""Rules that the host applies for the kernels and its launches, on the CPU."""
 import ctypes
 import os
 import shutil
@@ -86,3 +86,72 @@ def test_gram_slices_are_no_longer_than_the_base_plans(rules, prec, aligned):
             most = max(1, ((cap + b - 1) // b + step - 1) // step) * step
             assert ks.value <= most, (n, m, ns.value, ks.value, b, most)
             assert ns.value * ks.value >= cap and ks.value % step == 0
+
+
+class Fake:
+    """A context's workspace on a device of `capacity` bytes."""
+
+    def __init__(self, rules, capacity):
+        self.r = rules
+        rules.rules_ws_new.restype = ctypes.c_void_p
+        rules.rules_ws_new.argtypes = [ctypes.c_size_t]
+        rules.rules_ws_set.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+        rules.rules_ws_levels.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t), ctypes.c_int, ctypes.c_int]
+        rules.rules_ws_counts.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_int64)]
+        rules.rules_ws_delete.argtypes = [ctypes.c_void_p]
+        self.h = rules.rules_ws_new(capacity)
+
+    def set(self, capacity, frozen=False):
+        self.r.rules_ws_set(self.h, capacity, frozen)
+
+    def levels(self, *need, can_grow=True):
+        return self.r.rules_ws_levels(self.h, (ctypes.c_size_t * len(need))(*need), len(need), can_grow)
+
+    def counts(self):
+        out = (ctypes.c_int64 * 5)()
+        self.r.rules_ws_counts(self.h, out)
+        return list(out)
+
+    def __del__(self):
+        self.r.rules_ws_delete(self.h)
+
+
+def test_workspace_at_the_limit_costs_one_attempt(rules):
+    """A preferred layout that does not fit is tried once: later calls neither allocate, free nor synchronise."""
+    f = Fake(rules, 50)
+    assert f.levels(60, 45, 40) == 1
+    assert f.levels(70, 55, 45) == 2   # 55 may fit where 60 did not
+    held = f.counts()
+    assert held[0] == 45
+    for _ in range(5):
+        assert f.levels(60, 45, 40) == 1
+        assert f.levels(70, 55, 45) == 2
+    assert f.counts() == held
+    f.set(130)   # the program gave memory back
+    assert f.levels(60, 45, 40) == 0
+
+
+def test_workspace_stays_when_the_smaller_layout_has_room(rules):
+    f = Fake(rules, 90)
+    assert f.levels(50) == 0
+    assert f.levels(95, 45) == 1
+    assert f.counts()[0] == 50 and f.counts()[3] == 0   # (and with it a captured sequence of launches)
+
+
+def test_workspace_grows_in_place(rules):
+    f = Fake(rules, 100)
+    assert f.levels(50) == 0
+    assert f.levels(80, 40) == 0        # beside it there is no room
+    assert f.levels(101, 100) == 1      # the last resort has to grow too
+    assert f.levels(101, 101) == -1
+
+
+def test_workspace_held_by_a_capture(rules):
+    f = Fake(rules, 1000)
+    assert f.levels(50) == 0
+    f.set(1000, frozen=True)
+    assert f.levels(60, 50, 40) == 1 and f.levels(70, 60) == -1
+    assert f.counts()[1] == 1 and f.counts()[0] == 50
+    f.set(1000)
+    assert f.levels(60, 50, 40, can_grow=False) == 1 and f.levels(70, 60, can_grow=False) == -1
+    assert f.counts()[1] == 1
