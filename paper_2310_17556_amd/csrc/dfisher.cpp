@@ -80,6 +80,7 @@ struct dfisher_ctx {
   bool ev_used[NEV] = {};
   hipEvent_t ev[NEV] = {};
   dfi::Workspace ws;
+  bool held_lean = false;       // a captured call took its smallest layout
   // one device block of 8-byte slots, the first of them mirrored in pinned host memory: the triangular solves' tickets, their
   // word that a wait gave up (raised until a call reports it), the Cholesky's status, scalars ([0] diagonal max)
   uint32_t* d_tick = nullptr;   // slot 0; d_tick[2], slot 1: gave up
@@ -329,23 +330,25 @@ std::tuple<int, int64_t, int, int> tune_key(int prec, int64_t n, int64_t m, bool
 
 // The Gram plan for a shape: the tuned split-K factor / split mode of its size class if the
 // context has one, else the built-in choice. With little memory: planes = false, rows that are not 16-byte aligned are
-// split inside the tile kernel.
+// split inside the tile kernel; lean, no more slices than the base plan has.
 dfi::GramPlan make_gram_plan(const dfisher_ctx* ctx, const float* S, int64_t n, int64_t m, int64_t lds, int prec,
-                             bool planes = true) {
+                             bool planes = true, bool lean = false) {
   const bool al = rows_aligned16(S, lds);
   const bool in_kernel = !al && !planes;
   auto it = ctx->tune.find(tune_key(prec, n, m, al));
   if (it != ctx->tune.end())
     return dfi::gram_plan(n, m, lds, prec, al, it->second.first, in_kernel ? 0 : it->second.second);
-  return dfi::gram_plan(n, m, lds, prec, al, 0, in_kernel ? 0 : -1);
+  return dfi::gram_plan(n, m, lds, prec, al, lean ? -1 : 0, in_kernel ? 0 : -1);
 }
 
 // The workspace of a call, need() bytes under its Gram plan gp. It does not depend on the memory for the split-BF16 planes of
-// rows that are not 16-byte aligned (as much as S takes): without it the tile kernel splits them itself.
+// rows that are not 16-byte aligned (as much as S takes: the tile kernel splits them itself), for more Gram slices than
+// the base plan has, or for a packed factor outside the partial tiles (own_pack false: the Cholesky runs in place).
 template <class F>
-dfisher_status ensure_gram_ws(dfisher_ctx* ctx, const float* S, dfi::GramPlan& gp, F need) {
-  return ensure_levels(ctx, 2, [&](int l) {
-    gp = make_gram_plan(ctx, S, gp.n, gp.m, gp.lds, gp.prec, l < 1);
+dfisher_status ensure_gram_ws(dfisher_ctx* ctx, const float* S, dfi::GramPlan& gp, bool& own_pack, F need) {
+  return ensure_levels(ctx, 3, [&](int l) {
+    gp = make_gram_plan(ctx, S, gp.n, gp.m, gp.lds, gp.prec, l < 1, l >= 2);
+    own_pack = l < 2;
     return need();
   });
 }
@@ -399,7 +402,8 @@ struct SolveBufs {
   double* t;       // S^T y (m, FP64)
   double* Dinv;    // inverses of L's 128 x 128 diagonal blocks
   double* dkk;     // Cholesky scratch: current diagonal block inverse
-  double* pack;    // Cholesky scratch: the packed factor, then its ticket (in the Gram partials, free by then)
+  double* pack;    // Cholesky scratch: the packed factor, then its ticket (in the Gram partials, free by then); null:
+                   // factored in place
   uint32_t* tick;  // the triangular solves' tickets (the context's)
   uint8_t* q8;     // scaled-FP8 codes of S (n x ldq), when the Gram is MXFP8
   uint8_t* sc8;    // their E8M0 scales (n x ldq/32)
@@ -419,7 +423,7 @@ struct SolveBufs {
 
 SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const dfi::RowPassPlan& rp,
                 const dfi::ColPassPlan& cp, bool need_L, bool need_t, const dfi::RefinePassPlan* fp = nullptr,
-                bool final8 = false, bool final8_cs = false) {
+                bool final8 = false, bool final8_cs = false, bool own_pack = true) {
   Carver c;
   c.base = base;
   SolveBufs s{};
@@ -443,7 +447,8 @@ SolveBufs carve(char* base, int64_t n, int64_t m, const dfi::GramPlan* gp, const
   // (8 slices or more of partial tiles always hold the packed factor's half matrix)
   s.pack = !need_L && !s.W ? nullptr
            : gp && gp->part_bytes >= chol_scratch_bytes(n, 1)
-               ? reinterpret_cast<double*>(s.gpart) : c.take<double>(chol_scratch_bytes(n, 1) / sizeof(double));
+               ? reinterpret_cast<double*>(s.gpart)
+           : own_pack ? c.take<double>(chol_scratch_bytes(n, 1) / sizeof(double)) : nullptr;
   s.ldq = dfi::fp8_ldq(m);
   const bool fp8 = gp && gp->prec == DFISHER_GRAM_MXFP8;
   s.q8 = fp8 ? c.take<uint8_t>((size_t)(n * s.ldq)) : nullptr;
@@ -1009,6 +1014,7 @@ struct UnevenLayout {
   double *W = nullptr, *Dinv = nullptr, *dkk = nullptr, *dmax = nullptr;
   bool packed = true;                      // room for the factors' packed copies (the one-launch Cholesky)
   bool planes = true;                      // room for the split-BF16 planes of rows that are not 16-byte aligned
+  bool lean = false;                       // Gram plans with as few slices as the base plan's (see make_gram_plan)
   std::vector<int64_t> poff;               // doubles
   double* pack = nullptr;
   uint32_t* ticket = nullptr;
@@ -1064,7 +1070,7 @@ void uneven_layout(const dfisher_ctx* ctx, char* base, int32_t np, const float* 
   int64_t wtot = 0, dtot = 0;
   size_t gpart = 0, rpart = 0, cpart = 0, q8 = 0, sc8 = 0, planes = 0;
   for (int32_t p = 0; p < np; ++p) {
-    U.gp.push_back(make_gram_plan(ctx, S[p], n[p], m[p], lds[p], prec, U.planes));
+    U.gp.push_back(make_gram_plan(ctx, S[p], n[p], m[p], lds[p], prec, U.planes, U.lean));
     U.rp.push_back(dfi::rowpass_plan(n[p], m[p], lds[p]));
     U.cp.push_back(dfi::colpass_plan(n[p], m[p]));
     U.fp.push_back(dfi::refine_pass_plan(n[p], m[p], lds[p], S[p]));
@@ -1434,10 +1440,12 @@ dfisher_status uneven_solve(dfisher_ctx* ctx, int32_t np, const float* const* S,
   UnevenLayout U;
   const int need_t = (max_sw > 0 || o.final_resid) ? 1 : 0;
   const bool want_f8 = o.sweeps != 0 && !o.final_resid && (o.flags & DFISHER_EXACT_APPLY) == 0;
-  // without the memory the factorisations run in place, then rows that are not 16-byte aligned go without planes
-  DF_TRY(ensure_levels(ctx, 3, [&](int l) {
+  // without the memory the factorisations run in place, then rows that are not 16-byte aligned go without planes, then the
+  // Gram takes its base plans
+  DF_TRY(ensure_levels(ctx, 4, [&](int l) {
     U.packed = l < 1;
     U.planes = l < 2;
+    U.lean = l >= 3;
     uneven_layout(ctx, nullptr, np, S, n, m, lds, o.gram_prec, need_t, U, want_f8, is_centered(o));
     return U.bytes;
   }));
@@ -1935,10 +1943,11 @@ dfisher_status dfisher_gram(dfisher_ctx* ctx, const float* S, int64_t n, int64_t
   dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
+  bool own_pack = true;
   auto lay = [&](char* base) {
-    return carve(base, n, m, &gp, rp, cp, false, false);
+    return carve(base, n, m, &gp, rp, cp, false, false, nullptr, false, false, own_pack);
   };
-  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
+  DF_TRY(ensure_gram_ws(ctx, S, gp, own_pack, [&] { return lay(nullptr).bytes; }));
   SolveBufs B = lay(static_cast<char*>(ctx->ws.ptr));
   StageClock clk(ctx, st);
   DF_TRY(gram_stage(S, nullptr, gp, rp, B, lambda, W, 1, st, &clk));
@@ -2060,10 +2069,11 @@ dfisher_status dfisher_factor_create(dfisher_ctx* ctx, const float* S, int64_t n
   dfi::GramPlan gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec);
   const dfi::RowPassPlan rp = dfi::rowpass_plan(n, m, lds);
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
+  bool own_pack = true;
   auto lay = [&](char* base) {
-    return carve(base, n, m, &gp, rp, cp, false, false);
+    return carve(base, n, m, &gp, rp, cp, false, false, nullptr, false, false, own_pack);
   };
-  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
+  DF_TRY(ensure_gram_ws(ctx, S, gp, own_pack, [&] { return lay(nullptr).bytes; }));
   SolveBufs B = lay(static_cast<char*>(ctx->ws.ptr));
   dfisher_factor* f = new dfisher_factor();
   f->ctx = ctx;
@@ -2277,10 +2287,11 @@ dfisher_status dfisher_solve(dfisher_ctx* ctx, const float* S, int64_t n, int64_
   // codes exist, the passes can carry S^T y, there is a correction, and the caller allows it
   const bool final8 = o.gram_prec == DFISHER_GRAM_MXFP8 && fp.usable && fp.line && o.sweeps != 0 &&
                       !o.final_resid && (o.flags & DFISHER_EXACT_APPLY) == 0;
+  bool own_pack = true;
   auto lay = [&](char* base) {
-    return carve(base, n, m, &gp, rp, cp, true, need_t, &fp, final8, is_centered(o));
+    return carve(base, n, m, &gp, rp, cp, true, need_t, &fp, final8, is_centered(o), own_pack);
   };
-  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
+  DF_TRY(ensure_gram_ws(ctx, S, gp, own_pack, [&] { return lay(nullptr).bytes; }));
   SolveBufs B = lay(static_cast<char*>(ctx->ws.ptr));
   B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
@@ -2362,10 +2373,11 @@ dfisher_status dfisher_solve_rowspace(dfisher_ctx* ctx, const float* S, int64_t 
   const dfi::ColPassPlan cp = dfi::colpass_plan(n, m);
   const dfi::RefinePassPlan fp = dfi::refine_pass_plan(n, m, lds, S);
   const bool need_t = (o.sweeps != 0 || o.final_resid) && !fp.usable;
+  bool own_pack = true;
   auto lay = [&](char* base) {
-    return carve(base, n, m, &gp, rp, cp, true, need_t, &fp);
+    return carve(base, n, m, &gp, rp, cp, true, need_t, &fp, false, false, own_pack);
   };
-  DF_TRY(ensure_gram_ws(ctx, S, gp, [&] { return lay(nullptr).bytes; }));
+  DF_TRY(ensure_gram_ws(ctx, S, gp, own_pack, [&] { return lay(nullptr).bytes; }));
   SolveBufs B = lay(static_cast<char*>(ctx->ws.ptr));
   B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
@@ -2478,8 +2490,9 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
     double *G, *P, *Q, *U1, *U2, *T, *Yi, *mpart;
     float* vp;
   };
+  bool own_pack = true;
   auto lay = [&](char* base, SolveBufs& B, Extra& X) -> size_t {
-    B = carve(base, N, m, &gp, rp, cp, true, false);
+    B = carve(base, N, m, &gp, rp, cp, true, false, nullptr, false, false, own_pack);
     Carver c;
     c.base = base;
     c.off = B.bytes;
@@ -2496,7 +2509,7 @@ dfisher_status dfisher_solve_complex(dfisher_ctx* ctx, const float* Z, int64_t n
   };
   SolveBufs B;
   Extra X;
-  DF_TRY(ensure_gram_ws(ctx, Z, gp, [&] { return lay(nullptr, B, X); }));
+  DF_TRY(ensure_gram_ws(ctx, Z, gp, own_pack, [&] { return lay(nullptr, B, X); }));
   lay(static_cast<char*>(ctx->ws.ptr), B, X);
   B.tick = ctx->d_tick;
   StageClock clk(ctx, st);
@@ -2625,7 +2638,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   double* packs = nullptr;
   auto layout = [&](char* base, SolveBufs& B, double*& Lall, double*& Dall, double*& dkk, int64_t*& dinfo,
                     int32_t*& dflag, MultiBufs& mb) {
-    B = carve(base, n, m, &gp, rp, cp, true, false);
+    B = carve(base, n, m, &gp, rp, cp, true, false, nullptr, false, false, packed);
     Carver c;
     c.base = base;
     c.off = B.bytes;
@@ -2647,13 +2660,16 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
   int32_t* dflag;
   MultiBufs mb;
   // without the memory (or, in a capture, the workspace of the call before it): two groups of vectors a pass, then the
-  // factorisations in place, then no planes (see ensure_gram_ws)
+  // factorisations in place, then no planes and the base plan's Gram slices (see ensure_gram_ws)
+  // (A workspace held by a capture is not shared out that finely, unless the captured call had to: a larger call is refused.)
   size_t need = 0;
-  const int levels = 4;
+  bool lean = false;
+  const int levels = ctx->ws.frozen && !ctx->held_lean ? 4 : 5;
   auto level = [&](int l) {
+    lean = l >= 4;
     most = l < 1 ? dfi::MULTI_GROUPS : 2;
     packed = l < 2;
-    gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec, l < 3);
+    gp = make_gram_plan(ctx, S, n, m, lds, o.gram_prec, l < 3, lean);
     return need = layout(nullptr, B, Lall, Dall, dkk, dinfo, dflag, mb);
   };
   if (capturing) {   // no allocation inside a capture; the graph will hold the workspace's addresses
@@ -2663,6 +2679,7 @@ dfisher_status dfisher_solve_batched(dfisher_ctx* ctx, const float* S, int64_t n
                   "the workspace must grow to %zu bytes, which cannot happen during a capture: make the same call "
                   "once outside the capture first", need);
     ctx->ws.frozen = true;
+    ctx->held_lean = ctx->held_lean || lean;
   } else {
     DF_TRY(ensure_levels(ctx, levels, level));
   }

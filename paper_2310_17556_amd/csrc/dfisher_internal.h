@@ -25,7 +25,7 @@ struct GramPlan {
 
 // aligned16: rows of S start on 16-byte boundaries (lds % 4 == 0 and S 16-byte aligned). For
 // split-BF16 the plan uses planes hi/lo written by the row pass (ldh > 0).
-// q_override > 0 fixes the split-K factor (nslice = 8 q); split_mode 0 keeps split-BF16 inside the
+// q_override > 0 fixes the split-K factor (nslice = 8 q), -1 takes the base plan's (the fewest slices); split_mode 0 keeps split-BF16 inside the
 // tile kernel (-1: planes).
 GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, int q_override = 0,
                    int split_mode = -1);

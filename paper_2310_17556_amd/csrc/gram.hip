@@ -1404,7 +1404,7 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
   const int64_t kstep = (prec == 2) ? 64 : KS;
   auto columns = [&](int64_t ns) { return std::max<int64_t>(1, ((cap + ns - 1) / ns + kstep - 1) / kstep) * kstep; };
   p.nslice = 8 * (q_override > 0 ? (int64_t)q_override : best_q);
-  if (q_override <= 0) {
+  if (q_override == 0) {
     // Then the cheapest of the base plan and the slice counts that just fill 1, 2, ... rounds of 256
     // workgroups. A round takes the columns of a slice at the tile kernel's rate on a full chip, every
     // work item writes and the reduction reads 256 KB of partials. (The base plan leaves most of the chip

@@ -46,6 +46,51 @@ def test_cholesky_in_place(n):
     b.close()
 
 
+def sized(tmp_path, n, call):
+    """A context whose held workspace just fits `call` of a longer problem with the base plan's slices (see test_base_plan)."""
+    ctx = dfl.dfisher_ctx_create(0)
+    f = tmp_path / "tune"
+    f.write_text("".join(f"{prec} 1 17 {al} 4 0\n" for prec in (0, 1) for al in (0, 1)))
+    dfl.dfisher_ctx_load_tuning(ctx, str(f))
+    call(ctx, 131072)
+    return ctx, hold(ctx)
+
+
+@pytest.mark.parametrize("what", ["solve", "rowspace", "factor", "gram"])
+def test_base_plan(tmp_path, what):
+    """n = 64, m = 70000: the plan takes more than 200 slices; the workspace holds the base plan's 32."""
+    n = 64
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    big = torch.randn(n, 131072, device="cuda", generator=gen) / 131072 ** 0.5
+    v = torch.randn(1, 131072, device="cuda", generator=gen)
+    f = torch.randn(n, device="cuda", dtype=torch.float64, generator=gen)
+    kw = dict(gram_prec=dfl.DFISHER_GRAM_FP32, sweeps=4, x_fp64=True)
+
+    def call(ctx, m):
+        S, V = big[:, :m].contiguous(), v[:, :m].contiguous()
+        if what == "solve":
+            return dfl.dfisher_solve(ctx, S, V[0], 0.1, **kw)[0]
+        if what == "rowspace":
+            return dfl.dfisher_solve_rowspace(ctx, S, f, 0.1, **kw)[0]
+        if what == "gram":
+            return dfl.dfisher_gram(ctx, S, dfl.DFISHER_GRAM_FP32, 0.1)
+        fac, _ = dfl.dfisher_factor_create(ctx, S, 0.1, **kw)
+        L = dfl.dfisher_factor_copy_L(fac)
+        fac.close()
+        return L
+
+    held, graph = sized(tmp_path, n, call)
+    got = call(held, 70000)
+    free = dfl.dfisher_ctx_create(0)
+    want = call(free, 70000)
+    # solves: four refinement sweeps from either Gram end at FP64 rounding; Gram and factor: FP32 sums of a slice
+    tol = 1e-5 if what in ("gram", "factor") else 1e-11
+    assert float((got - want).abs().max() / want.abs().max()) <= tol
+    del graph
+    held.close()
+    free.close()
+
+
 def test_planes_do_not_fit():
     """Little free memory (not a held workspace): rows that are not 16-byte aligned go without planes, twice alike."""
     n, m = 64, (1 << 24) + 1   # 4 GB, and as much for the planes
