@@ -1387,7 +1387,6 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
   // the exact column pass (one of the two returns at once)
   std::vector<dfi::Final8Job> fin;
   std::vector<dfi::ColJob> col;
-  int64_t blocks = 0;
   for (int32_t p : order) {
     const size_t q = (size_t)p;
     const int64_t off = U.voff[q];
@@ -1401,19 +1400,21 @@ dfisher_status uneven_enqueue(dfisher_ctx* ctx, int32_t np, const float* const* 
                                    dfi::fp8_ldq(m[p])});
     }
     col.push_back(dfi::ColJob{S[p], U.y + off, v[p], x[p], use, lambda[p], n[p], m[p], lds[p]});
-    blocks += dfi::colpass_blocks(m[p]);
   }
   HIP_TRY(dfi::final8_jobs(fin.data(), (int)fin.size(), FINAL8_EST_MAX, o.x_fp64, st));
-  // one launch where the column blocks fill the device (256 compute units x 8 workgroups) without a split of the rows;
-  // else per problem
-  if (blocks >= 2048) {
-    HIP_TRY(dfi::colpass_jobs(col.data(), np, o.x_fp64 ? 1 : 0, st));
-  } else {
-    for (const dfi::ColJob& j : col) {
-      const dfi::ColPassPlan cp = dfi::colpass_plan(j.n, j.m);
-      HIP_TRY(dfi::colpass_launch(cp, j.S, j.n, j.m, j.lds, j.y, j.v, j.lam, j.x, o.x_fp64, U.shared.cpart, st, j.skip));
-    }
+  std::vector<dfi::ColJob> together;
+  std::vector<char> taken((size_t)np, 0);
+  for (int k : dfi::colpass_together(col.data(), np)) {
+    together.push_back(col[(size_t)k]);
+    taken[(size_t)k] = 1;
   }
+  for (int32_t k = 0; k < np; ++k) {
+    const dfi::ColJob& j = col[(size_t)k];
+    if (taken[(size_t)k]) continue;
+    const dfi::ColPassPlan cp = dfi::colpass_plan(j.n, j.m);
+    HIP_TRY(dfi::colpass_launch(cp, j.S, j.n, j.m, j.lds, j.y, j.v, j.lam, j.x, o.x_fp64, U.shared.cpart, st, j.skip));
+  }
+  HIP_TRY(dfi::colpass_jobs(together.data(), (int)together.size(), o.x_fp64 ? 1 : 0, st));
   return DFISHER_OK;
 }
 

@@ -2,7 +2,9 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
+#include <vector>
 
 namespace dfi {
 
@@ -230,7 +232,30 @@ struct ColJob {
   double lam;
   int64_t n, m, lds;
 };
-int64_t colpass_blocks(int64_t m);
+constexpr int CP_COLS = 1024;    // columns per workgroup of the column pass
+inline int64_t colpass_blocks(int64_t m) { return (m + CP_COLS - 1) / CP_COLS; }
+// The jobs (indexes, the longest walks over rows first) that share one launch; the others go alone, their rows split.
+// A launch needs enough column blocks to fill the device (256 compute units x 8 workgroups) without a split, and none of its
+// workgroups may walk for longer than the launch streams: 0.13 us a row alone, 4 KB a row of a block at 5 TB/s, so no job
+// of more than 1 / 160 of all the blocks' rows. (64 x 2097152 and 4096 x 8192: 536 us in one launch, 178 apart; and 512 x 8192: 178 with
+// the longest walk last, 162 first.)
+inline std::vector<int> colpass_together(const ColJob* jobs, int count) {
+  std::vector<int> at;
+  int64_t rows = 0, blocks = 0;
+  for (int k = 0; k < count; ++k) {
+    at.push_back(k);
+    rows += colpass_blocks(jobs[k].m) * jobs[k].n;
+    blocks += colpass_blocks(jobs[k].m);
+  }
+  std::stable_sort(at.begin(), at.end(), [&](int a, int b) { return jobs[a].n > jobs[b].n; });
+  size_t first = 0;
+  for (; first < at.size() && jobs[at[first]].n > rows / 160; ++first) {
+    rows -= colpass_blocks(jobs[at[first]].m) * jobs[at[first]].n;
+    blocks -= colpass_blocks(jobs[at[first]].m);
+  }
+  at.erase(at.begin(), at.begin() + (blocks >= 2048 ? first : at.size()));
+  return at;
+}
 hipError_t colpass_jobs(const ColJob* jobs, int count, int mode, hipStream_t st);
 
 // Reductions of scaled-FP8 Grams (gram_reduce without mirror), projections (gram_project of one segment), the

@@ -258,7 +258,7 @@ refine_reduce_grouped_kernel(const ReduceJob* __restrict__ jobs, int njobs) {
 
 // ---------------------------------------------------------------------------- column pass
 constexpr int CP_THREADS = 256;
-constexpr int CP_COLS = CP_THREADS * 4;  // 1024 columns per workgroup
+static_assert(CP_COLS == 4 * CP_THREADS, "four columns a thread");
 constexpr int CP_UNROLL = 8;
 
 template <int MODE>
@@ -1098,8 +1098,6 @@ hipError_t rowpass_prep_jobs(const PrepJob* jobs, int count, hipStream_t st) {
                        hipLaunchKernelGGL(rowpass_reduce_jobs_kernel, dim3(blocks), dim3(256), 0, st, l);
                      });
 }
-
-int64_t colpass_blocks(int64_t m) { return (m + CP_COLS - 1) / CP_COLS; }
 
 hipError_t colpass_jobs(const ColJob* jobs, int count, int mode, hipStream_t st) {
   if (mode != 0 && mode != 1) return hipErrorInvalidValue;

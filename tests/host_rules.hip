@@ -66,3 +66,15 @@ RULES void rules_ws_counts(FakeContext* c, int64_t* out) {
   for (int i = 0; i < 5; ++i) out[i] = v[i];
 }
 RULES void rules_ws_delete(FakeContext* c) { delete c; }
+
+// the jobs that share a launch, in launch order; returns how many
+RULES int rules_colpass_together(const int64_t* n, const int64_t* m, int count, int* out) {
+  std::vector<dfi::ColJob> jobs((size_t)count);
+  for (int k = 0; k < count; ++k) {
+    jobs[(size_t)k].n = n[k];
+    jobs[(size_t)k].m = m[k];
+  }
+  const std::vector<int> at = dfi::colpass_together(jobs.data(), count);
+  std::copy(at.begin(), at.end(), out);
+  return (int)at.size();
+}

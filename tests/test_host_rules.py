@@ -155,3 +155,22 @@ def test_workspace_held_by_a_capture(rules):
     f.set(1000)
     assert f.levels(60, 50, 40, can_grow=False) == 1 and f.levels(70, 60, can_grow=False) == -1
     assert f.counts()[1] == 1
+
+
+@pytest.mark.parametrize("shapes,alone", [
+    ([(64, 1 << 21)], []),
+    ([(64, 1 << 21), (4096, 8192)], [1]),              # 8 workgroups would walk 4096 rows behind a short launch
+    ([(4096, 8192), (64, 1 << 21), (3000, 4096)], [0, 2]),
+    ([(512, 8192), (64, 1 << 21)], []),
+    ([(64, 1 << 21), (1024, 262144), (300, 9000)], []),
+    ([(1024, 65536)] * 40, []),
+    ([(64, 32768)] * 30, list(range(30))),             # too few column blocks to fill the device
+    ([(4096, 8192), (64, 2040 * 1024)], [0, 1]),       # the first alone, too few left
+])
+def test_column_passes_that_share_a_launch(rules, shapes, alone):
+    k = len(shapes)
+    n, m = ((ctypes.c_int64 * k)(*v) for v in zip(*shapes))
+    out = (ctypes.c_int * k)()
+    took = list(out[:rules.rules_colpass_together(n, m, k, out)])
+    assert sorted(set(range(k)) - set(took)) == alone
+    assert [shapes[i][0] for i in took] == sorted((shapes[i][0] for i in took), reverse=True)
