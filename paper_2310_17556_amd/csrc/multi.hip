@@ -339,16 +339,30 @@ rowpass_multi_tm_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64
       __builtin_amdgcn_sched_barrier(0);   // widen load u's values only where its products use them
     }
   };
+  // The loads of vectors into LDS have landed: all but the loads of S issued behind them (kept there by the fence in load).
+  // (vmcnt(NU), the other counters alone.)
+  auto landed = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!FP32V) __builtin_amdgcn_s_waitcnt((NU & 15) | ((NU >> 4) << 14) | (7 << 4) | (15 << 8));
+    asm volatile("" ::: "memory");
+  };
+  auto load = [&](auto bc, int64_t cs, f32x4* sv) __attribute__((always_inline)) {
+    load_t(bc, cs);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    load_s(cs, sv);
+    __builtin_amdgcn_sched_barrier(0);
+  };
   // A step with another behind it, whose S goes to nx and whose vectors go to the other buffer meanwhile. Two register sets
   // in turn and no branch: with one set and a copy, or loads under a condition, the compiler waits for the loads as soon
   // as they are issued, a whole memory latency a step.
   auto step = [&](auto bc, int64_t cs, const f32x4* sv, f32x4* nx) __attribute__((always_inline)) {
     using Other = std::integral_constant<int, 1 - decltype(bc)::value>;
-    load_t(Other{}, cs + STEP);
-    load_s(cs + STEP, nx);
+    load(Other{}, cs + STEP, nx);
     products(bc, sv);
     store_t(Other{});   // last read before the previous barrier
-    __syncthreads();    // (every load has landed)
+    landed();
+    __syncthreads();
   };
   // the last step: columns past c1 count as zero
   auto last = [&](auto bc, int64_t cs, f32x4* sv) __attribute__((always_inline)) {
@@ -363,9 +377,9 @@ rowpass_multi_tm_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64
     using B0 = std::integral_constant<int, 0>;
     using B1 = std::integral_constant<int, 1>;
     f32x4 s0[NU], s1[NU];
-    load_t(B0{}, c0);
-    load_s(c0, s0);
+    load(B0{}, c0, s0);
     store_t(B0{});
+    landed();
     __syncthreads();
     int64_t cs = c0;
     for (; cs + 2 * STEP < c1; cs += 2 * STEP) {
