@@ -201,6 +201,25 @@ __device__ __forceinline__ void gather_rows(double x, double (&y)[4]) {
   for (int g = 0; g < 4; ++g) y[g] = __longlong_as_double((long long)(((uint64_t)o[g][1] << 32) | o[g][0]));
 }
 
+// A diagonal entry of W below this may leave a pivot whose reciprocal overflows (2^-1024): factor16 then gets the block with
+// every row and column scaled by a power of two (scale16), which is exact and taken off its results again. The entries are
+// looked at before a task's waits, so that the chain of pivots carries nothing of it.
+constexpr double SMALL_DIAG = 0x1p-900;
+__device__ __forceinline__ int row_exponent(const f64x4& t, int lane) {   // half of T[r][r]'s, 0 unless it is > 0
+  const int r = lane & 15;
+  double d = 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double v = __shfl(t[q], 16 * (r & 3) + r, 64);
+    if ((r >> 2) == q) d = v;
+  }
+  return d > 0.0 && d < __builtin_inf() ? __builtin_amdgcn_frexp_exp(d) >> 1 : 0;
+}
+__device__ __forceinline__ void scale16(f64x4& t, int k, int lane) {   // k: the row's exponent
+#pragma unroll
+  for (int q = 0; q < 4; ++q) t[q] = __builtin_ldexp(t[q], -k - __shfl(k, 4 * q + (lane >> 4), 64));
+}
+
 // 1 / d and 1 / sqrt(d) of a normal d > 0: the hardware estimate (relative error e of about 2^-23) and
 // one third-order step, error e^3.
 __device__ __forceinline__ double recip(double d) {
@@ -428,8 +447,12 @@ __device__ void diag_task(double* A, const double* W, double add, int64_t n, int
   if (threadIdx.x < 16) sm.have_l[threadIdx.x >> 2][threadIdx.x & 3] = 0;
   f64x4 t1[4], t2[4];
   load_strip(t2, W, add, n, J, J, w, lane);
+  const int64_t own = min<int64_t>((int64_t)J * NB + 16 * w + (lane & 15), n - 1);
+  const double own_diag = W[own * n + own] + add;
   __builtin_amdgcn_s_setprio(3);   // ahead of the tile task that shares the compute unit's matrix cores
   __syncthreads();
+  bool small = false;
+  if (J == 0) small = __ballot(own_diag > 0.0 && own_diag < SMALL_DIAG) != 0;
   if (J > 0) {
     bool ok = true;
     const double* rowP = pack + (int64_t)(J - 1) * J / 2 * TD;
@@ -453,6 +476,7 @@ __device__ void diag_task(double* A, const double* W, double add, int64_t n, int
     }
 #pragma unroll
     for (int p = 0; p < 4; ++p) t1[p] = -t1[p];
+    small = __ballot(own_diag > 0.0 && own_diag < SMALL_DIAG) != 0;
     // own rows of L_{J,J-1}, panel by panel
     const bool solved = solve_strip(t1, rowP + (int64_t)(J - 1) * TD, fP + (J - 1), ticket, lane,
                                     [&](int p, const f64x4& xn) {
@@ -541,7 +565,18 @@ __device__ void diag_task(double* A, const double* W, double add, int64_t n, int
   }
   f64x4 lw, dw;
   double piv[4];
+  int k = 0;
+  if (small) {
+    k = row_exponent(td, lane);
+    scale16(td, k, lane);
+  }
   factor16(td, lw, dw, piv, lane);
+  if (small)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      lw[q] = __builtin_ldexp(lw[q], k);
+      dw[q] = __builtin_ldexp(dw[q], -k);
+    }
 #pragma unroll
   for (int q = 0; q < 4; ++q) sm.d[w][((lane >> 4) + 4 * q) * LDD + (lane & 15)] = dw[q];
   have(&sm.have_l[w][w]);
