@@ -1459,10 +1459,11 @@ void gram_q_candidates(int64_t n, int64_t m, size_t max_part_bytes, int* out, in
   const int64_t ntile = (n + T - 1) / T;
   const int64_t ntri = ntile * (ntile + 1) / 2;
   const int64_t maxq = std::max<int64_t>(1, m / (8 * 2048));
+  const int64_t fill = std::min<int64_t>(m / (8 * 256), 4352 / (8 * ntri));   // the limits of the built-in plan's slices
   static const int qs[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
   int c = 0;
   for (int q : qs) {
-    if (q > 1 && q > maxq) break;
+    if (q > 1 && q > std::max(maxq, fill)) break;
     if (q > 1 && (size_t)8 * q * ntri * T * T * sizeof(float) > max_part_bytes) break;
     if (c < cap) out[c++] = q;
   }

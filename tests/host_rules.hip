@@ -78,3 +78,9 @@ RULES int rules_colpass_together(const int64_t* n, const int64_t* m, int count, 
   std::copy(at.begin(), at.end(), out);
   return (int)at.size();
 }
+
+RULES int rules_gram_candidates(int64_t n, int64_t m, int* out) {
+  int count = 0;
+  dfi::gram_q_candidates(n, m, (size_t)4 << 30, out, &count, 16);
+  return count;
+}

@@ -174,3 +174,18 @@ def test_column_passes_that_share_a_launch(rules, shapes, alone):
     took = list(out[:rules.rules_colpass_together(n, m, k, out)])
     assert sorted(set(range(k)) - set(took)) == alone
     assert [shapes[i][0] for i in took] == sorted((shapes[i][0] for i in took), reverse=True)
+
+
+def test_tuner_reaches_the_built_in_plan(rules):
+    """The candidates go up to at least half the built-in plan's slices (512 is the most that a tuning table can hold), so that
+    tuning a context does not cost it the plan it had."""
+    ns, ks, q = ctypes.c_int64(), ctypes.c_int64(), (ctypes.c_int * 16)()
+    rules.rules_gram_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int64)] * 2
+    rules.rules_gram_candidates.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(ctypes.c_int)]
+    for n in (8, 64, 256, 300, 520, 1000, 1500, 2048, 4096, 8192):
+        for m in (1000, 10_000, 40_000, 100_000, 250_000, 1_000_000):
+            got = list(q[:rules.rules_gram_candidates(n, m, q)])
+            assert got[0] == 1 and got == sorted(got) and got[-1] <= 64
+            for prec in (0, 1, 2):
+                rules.rules_gram_plan(n, m, m, prec, 1, 0, -1, ns, ks)
+                assert 8 * got[-1] >= min(ns.value, 512) / 2, (n, m, prec, got, ns.value)
