@@ -650,7 +650,7 @@ __host__ __device__ inline int64_t chol_tasks(int64_t nb) { return 1 + nb * (nb 
 // nbatch matrices (matrix b at A + b sA, pack + b sP, ready + b sR; with src.W all read src.W, its diagonal shifted by
 // each matrix's own term, and A is only written): ticket t is task t / nbatch of
 // matrix t % nbatch. With jobs / tasks: ticket t is entry t of the task table. 256 threads; two
-// workgroups per compute unit (50 KB of LDS, at most 256 registers).
+// workgroups per compute unit (74 KB of its 160 KB of LDS each, at most 256 registers).
 __global__ void __launch_bounds__(256, 2)
 chol_kernel(double* A, int64_t n, int64_t sA, double* pack, int64_t sP, uint32_t* ready, int64_t sR, int64_t* info,
             int32_t* flag, uint32_t* ticket, int nbatch, const FactorJob* __restrict__ jobs,

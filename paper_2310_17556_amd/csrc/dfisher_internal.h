@@ -36,8 +36,6 @@ GramPlan gram_plan(int64_t n, int64_t m, int64_t lds, int prec, bool aligned16, 
 // first limit alone a tuned context took 48 slices where the built-in plan takes 241: n = 256, m = 1e5.)
 void gram_q_candidates(int64_t n, int64_t m, size_t max_part_bytes, int* out, int* count, int cap);
 hipError_t gram_launch(const GramPlan& p, const float* S, float* part, hipStream_t st);
-// The first column the tile kernel of plan p leaves to gram_reduce.
-int64_t gram_tail_start(const GramPlan& p, const float* S);
 // Row stride (bf16 elements) of the split-BF16 planes for m columns.
 inline int64_t split_ldh(int64_t m) { return (m + 63) / 64 * 64; }
 // Split-BF16 Gram from the column-blocked planes hi = bf16(S), lo = bf16(S - hi) (p.ldh > 0).
@@ -91,7 +89,7 @@ struct RowPassPlan {
 };
 RowPassPlan rowpass_plan(int64_t n, int64_t m, int64_t lds);
 // With q != nullptr the pass also writes the scaled-FP8 copy of S (codes n x ldq bytes, E8M0
-// scale bytes n x ldq/32; ldq a multiple of 64, >= m; needs 16-byte aligned rows and want_d).
+// scale bytes n x ldq/32; ldq a multiple of 64, >= m; needs want_d).
 // Row-major, or with `blocked` (ldq a multiple of 128) in the column-blocked layout the
 // scaled-FP8 Gram reads: codes in 64-column blocks, each holding all n rows contiguously, code
 // (i, k) at q[((k / 64) n + i) 64 + k % 64]; scale byte (i, k / 32) at sc[((k / 128) n + i) 4 + (k / 32) % 4].
@@ -367,7 +365,6 @@ hipError_t axpy_many(double* y, const double* d, int64_t len, hipStream_t st);
 // scratch of 64 x 64 doubles (the inverses of the current diagonal block's four 16 x 16
 // diagonal sub-blocks, for the panel solve).
 constexpr size_t POTRF_DKK_BYTES = 64 * 64 * sizeof(double);
-hipError_t potrf_launch(double* A, int64_t n, int64_t* info_dev, int32_t* flag_dev, double* dkk, hipStream_t st);
 // nbatch independent factorisations in the same launches: matrix b at A + b sA, info_dev[b],
 // flag_dev[b], dkk + b 64 * 64 (nbatch <= 65535).
 hipError_t potrf_launch_batched(double* A, int64_t n, int64_t nbatch, int64_t sA, int64_t* info_dev, int32_t* flag_dev,
@@ -402,8 +399,8 @@ struct CholSource {
 };
 hipError_t chol_launch_batched(double* A, int64_t n, int64_t nbatch, int64_t sA, int64_t* info_dev, int32_t* flag_dev,
                                double* pack, uint32_t* ticket, hipStream_t st, const CholSource& src = CholSource{});
-// Grouped: tasks_dev lists every job's tasks (chol_task of s = 0 .. chol_task_count(n) - 1 of each job), any
-// interleaving that keeps each job's order.
+// Grouped: tasks_dev lists every job's chol_task_count(n) tasks, any interleaving that keeps each job's order: block column
+// c's diagonal task (i = 0), then (c > 0) those of the tiles (c + i, c - 1), i = 1 .. nb - 1 - c.
 struct FactorTask {
   int32_t job, c, i, pad;
 };
@@ -524,8 +521,6 @@ hipError_t add_diag_copy(const double* src, double* dst, int64_t n, double lam, 
 // dst = src + (lam + scale * dmax[0]) * I (dmax unread if scale == 0)
 hipError_t shift_add_copy(const double* src, double* dst, int64_t n, double scale, const double* dmax, double lam,
                           hipStream_t st);
-// y += d (length n)
-hipError_t axpy_inplace(double* y, const double* d, int64_t n, hipStream_t st);
 // y = 0 (length n; a kernel, not a memset, so that it may sit in a captured graph)
 hipError_t fill_zero(double* y, int64_t n, hipStream_t st);
 // max_i W_ii

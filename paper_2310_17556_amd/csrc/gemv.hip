@@ -702,8 +702,7 @@ __device__ __forceinline__ void refine_line_body(const float* __restrict__ S, in
   __shared__ double tp[FR_WAVES][2 * FS_COLS];   // per wave: column partials of S^T y, then of S^T 1
   __shared__ double tf[2 * FS_COLS];
   __shared__ int got;
-  constexpr bool wcs = CS;                        // also the column sums S^T 1 into csout
-  constexpr int nl = CS ? 2 * FS_COLS : FS_COLS;  // lanes of wave 0 that carry a column value
+  constexpr int nl = CS ? 2 * FS_COLS : FS_COLS;  // lanes of wave 0 that carry a column value (CS: S^T 1 as well)
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -966,8 +965,6 @@ __global__ void fill_u64_kernel(uint64_t* __restrict__ a, int64_t k, uint64_t v)
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < k) a[i] = v;
 }
-
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
 

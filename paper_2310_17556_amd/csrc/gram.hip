@@ -1510,8 +1510,6 @@ static int64_t tail_start(const GramPlan& p, const float* S) {
   return use_v2(p) && vec_rows(p, S) ? (p.m & ~(int64_t)3) : p.m;
 }
 
-int64_t gram_tail_start(const GramPlan& p, const float* S) { return tail_start(p, S); }
-
 hipError_t gram_launch(const GramPlan& p, const float* S, float* part, hipStream_t st) {
   const bool vec = vec_rows(p, S);
   const dim3 grid((unsigned)(8 * items_per_xcd(p.ntri, p.nslice)));

@@ -438,11 +438,6 @@ __global__ void shift_copy_kernel(const double* __restrict__ src, double* __rest
   dst[idx] = src[idx] + add;
 }
 
-__global__ void axpy_kernel(double* __restrict__ y, const double* __restrict__ d, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) y[i] += d[i];
-}
-
 __global__ void fill_zero_kernel(double* __restrict__ y, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) y[i] = 0.0;
@@ -533,10 +528,6 @@ hipError_t potrf_launch_grouped(const FactorJob* jobs_dev, int64_t njobs, int64_
   return hipGetLastError();
 }
 
-hipError_t potrf_launch(double* A, int64_t n, int64_t* info_dev, int32_t* flag_dev, double* dkk, hipStream_t st) {
-  return potrf_launch_batched(A, n, 1, n * n, info_dev, flag_dev, dkk, st);
-}
-
 hipError_t zero_upper(double* A, int64_t n, hipStream_t st) {
   const int64_t nb = (n + 255) / 256;
   hipLaunchKernelGGL(zero_upper_kernel, dim3((unsigned)(nb * n)), dim3(256), 0, st, A, n);
@@ -555,11 +546,6 @@ hipError_t shift_add_copy(const double* src, double* dst, int64_t n, double scal
   const int64_t tot = n * n;
   hipLaunchKernelGGL(shift_copy_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, src, dst, n, scale, dmax,
                      lam);
-  return hipGetLastError();
-}
-
-hipError_t axpy_inplace(double* y, const double* d, int64_t n, hipStream_t st) {
-  hipLaunchKernelGGL(axpy_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, y, d, n);
   return hipGetLastError();
 }
 
