@@ -63,40 +63,32 @@ struct Vec4<double> {
   double x[4];
 };
 
-// Four consecutive values by one load of their own alignment only (rows of any stride and offset): a wave's 1 KB then
-// touches one 128-byte line more than with 16-byte aligned rows, against four loads a lane. 1000 x 99999, S v: 79 us
-// (127 with four loads; 78 with aligned rows); (v - S^T y) / lambda: 100 us (110; 80). 4096 x 100001: 283 us (410; 280) and
-// 359 us (409; 301).
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef double f64x4u __attribute__((ext_vector_type(4), aligned(8)));
-
+// Loads of four consecutive values a lane from a wave-uniform start, rows of any stride and offset, as buffers that end with the
+// columns: a lane or a word of it past them gets zeros without a test. (With a test per load the lanes that fail it wait for
+// the load of the others, a memory latency a row at the end of the columns.) A wave's 1 KB of a row that is not 16-byte
+// aligned touches one 128-byte line more, against four loads a lane. 1000 x 99999, S v: 76 us (127 with four loads, 79 with
+// a test; aligned rows 76); (v - S^T y) / lambda: 79 us (110; 99; 79). 4096 x 100001: 282 us (410; 283; 279) and 307 us
+// (409; 359; 307). A problem of 300 x 4096: 11.9 and 8.8 us (13.3 and 12.7 with a test).
 template <typename VT>
-__device__ __forceinline__ void load_vec4(const VT* __restrict__ v, int64_t col, int64_t m, Vec4<VT>& out) {
-  if constexpr (sizeof(VT) == 4) {
-    if (col + 4 <= m) {
-      out.x = *reinterpret_cast<const f32x4u*>(v + col);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out.x[e] = (col + e < m) ? v[col + e] : 0.f;
-    }
-  } else {
-    if (col + 4 <= m) {
-      const f64x4u t = *reinterpret_cast<const f64x4u*>(v + col);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out.x[e] = t[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out.x[e] = (col + e < m) ? v[col + e] : 0.0;
-    }
-  }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t columns(const VT* p, int64_t left) {   // `left` of them, at most 2^20 used
+  const int n = (int)max<int64_t>(0, min<int64_t>(left, 1 << 20));
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<VT*>(p), 0, n * (int)sizeof(VT), 0x00020000);
 }
-
-__device__ __forceinline__ void load_s4(const float* __restrict__ p, int64_t col, int64_t m, f32x4& out) {
-  if (col + 4 <= m) {
-    out = *reinterpret_cast<const f32x4u*>(p);
+__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t rs, int first) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, 4 * first, 0, 0));
+}
+template <typename VT>
+__device__ __forceinline__ void load_vec4(__amdgpu_buffer_rsrc_t rs, int first, Vec4<VT>& out) {
+  if constexpr (sizeof(VT) == 4) {
+    out.x = load4(rs, first);
   } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) out[e] = (col + e < m) ? p[e] : 0.f;
+    const f32x4 lo = load4(rs, 2 * first), hi = load4(rs, 2 * first + 4);
+    typedef double f64x2 __attribute__((ext_vector_type(2)));
+    const f64x2 a = __builtin_bit_cast(f64x2, lo), b = __builtin_bit_cast(f64x2, hi);
+    out.x[0] = a[0];
+    out.x[1] = a[1];
+    out.x[2] = b[0];
+    out.x[3] = b[1];
   }
 }
 
@@ -113,7 +105,7 @@ rowpass_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, c
                int64_t cg, int64_t ngroups, double* __restrict__ part, uint8_t* __restrict__ q,
                uint8_t* __restrict__ sc, int64_t ldq) {
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t row0 = ((int64_t)blockIdx.x * RP_WAVES + wave) * RP_RPW;
   const int64_t g = blockIdx.y;
   const int64_t c0 = g * cg;
@@ -128,19 +120,17 @@ rowpass_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, c
   for (int64_t cs = c0; cs < c1; cs += RP_SUB) {
     Vec4<VT> vv[RP_U];
     if constexpr (WANT_B) {
+      const __amdgpu_buffer_rsrc_t rv = columns(v + cs, c1 - cs);
 #pragma unroll
-      for (int u = 0; u < RP_U; ++u) load_vec4<VT>(v, cs + 256 * u + 4 * lane, c1, vv[u]);
+      for (int u = 0; u < RP_U; ++u) load_vec4<VT>(rv, 256 * u + 4 * lane, vv[u]);
     }
 #pragma unroll
     for (int r = 0; r < RP_RPW; ++r) {
       if (r < nr) {
-        const float* rowp = S + (row0 + r) * lds;
+        const __amdgpu_buffer_rsrc_t rs = columns(S + (row0 + r) * lds + cs, c1 - cs);
         f32x4 sv[RP_U];
 #pragma unroll
-        for (int u = 0; u < RP_U; ++u) {
-          const int64_t col = cs + 256 * u + 4 * lane;
-          load_s4(rowp + col, col, c1, sv[u]);
-        }
+        for (int u = 0; u < RP_U; ++u) sv[u] = load4(rs, 256 * u + 4 * lane);
 #pragma unroll
         for (int u = 0; u < RP_U; ++u)
 #pragma unroll
@@ -282,18 +272,23 @@ __device__ __forceinline__ void colpass_store(void* out, const float* v, double 
 
 // Grid: x = column blocks of CP_COLS, y = row splits of `rps` rows. nsplit == 1 stores the final
 // result; otherwise FP64 partial sums go to part[split * m + col].
-template <int MODE>
+template <int MODE, bool Y2>
 __device__ __forceinline__ void colpass_body(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds,
                                              const double* __restrict__ y, const float* v, double lam, void* out,
                                              double* __restrict__ part, int64_t rps, const int* __restrict__ skip,
                                              const double* __restrict__ y2, int64_t colblock, int64_t split) {
   if (skip && *skip) return;
-  auto y_at = [&](int64_t i) { return y2 ? y[i] + y2[i] : y[i]; };
+  // (Y2 at compile time: with a test of y2 each row's load of y was waited for by itself, 16 us for a small pass against 14)
+  auto y_at = [&](int64_t i) {
+    if constexpr (Y2) return y[i] + y2[i];
+    else return y[i];
+  };
   const int64_t col = colblock * CP_COLS + 4 * threadIdx.x;
   const int64_t r0 = split * rps;
   const int64_t r1 = min(n, r0 + rps);
   double t[4] = {0.0, 0.0, 0.0, 0.0};
-  const bool full = col + 4 <= m;
+  const int64_t cb = colblock * CP_COLS;
+  const int lc = 4 * threadIdx.x;
   if (col < m) {
     int64_t i = r0;
     for (; i + CP_UNROLL <= r1; i += CP_UNROLL) {
@@ -301,12 +296,7 @@ __device__ __forceinline__ void colpass_body(const float* __restrict__ S, int64_
       double yy[CP_UNROLL];
 #pragma unroll
       for (int u = 0; u < CP_UNROLL; ++u) {
-        const float* p = S + (i + u) * lds + col;
-        if (full) sv[u] = *reinterpret_cast<const f32x4u*>(p);
-        else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) sv[u][e] = (col + e < m) ? p[e] : 0.f;
-        }
+        sv[u] = load4(columns(S + (i + u) * lds + cb, m - cb), lc);
         yy[u] = y_at(i + u);
       }
 #pragma unroll
@@ -315,13 +305,7 @@ __device__ __forceinline__ void colpass_body(const float* __restrict__ S, int64_
         for (int e = 0; e < 4; ++e) t[e] = fma((double)sv[u][e], yy[u], t[e]);
     }
     for (; i < r1; ++i) {
-      const float* p = S + i * lds + col;
-      f32x4 s;
-      if (full) s = *reinterpret_cast<const f32x4u*>(p);
-      else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] = (col + e < m) ? p[e] : 0.f;
-      }
+      const f32x4 s = load4(columns(S + i * lds + cb, m - cb), lc);
       const double yi = y_at(i);
 #pragma unroll
       for (int e = 0; e < 4; ++e) t[e] = fma((double)s[e], yi, t[e]);
@@ -338,12 +322,12 @@ __device__ __forceinline__ void colpass_body(const float* __restrict__ S, int64_
   }
 }
 
-template <int MODE>
+template <int MODE, bool Y2>
 __global__ void __launch_bounds__(CP_THREADS)
 colpass_kernel(const float* __restrict__ S, int64_t n, int64_t m, int64_t lds, const double* __restrict__ y,
                const float* v, double lam, void* out, double* __restrict__ part, int64_t rps,
                const int* __restrict__ skip, const double* __restrict__ y2) {
-  colpass_body<MODE>(S, n, m, lds, y, v, lam, out, part, rps, skip, y2, blockIdx.x, blockIdx.y);
+  colpass_body<MODE, Y2>(S, n, m, lds, y, v, lam, out, part, rps, skip, y2, blockIdx.x, blockIdx.y);
 }
 
 // many problems in one launch: enough column blocks between them, so that no rows are split
@@ -351,7 +335,7 @@ template <int MODE>
 __global__ void __launch_bounds__(CP_THREADS) colpass_jobs_kernel(JobList<ColJob> l) {
   const int k = job_of(l, blockIdx.x);
   const ColJob& j = l.job[k];
-  colpass_body<MODE>(j.S, j.n, j.m, j.lds, j.y, j.v, j.lam, j.x, nullptr, j.n, j.skip, nullptr, blockIdx.x - l.blk0[k], 0);
+  colpass_body<MODE, false>(j.S, j.n, j.m, j.lds, j.y, j.v, j.lam, j.x, nullptr, j.n, j.skip, nullptr, blockIdx.x - l.blk0[k], 0);
 }
 
 template <int MODE>
@@ -391,7 +375,7 @@ __device__ __forceinline__ void rowpass_prep_body(const float* __restrict__ S, i
                                                   int64_t rowblock, int64_t g, int64_t ngroups) {
   __shared__ __align__(16) uint8_t stage_all[RP_WAVES][RPREP_STAGE];
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint8_t* stg = stage_all[wave];
   const int64_t row0 = (rowblock * RP_WAVES + wave) * RP_RPW;
   const int64_t c0 = g * cg;
@@ -406,13 +390,11 @@ __device__ __forceinline__ void rowpass_prep_body(const float* __restrict__ S, i
   for (int64_t cs = c0; cs < c1; cs += RPREP_COLS) {
     const int64_t col = cs + 4 * lane;
     f32x4 vv = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (WANT_B) load_s4(v + col, col, c1, vv);
+    if constexpr (WANT_B) vv = load4(columns(v + cs, c1 - cs), 4 * lane);
     f32x4 sv[RP_RPW];
 #pragma unroll
-    for (int r = 0; r < RP_RPW; ++r) {
-      sv[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      if (r < nr) load_s4(S + (row0 + r) * lds + col, col, c1, sv[r]);
-    }
+    for (int r = 0; r < RP_RPW; ++r)   // (rows past n: no columns)
+      sv[r] = load4(columns(S + (row0 + (r < nr ? r : 0)) * lds + cs, r < nr ? c1 - cs : 0), 4 * lane);
 #pragma unroll
     for (int r = 0; r < RP_RPW; ++r)
 #pragma unroll
@@ -1062,11 +1044,14 @@ hipError_t colpass_launch(const ColPassPlan& p, const float* S, int64_t n, int64
                           const int* skip, const double* y2) {
   const dim3 grid((unsigned)((m + CP_COLS - 1) / CP_COLS), (unsigned)p.nsplit);
   double* pp = p.nsplit > 1 ? part : nullptr;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2);
+  };
   switch (mode) {
-    case 0: hipLaunchKernelGGL(colpass_kernel<0>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2); break;
-    case 1: hipLaunchKernelGGL(colpass_kernel<1>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2); break;
-    case 3: hipLaunchKernelGGL(colpass_kernel<3>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2); break;
-    default: hipLaunchKernelGGL(colpass_kernel<2>, grid, dim3(CP_THREADS), 0, st, S, n, m, lds, y, v, lambda, out, pp, p.rps, skip, y2); break;
+    case 0: y2 ? launch(colpass_kernel<0, true>) : launch(colpass_kernel<0, false>); break;
+    case 1: y2 ? launch(colpass_kernel<1, true>) : launch(colpass_kernel<1, false>); break;
+    case 3: y2 ? launch(colpass_kernel<3, true>) : launch(colpass_kernel<3, false>); break;
+    default: y2 ? launch(colpass_kernel<2, true>) : launch(colpass_kernel<2, false>); break;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.nsplit == 1) return e;
