@@ -117,3 +117,54 @@ def test_planes_do_not_fit():
     assert "gram_kernel_split" in kernels(lambda: dfl.dfisher_gram(ctx, S, dfl.DFISHER_GRAM_BF16X3, 0.5))
     assert float((got - one).abs().max() / one.abs().max()) <= 3e-5   # dropped lo.lo products
     ctx.close()
+
+
+@pytest.mark.parametrize("what,m", [("batched", 23000), ("factor", 60000)])
+def test_two_groups_a_pass(what, m):
+    """64 vectors on a workspace that the call for 32 vectors, or the factor, of a problem with m = 24000 left: two groups of 16 a
+    pass instead of four."""
+    n = 64
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    big, V = torch.randn(n, 60000, device="cuda", generator=gen) / 200, torch.randn(64, 60000, device="cuda", generator=gen)
+    kw = dict(gram_prec=dfl.DFISHER_GRAM_FP32, sweeps=4, shift_policy=dfl.DFISHER_SHIFT_NONE, x_fp64=True)
+
+    def prepare(ctx, m, nrhs):
+        S, W = big[:, :m].contiguous(), V[:nrhs, :m].contiguous()
+        if what == "batched":
+            return lambda: dfl.dfisher_solve_batched(ctx, S, [0.1, 0.2][:max(1, nrhs // 32)], W[:32], **kw)[0]
+        f, _ = dfl.dfisher_factor_create(ctx, S, 0.1, **kw)
+        return lambda: dfl.dfisher_factor_solve(f, W)
+
+    held, free = dfl.dfisher_ctx_create(0), dfl.dfisher_ctx_create(0)
+    prepare(held, 24000, 32)()
+    graph = hold(held)
+    X = []
+    for ctx, groups in ((held, 2), (free, 4)):
+        call = prepare(ctx, m, 64)
+        ran = kernels(lambda: X.append(call()))
+        assert f"rowpass_multi_tm_kernel<{groups}, false>" in ran and f"rowpass_multi_tm_kernel<{6 - groups}, false>" not in ran
+    a, b = (x[0] if isinstance(x, tuple) else x for x in X)
+    assert float((a - b).abs().max() / b.abs().max()) <= 1e-11   # four sweeps end at FP64 rounding, in either order of the sums
+    del graph
+
+
+def test_uneven_in_place(tmp_path):
+    """The packed copy of a factor of 1000 rows (4 MB) does not fit a workspace sized for a shorter problem."""
+    f = tmp_path / "tune"
+    f.write_text("0 4 17 1 1 -1\n0 4 18 1 1 -1\n")   # (the same slices for both lengths)
+    S = torch.randn(1000, 400000, device="cuda", generator=torch.Generator(device="cuda").manual_seed(5)) / 400000 ** 0.5
+    v = torch.randn(400000, device="cuda")
+    kw = dict(gram_prec=dfl.DFISHER_GRAM_FP32, sweeps=3, x_fp64=True)
+    xs, names = [], []
+    for held in (True, False):
+        ctx = dfl.dfisher_ctx_create(0)
+        dfl.dfisher_ctx_enable_graphs(ctx, False)
+        dfl.dfisher_ctx_load_tuning(ctx, str(f))
+        if held:
+            dfl.dfisher_solve_uneven(ctx, [S[:, :200000].contiguous()], [v[:200000].contiguous()], [0.1], **kw)
+            graph = hold(ctx)
+        names.append(kernels(lambda: xs.append(dfl.dfisher_solve_uneven(ctx, [S], [v], [0.1], **kw)[0][0])))
+    assert "potf2_kernel" in names[0] and "mirror_kernel" in names[0] and "chol_kernel" not in names[0]
+    assert "chol_kernel" in names[1] and "potf2_kernel" not in names[1]
+    assert float((xs[0] - xs[1]).abs().max() / xs[1].abs().max()) <= 1e-11
+    del graph
