@@ -168,11 +168,11 @@ GRAM_KERNEL = {"fp32": "gram_kernel_v2", "bf16x3": "gram_kernel_split", "mxfp8":
 # valid only for the kernel source they were taken on (sha256 of csrc/gram.hip); see profiles/.
 GRAM_TRAFFIC = {
     ("mxfp8", 4096, 4_000_000): {
-        "gram_hip_sha256": "454000540df86551ca60627f02d9e75ea906bf9985d082f61d3dbcb044930056",
+        "gram_hip_sha256": "f61b81222d3e4ee92696b6aecc482295eaadea7f838435eff187dc0ed1edf2c1",
         # FETCH_SIZE x 2 + WRITE_SIZE x 1 (KiB -> bytes), mean of 12 launches in the latest pair of
         # counter runs; the re-reads vary from box to box and run to run (75.8 to 116.5 GB over
-        # five pairs)
-        "bytes_per_launch": 109.66e9 + 0.51e9,
+        # six pairs)
+        "bytes_per_launch": 78.97e9 + 1.08e9,
     },
 }
 

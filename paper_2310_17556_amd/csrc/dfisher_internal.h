@@ -172,7 +172,7 @@ hipError_t refine_line_grouped_launch(const LineJob* jobs_dev, int njobs, int nc
                                       hipStream_t st);
 // The same step for many problems in one launch, the jobs by value; job k owns workgroups [blk0[k], blk0[k + 1]). (A launch and
 // its gap cost as much as a small step, and a large one alone ends with part of the chip idle: 24 problems of 5.9 GB, row passes
-// 2065 -> 1530 us, the small steps 1400 -> 400, the whole call 9.2 -> 7.9 ms with 97 launches instead of 429.)
+// 2065 -> 1530 us, the small steps 1400 -> 400, the whole call 9.2 -> 7.9 ms, 7.5 now, with 97 launches instead of 429.)
 template <class J>
 struct JobList {
   static constexpr int CAP = (int)(3584 / (sizeof(J) + sizeof(int64_t)));

@@ -1100,7 +1100,7 @@ RefinePassPlan refine_pass_plan(int64_t n, int64_t m, int64_t lds, const float* 
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
-  // (Rows that are not 16-byte aligned: 1000 x 99999 117 us, where a column and a row pass of their own took 213.)
+  // (Rows that are not 16-byte aligned: 1000 x 99999 117 us; a column and a row pass of their own 155.)
   // whole-line kernels (32-column blocks): one workgroup per block for n <= 2048; rows split over a
   // pair of workgroups for 2048 < n <= 4096 when every compute unit holds one workgroup and the
   // pairs fit the XCD layout
